@@ -216,3 +216,39 @@ def test_tiles_match_oracle():
         ref = cnn.candidate_tile(bw[wi], stats, int(e["dm_idx"]), int(e["t_peak"]),
                                  fb.widths[wi], ndm, nbx)
         assert (got[k] == ref).all(), k
+
+
+@pytest.mark.parametrize("nout", [4001, 70003])
+def test_tiles_widths_of_every_lane_group(nout):
+    """Windows read by 1 to 64 lanes, in single samples (w not a multiple of
+    8) and in 16-byte pieces, with more pieces than lanes, rows of odd length
+    (every alignment) and columns past the last position: equal to the
+    oracle's tiles bit for bit."""
+    from paper_1112_0065_amd import _lib as L
+    torch = torch_dev()
+    widths = [1, 2, 3, 5, 8, 12, 16, 24, 31, 40, 64, 100, 128, 136, 200, 256, 300, 512, 520, 1000]
+    ndm = 67
+    rng = np.random.default_rng(nout)
+    out = rng.integers(0, 3073, size=(ndm, nout)).astype(np.int64)
+    nbx = nout - widths[-1] + 1
+    series = to_dev(out.astype(np.uint16).view(np.int16))
+    pws = torch.empty(L.find_peaks_workspace_bytes(ndm, nout, widths), dtype=torch.uint8, device="cuda")
+    evb = torch.empty(40 << 16, dtype=torch.uint8, device="cuda")
+    L.find_peaks(series, ndm, nout, widths, 6.0, evb, 1 << 16, pws)
+    ev = np.zeros(2 * len(widths), dtype=L.EVENT_DTYPE)
+    ev["width_idx"] = np.arange(len(ev)) % len(widths)
+    ev["dm_idx"] = rng.integers(0, ndm, size=len(ev))
+    ev["t_peak"] = rng.integers(0, nbx, size=len(ev))
+    ev["t_peak"][:3] = [0, nbx - 1, nbx // 2]
+    tiles = torch.empty((len(ev), 64, 256), dtype=torch.int16, device="cuda")
+    L.triage_tiles(series, ndm, nout, widths, pws, to_dev(ev.view(np.uint8).copy()), len(ev), tiles)
+    got = cnn.bf16_value(tiles.cpu().numpy().view(np.uint16))
+    bw = oracle.boxcar(out, widths)
+    stats = {}
+    for k, e in enumerate(ev):
+        wi = int(e["width_idx"])
+        if wi not in stats:
+            stats[wi] = [oracle.series_stats(bw[wi, d]) for d in range(ndm)]
+        ref = cnn.candidate_tile(bw[wi], stats[wi], int(e["dm_idx"]), int(e["t_peak"]), widths[wi],
+                                 ndm, nbx)
+        assert (got[k] == ref).all(), (k, widths[wi])
