@@ -263,3 +263,29 @@ def test_repack_layout_every_word(nchans, nsamps):
     ref = _planes_reference(oracle.unpack_2bit(packed, nsamps, nchans), nwords)
     bad = np.argwhere(got != ref)
     assert len(bad) == 0, (len(bad), bad[:5].tolist())
+
+
+@pytest.mark.parametrize("nchans,ndm,nout", [
+    (8, 1, 100),         # one stage, one trial
+    (24, 17, 5000),      # odd number of stages; the second DM block holds one trial
+    (520, 41, 2049),     # 65 stages: full buffers, then an odd rest
+    (1368, 40, 3000),    # 16-level counters
+    (64, 128, 32800),    # half an item per CU or more (256 CUs): one block per item
+    (16, 460, 33000),    # just below two items per CU
+    (16, 500, 33000),    # just above: the ordinary kernel
+])
+def test_few_items(nchans, ndm, nout):
+    """Grids with at most two work items per CU take blocks of one trial per
+    wave and deeper stage buffers: equal to the oracle at the edges of their
+    shapes, in both output types."""
+    from paper_1112_0065_amd import _lib as L
+    df = -400.0 / max(nchans, 64)
+    dms = [0.35 * k for k in range(ndm)]
+    dly = oracle.delay_table(nchans, synth.F_TOP, df, synth.TSAMP, dms)
+    nsamps = nout + int(dly.max())
+    fb = synth.make_tiny(nchans + ndm, nchans, nsamps, dms, df=df)
+    p = L.dedisp_plan_create(nchans, fb.f_top, df, fb.tsamp, dms)
+    ref = oracle.dedisperse(oracle.unpack_2bit(fb.packed, nsamps, nchans), dly)
+    for dtype in (torch_dev().int32, torch_dev().int16):
+        got = _run(p, fb.packed, nsamps, dtype)
+        assert got.shape == ref.shape and (got == ref).all(), dtype
