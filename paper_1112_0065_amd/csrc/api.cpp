@@ -274,14 +274,14 @@ dedisp_status find_peaks_impl(const void* in, dedisp_out_type in_type, int32_t n
     const dd::PeaksWs ws = dd::peaks_ws(workspace, lay);
     const int u16 = in_type == DEDISP_OUT_U16;
     DD_HIP(dd::launch_peaks_count(in, u16, ndm, nout, W, lay, ws, kmant, kexp2, stream));
+    // the write pass works through a list on the device (none: its blocks end
+    // at once), so it needs no count on the host and one wait serves both
+    if (capacity > 0)
+        DD_HIP(dd::launch_peaks_write(in, u16, ndm, nout, W, lay, ws, events, capacity, stream));
     int64_t total = 0;
     DD_HIP(hipMemcpyAsync(&total, ws.total, sizeof total, hipMemcpyDeviceToHost, stream));
     DD_HIP(hipStreamSynchronize(stream));
     *n_events = total;
-    if (total > 0 && capacity > 0) {
-        DD_HIP(dd::launch_peaks_write(in, u16, ndm, nout, W, lay, ws, events, capacity, stream));
-        DD_HIP(hipStreamSynchronize(stream));
-    }
     if (total > capacity)
         return fail(DEDISP_ERR_CAPACITY, "%lld events found, capacity %lld",
                     static_cast<long long>(total), static_cast<long long>(capacity));

@@ -16,7 +16,8 @@
 //
 // Events (section 2.3: each maximal run of above-cut samples of one series
 // is one event) are compacted deterministically: count run starts per
-// (width, DM, segment), exclusive scan, then write each event at its offset
+// (width, DM, segment) and per series, exclusive scan over the series, then
+// write each event at its series' slot plus the counts of the segments before
 // -- the output order is (width, DM, t_start) without any sort.  Only the
 // (DM, segment)s whose largest boxcar reaches the cut are counted, and only
 // those with events are written: both passes work through lists of them.
@@ -31,11 +32,15 @@
 namespace {
 
 constexpr int kThreads = 256;
+// Threads per block of the list-driven count and write passes (see
+// few_segments).
+constexpr int kFewThreads = 1024;
 // ----------------------------------------------------------------------------
 // Block-level helpers.
 // ----------------------------------------------------------------------------
 
 // Exclusive prefix of one value per thread over the block (uint32, modular).
+template <int NT = kThreads>
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* wave_tot) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     uint32_t x = v;
@@ -47,7 +52,15 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* w
     if (lane == 63) wave_tot[wave] = x;
     __syncthreads();
     uint32_t base = 0;
-    for (int i = 0; i < wave; ++i) base += wave_tot[i];
+    if (NT <= 256) {
+        for (int i = 0; i < wave; ++i) base += wave_tot[i];
+    } else {
+        // the totals of the waves before this one, one per lane
+        uint32_t t = lane < wave ? wave_tot[lane] : 0u;
+#pragma unroll
+        for (int o = 1; o < NT / 64; o <<= 1) t += static_cast<uint32_t>(__shfl_xor(static_cast<int>(t), o, NT / 64));
+        base = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(t)));
+    }
     __syncthreads();
     return base + x - v;
 }
@@ -70,7 +83,7 @@ __device__ __forceinline__ uint32_t row_load(__amdgpu_buffer_rsrc_t rs, int byte
     return __builtin_amdgcn_raw_buffer_load_b32(rs, byte_off, 0, 0);
 }
 
-template <typename T>
+template <int NT = kThreads, typename T>
 __device__ void load_prefix(const T* __restrict__ row, int64_t nout, int64_t first, int n,
                             uint32_t* pl, uint32_t* wave_tot, uint32_t* vmax = nullptr) {
     // coalesced load of the raw values into pl[1..n); the launchers keep a
@@ -82,15 +95,15 @@ __device__ void load_prefix(const T* __restrict__ row, int64_t nout, int64_t fir
     // full batches (every index below n - 1) store without checks; the last,
     // partial one checks each index
     int base = threadIdx.x;
-    for (; base + (kBatch - 1) * kThreads < n - 1; base += kBatch * kThreads) {
+    for (; base + (kBatch - 1) * NT < n - 1; base += kBatch * NT) {
         uint32_t v[kBatch];
 #pragma unroll
         for (int k = 0; k < kBatch; ++k)
-            v[k] = row_load(rs, off0 + (base + k * kThreads) * static_cast<int>(sizeof(T)),
+            v[k] = row_load(rs, off0 + (base + k * NT) * static_cast<int>(sizeof(T)),
                             static_cast<T*>(nullptr));
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
-            pl[base + k * kThreads + 1] = v[k];
+            pl[base + k * NT + 1] = v[k];
             m = max(m, v[k]);
         }
     }
@@ -98,12 +111,12 @@ __device__ void load_prefix(const T* __restrict__ row, int64_t nout, int64_t fir
         uint32_t v[kBatch];
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
-            const int i = base + k * kThreads;
+            const int i = base + k * NT;
             v[k] = row_load(rs, off0 + i * static_cast<int>(sizeof(T)), static_cast<T*>(nullptr));
         }
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) {
-            const int i = base + k * kThreads;
+            const int i = base + k * NT;
             if (i < n - 1) {
                 pl[i + 1] = v[k];
                 m = max(m, v[k]);
@@ -119,7 +132,7 @@ __device__ void load_prefix(const T* __restrict__ row, int64_t nout, int64_t fir
     // *vmax; the barrier at the end orders them before its readers
     if (vmax && (threadIdx.x & 63) == 0) atomicMax(vmax, m);
     // each thread scans a contiguous chunk (odd chunk stride: no bank conflicts)
-    const int chunk = (((n - 1) + kThreads - 1) / kThreads) | 1;
+    const int chunk = (((n - 1) + NT - 1) / NT) | 1;
     const int lo = 1 + threadIdx.x * chunk;
     const int hi = min(n, lo + chunk);
     // full batches without checks, then one checked remainder batch
@@ -139,7 +152,7 @@ __device__ void load_prefix(const T* __restrict__ row, int64_t nout, int64_t fir
 #pragma unroll
         for (int k = 0; k < kBatch; ++k) sum += v[k];
     }
-    const uint32_t scan_base = block_exclusive_scan(sum, wave_tot);
+    const uint32_t scan_base = block_exclusive_scan<NT>(sum, wave_tot);
     uint32_t run = scan_base;
     for (int i0 = lo; i0 < full_end; i0 += kBatch) {
         uint32_t v[kBatch];
@@ -697,6 +710,7 @@ __global__ __launch_bounds__(kThreads) void series_threshold_kernel(int nseries,
     }
     if (t >= ns) return;
     const int s = s0 + t;
+    ws.tot[s] = 0u;     // the count pass adds the segments' run starts
     ws.s1[s] = s1;
     ws.s2lo[s] = static_cast<uint64_t>(s2);
     ws.s2hi[s] = static_cast<uint64_t>(s2 >> 64);
@@ -721,6 +735,7 @@ __global__ __launch_bounds__(kThreads) void mark_kernel(int ndm, int nseg, int n
     if (idx >= static_cast<int64_t>(ndm) * nseg) return;
     const int d = static_cast<int>(idx / nseg);
     bool any = false;
+#pragma unroll 4
     for (int wi = 0; wi < nw; ++wi)
         any |= ws.part_max[static_cast<int64_t>(wi) * ndm * nseg + idx] >= ws.thr32[wi * ndm + d];
     if (any) {
@@ -733,13 +748,13 @@ __global__ __launch_bounds__(kThreads) void mark_kernel(int ndm, int nseg, int n
 // Pass 3b: number of run starts per (width, DM, segment) of the listed
 // segments (a fixed grid of blocks works through the list).  Segments with
 // any start go on the write list.
-template <typename T>
-__global__ __launch_bounds__(kThreads) void peaks_count_kernel(const T* __restrict__ in, int ndm,
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void peaks_count_kernel(const T* __restrict__ in, int ndm,
                                                                int64_t nout, int64_t nbx,
                                                                dd::Widths W, int L, int nseg,
                                                                dd::PeaksWs ws) {
     extern __shared__ uint32_t pl[];
-    __shared__ uint32_t wave_tot[kThreads / 64];
+    __shared__ uint32_t wave_tot[NT / 64];
     __shared__ uint32_t cnt[dd::kMaxWidths];
     const uint32_t nitems = ws.nlist[0];
     const int lane = threadIdx.x & 63;
@@ -750,17 +765,17 @@ __global__ __launch_bounds__(kThreads) void peaks_count_kernel(const T* __restri
         const int64_t s0 = static_cast<int64_t>(seg) * L;
         const int n = L + W.w[W.n - 1] + 1;
         if (threadIdx.x < dd::kMaxWidths) cnt[threadIdx.x] = 0;
-        load_prefix(in + static_cast<int64_t>(d) * nout, nout, s0 - 1, n, pl, wave_tot);
+        load_prefix<NT>(in + static_cast<int64_t>(d) * nout, nout, s0 - 1, n, pl, wave_tot);
         const int npos = static_cast<int>(min<int64_t>(L, nbx - s0));
         for (int wi = 0; wi < W.n; ++wi) {
             const uint32_t thr = ws.thr32[wi * ndm + d];
             if (ws.part_max[(static_cast<int64_t>(wi) * ndm + d) * nseg + seg] < thr) continue;
             const int w = W.w[wi];
             uint32_t c = 0;
-            for (int i0 = threadIdx.x; i0 < npos; i0 += 4 * kThreads) {
+            for (int i0 = threadIdx.x; i0 < npos; i0 += 4 * NT) {
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const int i = i0 + k * kThreads;
+                    const int i = i0 + k * NT;
                     if (i < npos) {
                         const bool above = pl[i + 1 + w] - pl[i + 1] >= thr;
                         const bool prev = (s0 + i > 0) && (pl[i + w] - pl[i] >= thr);
@@ -773,8 +788,12 @@ __global__ __launch_bounds__(kThreads) void peaks_count_kernel(const T* __restri
             if (lane == 0 && c) atomicAdd(&cnt[wi], c);
         }
         __syncthreads();
-        if (threadIdx.x < W.n)
-            ws.counts[(static_cast<int64_t>(threadIdx.x) * ndm + d) * nseg + seg] = cnt[threadIdx.x];
+        if (threadIdx.x < W.n) {
+            const int64_t series = static_cast<int64_t>(threadIdx.x) * ndm + d;
+            ws.counts[series * nseg + seg] = cnt[threadIdx.x];
+            // (a series of one segment: its count is its total)
+            if (nseg > 1 && cnt[threadIdx.x]) atomicAdd(&ws.tot[series], cnt[threadIdx.x]);
+        }
         if (threadIdx.x == 0) {
             uint32_t tot = 0;
             for (int wi = 0; wi < W.n; ++wi) tot += cnt[wi];
@@ -842,6 +861,48 @@ __global__ __launch_bounds__(kThreads) void scan_add_kernel(int64_t* __restrict_
                                                             const int64_t* __restrict__ chunk_tot) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
     if (i < n) offs[i] += chunk_tot[i / kScanChunk];
+}
+
+// Exclusive scan of the series' event counts into their first slots, and the
+// total, by one block: kSeriesScan series per step, four per thread (64-bit
+// sums).
+constexpr int kScanThreads = 1024;
+constexpr int kSeriesScan = 4 * kScanThreads;
+__global__ __launch_bounds__(kScanThreads) void scan_series_kernel(const uint32_t* __restrict__ tot,
+                                                                   int n, int64_t* __restrict__ soff,
+                                                                   int64_t* __restrict__ total) {
+    __shared__ int64_t wave_tot[kScanThreads / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int64_t carry = 0;
+    for (int base = 0; base < n; base += kSeriesScan) {
+        const int i = base + 4 * static_cast<int>(threadIdx.x);
+        uint32_t v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = i + k < n ? tot[i + k] : 0u;
+        const int64_t own = static_cast<int64_t>(v[0]) + v[1] + v[2] + v[3];
+        int64_t x = own;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int64_t y = __shfl_up(x, o, 64);
+            if (lane >= o) x += y;
+        }
+        if (lane == 63) wave_tot[wave] = x;
+        __syncthreads();
+        int64_t ex = carry + x - own;
+#pragma unroll
+        for (int w = 0; w < kScanThreads / 64; ++w) {
+            const int64_t t = wave_tot[w];
+            if (w < wave) ex += t;
+            carry += t;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            if (i + k < n) soff[i + k] = ex;
+            ex += v[k];
+        }
+        __syncthreads();   // the next step rewrites wave_tot
+    }
+    if (threadIdx.x == 0) *total = carry;
 }
 
 // Walk the run that starts at t with boxcar value b and write its event
@@ -996,7 +1057,7 @@ __device__ __forceinline__ void write_event_wave(const T* __restrict__ row, int6
 constexpr int kMaxStarts = 1024;
 
 // The events of one listed (DM, segment).
-template <typename T>
+template <int NT, typename T>
 __device__ __forceinline__ void write_segment(const T* __restrict__ in, int ndm, int64_t nout, int64_t nbx,
                               const dd::Widths& W, int L, int nseg, const dd::PeaksWs& ws,
                               dedisp_event* __restrict__ events, int64_t capacity, int d, int seg,
@@ -1007,7 +1068,7 @@ __device__ __forceinline__ void write_segment(const T* __restrict__ in, int ndm,
     const int64_t s0 = static_cast<int64_t>(seg) * L;
     const int n = L + W.w[W.n - 1] + 1;
     const T* row = in + static_cast<int64_t>(d) * nout;
-    load_prefix(row, nout, s0 - 1, n, pl, wave_tot);
+    load_prefix<NT>(row, nout, s0 - 1, n, pl, wave_tot);
     const int npos = static_cast<int>(min<int64_t>(L, nbx - s0));
 
     // Every width at once when all the segment's run starts fit the list:
@@ -1016,6 +1077,16 @@ __device__ __forceinline__ void write_segment(const T* __restrict__ in, int ndm,
     // finds them, and then all runs of all widths are walked concurrently.
     __shared__ uint32_t wb[dd::kMaxWidths + 1], wc[dd::kMaxWidths], wfill[dd::kMaxWidths];
     __shared__ uint32_t wthr[dd::kMaxWidths];
+    __shared__ int64_t woff[dd::kMaxWidths];   // slot of the segment's first event of each width
+    for (int wi = threadIdx.x >> 6; wi < W.n; wi += NT / 64) {
+        // the series' first slot, then the events of its segments before this one
+        const int64_t series = static_cast<int64_t>(wi) * ndm + d;
+        int64_t before = 0;
+        for (int k = threadIdx.x & 63; k < seg; k += 64) before += ws.counts[series * nseg + k];
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
+        if ((threadIdx.x & 63) == 0) woff[wi] = ws.soff[series] + before;
+    }
     if (threadIdx.x < W.n) {
         const int wi = threadIdx.x;
         wc[wi] = ws.counts[(static_cast<int64_t>(wi) * ndm + d) * nseg + seg];
@@ -1039,10 +1110,10 @@ __device__ __forceinline__ void write_segment(const T* __restrict__ in, int ndm,
             if (wc[wi] == 0) continue;
             const int w = W.w[wi];
             const uint32_t thr = wthr[wi];
-            for (int i0 = threadIdx.x; i0 < npos; i0 += 4 * kThreads) {
+            for (int i0 = threadIdx.x; i0 < npos; i0 += 4 * NT) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    const int i = i0 + q * kThreads;
+                    const int i = i0 + q * NT;
                     if (i < npos) {
                         const bool above = pl[i + 1 + w] - pl[i + 1] >= thr;
                         const bool prev = (s0 + i > 0) && (pl[i + w] - pl[i] >= thr);
@@ -1057,7 +1128,7 @@ __device__ __forceinline__ void write_segment(const T* __restrict__ in, int ndm,
         __syncthreads();
         // one run per wave: its rank among its width's starts, then its walk
         const int lane = threadIdx.x & 63;
-        for (uint32_t k = threadIdx.x >> 6; k < total; k += kThreads / 64) {
+        for (uint32_t k = threadIdx.x >> 6; k < total; k += NT / 64) {
             int wi = 0;
             while (wb[wi + 1] <= k) ++wi;
             const int i = starts[k];
@@ -1065,8 +1136,7 @@ __device__ __forceinline__ void write_segment(const T* __restrict__ in, int ndm,
             for (uint32_t q = wb[wi] + lane; q < wb[wi + 1]; q += 64) rank += starts[q] < i;
 #pragma unroll
             for (int o = 32; o >= 1; o >>= 1) rank += __shfl_xor(rank, o, 64);
-            const int64_t cidx = (static_cast<int64_t>(wi) * ndm + d) * nseg + seg;
-            const int64_t e = ws.offs[cidx] + rank;
+            const int64_t e = woff[wi] + rank;
             const int w = W.w[wi];
             const int sidx = wi * ndm + d;
             if (e < capacity)
@@ -1077,20 +1147,19 @@ __device__ __forceinline__ void write_segment(const T* __restrict__ in, int ndm,
     }
 
     for (int wi = 0; wi < W.n; ++wi) {
-        const int64_t cidx = (static_cast<int64_t>(wi) * ndm + d) * nseg + seg;
-        const uint32_t cnt = ws.counts[cidx];
+        const uint32_t cnt = wc[wi];
         if (cnt == 0) continue;
         const int sidx = wi * ndm + d;
         const uint32_t thr = ws.thr32[sidx];
         const int w = W.w[wi];
-        const int64_t off = ws.offs[cidx];
+        const int64_t off = woff[wi];
         const uint64_t s1 = ws.s1[sidx];
         const double sq = ws.sqrt_d[sidx];
         const int lim = n - 1 - w;   // local positions whose boxcar the running sums cover
         if (cnt <= kMaxStarts) {
             if (threadIdx.x == 0) nstart = 0;
             __syncthreads();
-            for (int i = threadIdx.x; i < npos; i += kThreads) {
+            for (int i = threadIdx.x; i < npos; i += NT) {
                 const uint32_t b = pl[i + 1 + w] - pl[i + 1];
                 const bool prev = (s0 + i > 0) && (pl[i + w] - pl[i] >= thr);
                 if (b >= thr && !prev) {
@@ -1100,7 +1169,7 @@ __device__ __forceinline__ void write_segment(const T* __restrict__ in, int ndm,
             }
             __syncthreads();
             const int m = min(nstart, kMaxStarts);
-            for (int k = threadIdx.x; k < m; k += kThreads) {
+            for (int k = threadIdx.x; k < m; k += NT) {
                 const int i = starts[k];
                 int rank = 0;
                 for (int q = 0; q < m; ++q) rank += starts[q] < i;
@@ -1112,7 +1181,7 @@ __device__ __forceinline__ void write_segment(const T* __restrict__ in, int ndm,
             __syncthreads();
         } else {
             int64_t rank = off;
-            for (int base = 0; base < npos; base += kThreads) {
+            for (int base = 0; base < npos; base += NT) {
                 const int i = base + threadIdx.x;
                 bool start = false;
                 uint32_t b = 0;
@@ -1121,11 +1190,11 @@ __device__ __forceinline__ void write_segment(const T* __restrict__ in, int ndm,
                     const bool prev = (s0 + i > 0) && (pl[i + w] - pl[i] >= thr);
                     start = b >= thr && !prev;
                 }
-                const uint32_t ex = block_exclusive_scan(start ? 1u : 0u, wave_tot);
+                const uint32_t ex = block_exclusive_scan<NT>(start ? 1u : 0u, wave_tot);
                 if (start && rank + ex < capacity)
                     write_event(row, nbx, w, wi, d, s0 + i, b, thr, s1, sq, &events[rank + ex], pl, s0,
                                 lim);
-                if (threadIdx.x == kThreads - 1) slab_total = ex + (start ? 1u : 0u);
+                if (threadIdx.x == NT - 1) slab_total = ex + (start ? 1u : 0u);
                 __syncthreads();
                 rank += slab_total;
                 __syncthreads();
@@ -1134,22 +1203,22 @@ __device__ __forceinline__ void write_segment(const T* __restrict__ in, int ndm,
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kThreads) void peaks_write_kernel(const T* __restrict__ in, int ndm,
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void peaks_write_kernel(const T* __restrict__ in, int ndm,
                                                                int64_t nout, int64_t nbx,
                                                                dd::Widths W, int L, int nseg,
                                                                dd::PeaksWs ws,
                                                                dedisp_event* __restrict__ events,
                                                                int64_t capacity) {
     extern __shared__ uint32_t pl[];
-    __shared__ uint32_t wave_tot[kThreads / 64];
+    __shared__ uint32_t wave_tot[NT / 64];
     __shared__ int starts[kMaxStarts];
     __shared__ int nstart;
     __shared__ uint32_t slab_total;
     const uint32_t nitems = ws.nlist[1];
     for (uint32_t item = blockIdx.x; item < nitems; item += gridDim.x) {
         const int64_t idx = ws.list2[item];
-        write_segment(in, ndm, nout, nbx, W, L, nseg, ws, events, capacity,
+        write_segment<NT>(in, ndm, nout, nbx, W, L, nseg, ws, events, capacity,
                       static_cast<int>(idx / nseg), static_cast<int>(idx % nseg), pl, wave_tot,
                       starts, &nstart, &slab_total);
         __syncthreads();   // LDS is reused by the next item
@@ -1167,8 +1236,22 @@ int segment_length(int w_max) {
     return L;
 }
 
-// Blocks of the list-driven count and write passes (a few per CU).
-constexpr int64_t kListBlocks = 2048;
+// The lists hold the few (DM, segment)s with something above the cut, a few
+// per cent of them.  Up to kFewSegments segments in all, that leaves most of
+// the chip idle and a listed segment's own time counts: blocks of kFewThreads
+// (301 series of 100 003 samples, 3913 segments: count 39 -> 26 us, write 47 ->
+// 32; 100 segments: 35 -> 18, 40 -> 20).  With more listed segments than
+// resident blocks the smaller blocks win (74 400 segments: 192 us for both
+// passes, 247 with kFewThreads).
+constexpr int64_t kFewSegments = 32768;
+bool few_segments(int ndm, int nseg) { return static_cast<int64_t>(ndm) * nseg <= kFewSegments; }
+// Waves of the list-driven passes' blocks: 32 per CU.
+constexpr int64_t kListWaves = 8192;
+
+// Series that one block scans (a step of 4096 takes about 3 us: 12 000 series
+// 9.6 us, where scanning the counts of all their segments with three kernels
+// took 25); more take the three-kernel scan.
+constexpr int64_t kOneBlockScan = 16 * kSeriesScan;
 
 size_t peaks_lds_bytes(int L, int w_max) { return static_cast<size_t>(L + w_max + 1) * 4; }
 
@@ -1315,7 +1398,8 @@ PeaksWs peaks_ws(void* base, const PeaksLayout& lay) {
     ws.thr32 = reinterpret_cast<uint32_t*>(b + lay.o_thr32);
     ws.sqrt_d = reinterpret_cast<double*>(b + lay.o_sqrt_d);
     ws.counts = reinterpret_cast<uint32_t*>(b + lay.o_counts);
-    ws.offs = reinterpret_cast<int64_t*>(b + lay.o_offs);
+    ws.soff = reinterpret_cast<int64_t*>(b + lay.o_offs);
+    ws.tot = lay.nseg > 1 ? reinterpret_cast<uint32_t*>(ws.soff + lay.nseries) : ws.counts;
     ws.chunk_tot = reinterpret_cast<int64_t*>(b + lay.o_chunk);
     ws.total = reinterpret_cast<int64_t*>(b + lay.o_total);
     ws.list = reinterpret_cast<uint32_t*>(b + lay.o_list);
@@ -1337,6 +1421,42 @@ hipError_t launch_scan_u32(const uint32_t* counts, int64_t n, int64_t* offs, int
 
 int64_t scan_chunk_count(int64_t n) { return (n + kScanChunk - 1) / kScanChunk; }
 
+template <typename T, int NT>
+void launch_count_nt(const T* in, int ndm, int64_t nout, const Widths& W, const PeaksLayout& lay,
+                     const PeaksWs& ws, size_t lds, hipStream_t s) {
+    const int64_t nblk = std::min<int64_t>(static_cast<int64_t>(ndm) * lay.nseg, kListWaves * 64 / NT);
+    set_lds_limit(reinterpret_cast<const void*>(peaks_count_kernel<T, NT>), lds);
+    hipLaunchKernelGGL((peaks_count_kernel<T, NT>), dim3(static_cast<unsigned>(nblk)), dim3(NT), lds, s, in,
+                       ndm, nout, lay.nbx, W, lay.L, lay.nseg, ws);
+}
+
+template <typename T>
+void launch_count(const T* in, int ndm, int64_t nout, const Widths& W, const PeaksLayout& lay,
+                  const PeaksWs& ws, size_t lds, hipStream_t s) {
+    if (few_segments(ndm, lay.nseg))
+        launch_count_nt<T, kFewThreads>(in, ndm, nout, W, lay, ws, lds, s);
+    else
+        launch_count_nt<T, kThreads>(in, ndm, nout, W, lay, ws, lds, s);
+}
+
+template <typename T, int NT>
+void launch_write_nt(const T* in, int ndm, int64_t nout, const Widths& W, const PeaksLayout& lay,
+                     const PeaksWs& ws, dedisp_event* events, int64_t capacity, size_t lds, hipStream_t s) {
+    const int64_t nblk = std::min<int64_t>(static_cast<int64_t>(ndm) * lay.nseg, kListWaves * 64 / NT);
+    set_lds_limit(reinterpret_cast<const void*>(peaks_write_kernel<T, NT>), lds);
+    hipLaunchKernelGGL((peaks_write_kernel<T, NT>), dim3(static_cast<unsigned>(nblk)), dim3(NT), lds, s, in,
+                       ndm, nout, lay.nbx, W, lay.L, lay.nseg, ws, events, capacity);
+}
+
+template <typename T>
+void launch_write(const T* in, int ndm, int64_t nout, const Widths& W, const PeaksLayout& lay,
+                  const PeaksWs& ws, dedisp_event* events, int64_t capacity, size_t lds, hipStream_t s) {
+    if (few_segments(ndm, lay.nseg))
+        launch_write_nt<T, kFewThreads>(in, ndm, nout, W, lay, ws, events, capacity, lds, s);
+    else
+        launch_write_nt<T, kThreads>(in, ndm, nout, W, lay, ws, events, capacity, lds, s);
+}
+
 hipError_t launch_peaks_count(const void* in, int in_u16, int ndm, int64_t nout, const Widths& W,
                               const PeaksLayout& lay, const PeaksWs& ws, uint32_t kmant, int kexp2,
                               hipStream_t s) {
@@ -1353,26 +1473,17 @@ hipError_t launch_peaks_count(const void* in, int in_u16, int ndm, int64_t nout,
     const int64_t nblk = static_cast<int64_t>(ndm) * lay.nseg;
     hipLaunchKernelGGL(mark_kernel, dim3(static_cast<unsigned>((nblk + kThreads - 1) / kThreads)),
                        dim3(kThreads), 0, s, ndm, lay.nseg, W.n, ws);
-    const dim3 wgrid(static_cast<unsigned>(std::min<int64_t>(nblk, kListBlocks)));
-    if (in_u16) {
-        set_lds_limit(reinterpret_cast<const void*>(peaks_count_kernel<uint16_t>), lds);
-        hipLaunchKernelGGL(peaks_count_kernel<uint16_t>, wgrid, dim3(kThreads), lds, s,
-                           static_cast<const uint16_t*>(in), ndm, nout, lay.nbx, W, lay.L, lay.nseg,
-                           ws);
-    } else {
-        set_lds_limit(reinterpret_cast<const void*>(peaks_count_kernel<int32_t>), lds);
-        hipLaunchKernelGGL(peaks_count_kernel<int32_t>, wgrid, dim3(kThreads), lds, s,
-                           static_cast<const int32_t*>(in), ndm, nout, lay.nbx, W, lay.L, lay.nseg,
-                           ws);
-    }
+    if (in_u16)
+        launch_count(static_cast<const uint16_t*>(in), ndm, nout, W, lay, ws, lds, s);
+    else
+        launch_count(static_cast<const int32_t*>(in), ndm, nout, W, lay, ws, lds, s);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(scan_chunks_kernel, dim3(lay.nchunks), dim3(kThreads), 0, s, ws.counts,
-                       lay.ncounts, ws.offs, ws.chunk_tot);
-    hipLaunchKernelGGL(scan_totals_kernel, dim3(1), dim3(kThreads), 0, s, ws.chunk_tot, lay.nchunks, ws.total);
-    hipLaunchKernelGGL(scan_add_kernel, dim3(static_cast<unsigned>((lay.ncounts + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, s, ws.offs, lay.ncounts, ws.chunk_tot);
-    return hipGetLastError();
+    if (lay.nseries <= kOneBlockScan) {
+        hipLaunchKernelGGL(scan_series_kernel, dim3(1), dim3(kScanThreads), 0, s, ws.tot, nser, ws.soff, ws.total);
+        return hipGetLastError();
+    }
+    return launch_scan_u32(ws.tot, lay.nseries, ws.soff, ws.chunk_tot, ws.total, s);
 }
 
 hipError_t launch_peaks_write(const void* in, int in_u16, int ndm, int64_t nout, const Widths& W,
@@ -1380,19 +1491,10 @@ hipError_t launch_peaks_write(const void* in, int in_u16, int ndm, int64_t nout,
                               int64_t capacity, hipStream_t s) {
     const int w_max = W.w[W.n - 1];
     const size_t lds = peaks_lds_bytes(lay.L, w_max);
-    const dim3 grid(static_cast<unsigned>(
-        std::min<int64_t>(static_cast<int64_t>(ndm) * lay.nseg, kListBlocks)));
-    if (in_u16) {
-        set_lds_limit(reinterpret_cast<const void*>(peaks_write_kernel<uint16_t>), lds);
-        hipLaunchKernelGGL(peaks_write_kernel<uint16_t>, grid, dim3(kThreads), lds, s,
-                           static_cast<const uint16_t*>(in), ndm, nout, lay.nbx, W, lay.L, lay.nseg,
-                           ws, events, capacity);
-    } else {
-        set_lds_limit(reinterpret_cast<const void*>(peaks_write_kernel<int32_t>), lds);
-        hipLaunchKernelGGL(peaks_write_kernel<int32_t>, grid, dim3(kThreads), lds, s,
-                           static_cast<const int32_t*>(in), ndm, nout, lay.nbx, W, lay.L, lay.nseg,
-                           ws, events, capacity);
-    }
+    if (in_u16)
+        launch_write(static_cast<const uint16_t*>(in), ndm, nout, W, lay, ws, events, capacity, lds, s);
+    else
+        launch_write(static_cast<const int32_t*>(in), ndm, nout, W, lay, ws, events, capacity, lds, s);
     return hipGetLastError();
 }
 

@@ -32,7 +32,8 @@ struct PeaksWs {
     uint32_t* thr32;       // [nw][ndm], 0xFFFFFFFF: nothing can pass
     double* sqrt_d;        // [nw][ndm]
     uint32_t* counts;      // [nw][ndm][nseg] run starts
-    int64_t* offs;         // [nw][ndm][nseg] exclusive scan of counts
+    uint32_t* tot;         // [nw][ndm] run starts of the series (the counts themselves when nseg == 1)
+    int64_t* soff;         // [nw][ndm] exclusive scan of tot: the series' first event slot
     int64_t* chunk_tot;    // scan scratch
     int64_t* total;        // total number of events
     uint32_t* list;        // [ndm * nseg] (DM, segment)s to count (d * nseg + seg)

@@ -287,3 +287,21 @@ def test_find_peaks_uint16_window_loads(nout):
     ev, (g1, g2, gt) = _find(series, widths, 6.0, True)
     assert (g1 == s1).all() and (g2 == s2).all() and (gt == thr).all()
     events_equal(ev, ref)
+
+
+@pytest.mark.parametrize("ndm,nout,nw", [
+    (5, 700, 4),         # one segment per series: its count is the series' total
+    (1300, 9001, 4),     # two segments; two steps of the one-block series scan
+    (2100, 90, 32),      # 67 200 series: more than one block scans
+])
+def test_event_slots_over_series_and_segments(ndm, nout, nw):
+    """Every event lands in its slot whatever scans the series' counts and
+    however many segments come before its own in the series."""
+    rng = np.random.default_rng(ndm)
+    series = rng.integers(0, 40, size=(ndm, nout)).astype(np.int64)
+    series[rng.integers(ndm, size=ndm // 2), rng.integers(nout, size=ndm // 2)] += 200
+    widths = list(range(1, nw + 1))
+    ref = oracle.find_events(oracle.boxcar(series, widths), 4.0)
+    for u16 in (False, True):
+        ev, _ = _find(series, widths, 4.0, u16, capacity=1 << 19)
+        events_equal(ev, ref)
