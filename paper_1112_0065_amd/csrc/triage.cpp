@@ -28,13 +28,12 @@ namespace {
 constexpr char kMagic[8] = {'T', 'R', 'I', 'A', 'G', 'E', '0', '1'};
 
 void free_acts(tk::Net& n) {
-    void* ptrs[] = {n.a[0], n.a[1], n.a[2], n.a[3], n.p[0], n.p[1], n.p[2], n.p[3], n.idx[0], n.idx[1],
-                    n.idx[2], n.idx[3], n.g, n.logits, n.dlogit, n.dp, n.dz, n.part, n.red, n.scores};
+    void* ptrs[] = {n.p[0], n.p[1], n.p[2], n.p[3], n.idx[0], n.idx[1], n.idx[2], n.idx[3], n.zc[0], n.zc[1],
+                    n.zc[2], n.zc[3], n.g, n.logits, n.dlogit, n.part, n.red, n.scores};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
-    for (int l = 0; l < 4; ++l) n.a[l] = n.p[l] = nullptr, n.idx[l] = nullptr;
-    n.g = n.logits = n.dlogit = n.dp = n.part = n.red = n.scores = nullptr;
-    n.dz = nullptr;
+    for (int l = 0; l < 4; ++l) n.p[l] = n.zc[l] = nullptr, n.idx[l] = nullptr;
+    n.g = n.logits = n.dlogit = n.part = n.red = n.scores = nullptr;
     n.cap = 0;
 }
 
@@ -42,25 +41,22 @@ void free_acts(tk::Net& n) {
 hipError_t ensure_cap(tk::Net& n, int cap) {
     if (cap <= n.cap) return hipSuccess;
     free_acts(n);
-    const int Hs[4] = {64, 32, 16, 8}, Ws[4] = {256, 128, 64, 32};
     hipError_t e = hipSuccess;
     const size_t N = static_cast<size_t>(cap);
     for (int l = 0; l < 4 && e == hipSuccess; ++l) {
-        const size_t full = N * Hs[l] * Ws[l] * tk::kCH, half = full / 4;
-        e = hipMalloc(&n.a[l], full * 2);
-        if (e == hipSuccess) e = hipMalloc(&n.p[l], half * 2);
-        if (e == hipSuccess) e = hipMalloc(&n.idx[l], half);
+        const size_t px = N * (32 >> l) * (128 >> l);   // pooled pixels
+        e = hipMalloc(&n.p[l], px * tk::kCH * 2);
+        if (e == hipSuccess) e = hipMalloc(&n.idx[l], px * sizeof(uint2));
+        if (e == hipSuccess) e = hipMalloc(&n.zc[l], px * tk::kCH * 2);
     }
-    const size_t parts = std::max<size_t>(N * 64 / tk::kRowsPerBlock * 320,
-                                          N * 32 / tk::kRowsPerBlock * 9 * tk::kCH * tk::kCH);
+    size_t parts = 0;
+    for (int l = 0; l < 4; ++l) parts += static_cast<size_t>(tk::kMaxParts[l]) * (l == 0 ? tk::kPart1 : tk::kPart32);
     if (e == hipSuccess) e = hipMalloc(&n.g, N * tk::kCH * 4);
     if (e == hipSuccess) e = hipMalloc(&n.logits, N * 4);
     if (e == hipSuccess) e = hipMalloc(&n.dlogit, N * 4);
     if (e == hipSuccess) e = hipMalloc(&n.scores, N * 4);
-    if (e == hipSuccess) e = hipMalloc(&n.dp, N * 32 * 128 * tk::kCH * 4);
-    if (e == hipSuccess) e = hipMalloc(&n.dz, N * 64 * 256 * tk::kCH * 2);
     if (e == hipSuccess) e = hipMalloc(&n.part, parts * 4);
-    if (e == hipSuccess) e = hipMalloc(&n.red, static_cast<size_t>(tk::kRedSlices) * 9 * tk::kCH * tk::kCH * 4);
+    if (e == hipSuccess) e = hipMalloc(&n.red, static_cast<size_t>(tk::kRedSlices) * tk::kPartAll * 4);
     if (e == hipSuccess) n.cap = cap;
     return e;
 }
@@ -68,7 +64,7 @@ hipError_t ensure_cap(tk::Net& n, int cap) {
 void free_model(triage_model_s* m) {
     free_acts(m->net);
     void* ptrs[] = {m->net.master, m->net.grad, m->net.m, m->net.v, m->net.w1b, m->net.wfwd, m->net.wdg,
-                    m->net.loss, m->net.dtap, m->net.bad, m->tiles};
+                    m->net.loss, m->net.bad, m->tiles};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     delete m;
@@ -147,7 +143,6 @@ extern "C" dedisp_status triage_create(const char* weights_path, uint64_t seed, 
     if (e == hipSuccess) e = hipMalloc(&m->net.wfwd, 3 * per * 2);
     if (e == hipSuccess) e = hipMalloc(&m->net.wdg, 3 * per * 2);
     if (e == hipSuccess) e = hipMalloc(&m->net.loss, 4);
-    if (e == hipSuccess) e = hipMalloc(&m->net.dtap, 9 * 32 * 32 * 4);
     if (e == hipSuccess) e = hipMalloc(&m->net.bad, 4);
     if (e != hipSuccess) {
         free_model(m);
@@ -193,9 +188,7 @@ extern "C" dedisp_status triage_forward(triage_model m, const uint16_t* tiles_bf
     if (!m || !tiles_bf16 || n < 1) return fail(DEDISP_ERR_INVALID_ARG, "bad forward arguments");
     std::lock_guard<std::mutex> g(m->mu);
     DD_HIP(ensure_cap(m->net, n));
-    DD_HIP(tk::launch_forward(m->net, tiles_bf16, n, stream));
-    if (logits) DD_HIP(hipMemcpyAsync(logits, m->net.logits, n * 4, hipMemcpyDeviceToDevice, stream));
-    if (scores) DD_HIP(tk::launch_sigmoid(m->net.logits, n, scores, stream));
+    DD_HIP(tk::launch_forward(m->net, tiles_bf16, n, logits, scores, stream));
     return DEDISP_OK;
 }
 
@@ -211,7 +204,7 @@ extern "C" dedisp_status triage_forward_backward(triage_model m, const uint16_t*
     if (!m || !tiles_bf16 || !labels || n < 1) return fail(DEDISP_ERR_INVALID_ARG, "bad arguments");
     std::lock_guard<std::mutex> g(m->mu);
     DD_HIP(ensure_cap(m->net, n));
-    DD_HIP(tk::launch_forward(m->net, tiles_bf16, n, stream));
+    DD_HIP(tk::launch_forward(m->net, tiles_bf16, n, nullptr, nullptr, stream));
     DD_HIP(tk::launch_backward(m->net, tiles_bf16, labels, n, stream));
     if (loss) {
         DD_HIP(hipMemcpyAsync(loss, m->net.loss, 4, hipMemcpyDeviceToHost, stream));
@@ -295,11 +288,10 @@ dedisp_status triage_score_events(triage_model m, const void* series_u16, const 
         }
         dedisp_status st = triage_tiles(series_u16, ndm, nout, w.data(), W.n, pk_ws, d_events + b0, nb, m->tiles, s);
         if (st != DEDISP_OK) return st;
-        st = triage_forward(m, m->tiles, nb, nullptr, nullptr, s);
-        if (st != DEDISP_OK) return st;
         {
             std::lock_guard<std::mutex> g(m->mu);
-            DD_HIP(tk::launch_sigmoid(m->net.logits, nb, m->net.scores, s));
+            DD_HIP(ensure_cap(m->net, nb));
+            DD_HIP(tk::launch_forward(m->net, m->tiles, nb, nullptr, m->net.scores, s));
             DD_HIP(hipMemcpyAsync(scores->data() + b0, m->net.scores, nb * 4, hipMemcpyDeviceToHost, s));
             DD_HIP(hipStreamSynchronize(s));
         }

@@ -252,3 +252,51 @@ def test_tiles_widths_of_every_lane_group(nout):
         ref = cnn.candidate_tile(bw[wi], stats[wi], int(e["dm_idx"]), int(e["t_peak"]), widths[wi],
                                  ndm, nbx)
         assert (got[k] == ref).all(), (k, widths[wi])
+
+
+@pytest.mark.parametrize("n,shift", [(1, 0), (11, 1)])
+def test_forward_backward_small_batches_any_alignment(n, shift):
+    """One tile, and an odd number of them 2 bytes off word alignment: logits
+    and gradients against the oracle, bounds as for the batch of 8."""
+    from paper_1112_0065_amd import _lib as L
+    torch = torch_dev()
+    p = _params(5)
+    bits, vals = _tiles(6, n)
+    labels = np.arange(n) % 2 * 1.0
+    m = L.triage_create(None, 0)
+    L.triage_set_params(m, flat(p))
+    buf = torch.zeros(n * 64 * 256 + 8, dtype=torch.int16, device="cuda")
+    t = buf[shift:shift + n * 64 * 256]
+    t.copy_(_dev_tiles(bits).view(-1))
+    logits = torch.empty(n, dtype=torch.float32, device="cuda")
+    L.triage_forward(m, t, n, logits=logits)
+    ref_logits, cache = cnn.forward({k: v for k, v in p.items()}, vals, bf16=True)
+    assert np.all(np.abs(logits.cpu().numpy() - ref_logits) <= 1e-2 * (1 + np.abs(ref_logits)))
+    L.triage_forward_backward(m, t, torch.tensor(labels, dtype=torch.float32, device="cuda"), n)
+    gg = unflat(L.triage_get_params(m)[1])
+    ref = cnn.backward(p, cache, ref_logits, labels, bf16=True)
+    for k in ORDER:
+        assert np.linalg.norm(gg[k] - ref[k]) <= 2e-2 * (np.linalg.norm(ref[k]) + 1e-12), k
+
+
+def test_gradient_of_a_large_batch_is_the_mean_of_its_halves():
+    """256 tiles give every layer's blocks several work units; halves of 128
+    (gradients of the logits twice as large: every bfloat16 rounding is the
+    same) sum other partials.  A weight's gradient sums at most 256 x 16 384
+    products in float32: at random signs sqrt(4e6) x 2^-24 < 2e-4 of the
+    largest partial sum, far less of the whole gradient's norm."""
+    from paper_1112_0065_amd import _lib as L
+    torch = torch_dev()
+    m = L.triage_create(None, 3)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    t = torch.randn((256, 64, 256), generator=g, device="cuda").to(torch.bfloat16)
+    lab = (torch.arange(256, device="cuda") % 3 == 0).float()
+    grads = []
+    for a, b in ((0, 256), (0, 128), (128, 256)):
+        L.triage_forward_backward(m, t[a:b].contiguous(), lab[a:b].contiguous(), b - a)
+        grads.append(unflat(L.triage_get_params(m)[1]))
+    for k in ORDER:
+        half = 0.5 * (grads[1][k] + grads[2][k])
+        err = np.linalg.norm(grads[0][k] - half) / np.linalg.norm(half)
+        log("grad", k, "rel L2", err)
+        assert err <= 2e-4, k
