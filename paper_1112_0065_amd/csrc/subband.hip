@@ -20,10 +20,10 @@
 // per subband on the common channel-major bit-plane copy of the input (each
 // subband is a block of rows), writing uint16 series.  Stage 2 is a gather
 // of nsub values per output: a block takes one trial group and a tile of
-// 1024 output samples, stages the group's rows of up to 8 subbands at a time
+// 2048 output samples, stages the group's rows of a few subbands at a time
 // in LDS (the tile plus the spread of the group's subband delays), and sums
-// them in registers for every trial of the group -- the LDS rows are shared
-// by the G trials.  Stage 1 does ncoarse * nchans adds per sample instead of
+// them in registers for every trial of the group, two 16-bit sums per word --
+// the LDS rows are shared by the G trials.  Stage 1 does ncoarse * nchans adds per sample instead of
 // ndm * nchans; stage 2 adds ndm * nsub.
 #include <algorithm>
 #include <climits>
@@ -34,23 +34,45 @@
 namespace {
 
 constexpr int kS2Threads = 256;
-constexpr int kS2Tile = 1024;        // output samples per block (4 per thread)
-constexpr int kS2PerThread = kS2Tile / kS2Threads;
+constexpr int kS2Pairs = 4;          // pairs of output samples per thread
+constexpr int kS2Tile = 2 * kS2Threads * kS2Pairs;   // output samples per block
 constexpr int kMaxGroup = 16;        // fine trials per coarse trial
-// LDS per block: rows of a few subbands at a time; 16 KiB (several blocks per
-// CU) ran stage 2 a fifth faster than 64 KiB, 8-12 KiB no faster
+// LDS per block: rows of a few subbands at a time, so that several blocks share
+// a CU.  16 x 8 on the survey beam, both stages: 16 KiB 2.43 ms, 32 KiB 2.47, 48
+// KiB 2.91; tiles of 1024 samples 2.71-2.90.
 constexpr int kS2LdsBytes = 16 * 1024;
+
+// Largest spread of a group's subband delays: a staged row and its second copy
+// then fit 40 KiB.
+constexpr int kS2MaxSpan = 7152;
+
+// Any run of words at an element boundary (one store).
+struct __attribute__((packed, aligned(2))) Word1 {
+    uint32_t w;
+};
+struct __attribute__((packed, aligned(4))) Word2 {
+    uint32_t w[2];
+};
+
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 // Block (tile, group q): out[d][t] for the group's trials and t in the tile.
 // sub: uint16 series of subband s at sub + ncoarse * (s * nsamps - cum[s]),
 // rows of nsamps - maxd[s] samples (the stage-1 output of each subband).
 // lo[q][s]: smallest delay[d][c0(s)] over the group.  The samples
-// [t0 + lo, t0 + lo + row_len) of subband sc0 + k are staged in LDS row k with
-// 16-byte loads from the 16-byte boundary at or before the first one; that
-// sample sits at LDS index mis (0..7) of the row, and mis is folded into the
-// trials' read offsets, which are block-uniform and come from scalar loads of
-// the delay tables, so that all reads of a subband issue back to back.  Chunks that reach past the row end load sample by
-// sample (positions past it read as 0; they only feed outputs past nout).
+// [t0 + lo, t0 + lo + row_len) of subband sc0 + k are staged in LDS with 16-byte
+// loads from the 16-byte boundary at or before the first one; that sample sits
+// at LDS index mis (0..7) of the row, and mis is folded into the trials' read
+// offsets, which are block-uniform and come from scalar loads of the delay
+// tables, so that all reads of a subband issue back to back.  Positions past
+// the row end read as 0; they only feed outputs past nout.
+//
+// A thread adds pairs of neighbouring samples, two 16-bit sums in one word
+// (every partial sum stays at or below 3 nchans <= 65535), so a row is kept
+// twice, the second time one sample on: a trial's offset is then even in one
+// of the two and its pairs are aligned words.  (One sample per read and add,
+// 1024-sample tiles: 2.70 ms for both stages instead of 2.43.)  What remains is
+// mostly the stage-1 series' way through HBM: 2.45 GB written and read.
 constexpr int kS2MaxChunk = 16;
 
 template <int GM, bool OUT16>
@@ -60,21 +82,23 @@ __global__ __launch_bounds__(kS2Threads) void subband_sum_kernel(
     const int32_t* __restrict__ lo, int nsub, int ncoarse, int ndm, int group, int64_t nsamps,
     int64_t nout, int row_len, int row_stride, int chunk, void* __restrict__ out) {
     extern __shared__ uint4 rows_raw[];
-    uint16_t* rows = reinterpret_cast<uint16_t*>(rows_raw);
+    char* rows = reinterpret_cast<char*>(rows_raw);
     const int q = blockIdx.y;
     const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kS2Tile;
     const int d0 = q * group;
     const int gq = min(group, ndm - d0);
     const int tid = threadIdx.x;
-    uint32_t acc[GM][kS2PerThread];
+    // half a block (two waves) stages a row
+    const int half = __builtin_amdgcn_readfirstlane(tid >> 7);
+    u16x2 acc[GM][kS2Pairs];
 #pragma unroll
     for (int g = 0; g < GM; ++g)
 #pragma unroll
-        for (int j = 0; j < kS2PerThread; ++j) acc[g][j] = 0;
+        for (int j = 0; j < kS2Pairs; ++j) acc[g][j] = u16x2{0, 0};
 
     for (int sc0 = 0; sc0 < nsub; sc0 += chunk) {
         const int nsc = min(chunk, nsub - sc0);
-        for (int k = 0; k < nsc; ++k) {
+        for (int k = half; k < nsc; k += 2) {
             const int s = sc0 + k;
             const int64_t nrow = nsamps - maxd[s];
             const uint16_t* row = sub + static_cast<int64_t>(ncoarse) * (s * nsamps - cum[s]) +
@@ -85,16 +109,27 @@ __global__ __launch_bounds__(kS2Threads) void subband_sum_kernel(
             const uint16_t* a0 = first - mis;                 // 16-byte aligned
             const int nchunk = (mis + row_len + 7) >> 3;
             const int64_t valid = nrow - base + mis;           // a0[i] is in the row for i < valid
-            uint16_t* dst = rows + k * row_stride;
-            for (int c = tid; c < nchunk; c += kS2Threads) {
+            uint4* dst = reinterpret_cast<uint4*>(rows + 2 * k * row_stride * 2);
+            for (int c = tid & 127; c < nchunk; c += kS2Threads / 2) {
                 const int64_t i0 = static_cast<int64_t>(c) * 8;
-                if (i0 + 8 <= valid) {
-                    reinterpret_cast<uint4*>(dst)[c] = *reinterpret_cast<const uint4*>(a0 + i0);
+                uint32_t w[4], next = 0;
+                if (i0 + 9 <= valid) {
+                    const uint4 x = *reinterpret_cast<const uint4*>(a0 + i0);
+                    w[0] = x.x; w[1] = x.y; w[2] = x.z; w[3] = x.w;
+                    next = a0[i0 + 8];
                 } else {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e)
-                        dst[i0 + e] = (i0 + e >= mis && i0 + e < valid) ? a0[i0 + e] : static_cast<uint16_t>(0);
+                    for (int e = 0; e < 4; ++e) {
+                        const int64_t i = i0 + 2 * e;
+                        const uint32_t l = i >= mis && i < valid ? a0[i] : 0u;
+                        const uint32_t h = i + 1 >= mis && i + 1 < valid ? a0[i + 1] : 0u;
+                        w[e] = l | (h << 16);
+                    }
                 }
+                dst[c] = make_uint4(w[0], w[1], w[2], w[3]);
+                dst[c + (row_stride >> 3)] =
+                    make_uint4(__builtin_amdgcn_alignbit(w[1], w[0], 16), __builtin_amdgcn_alignbit(w[2], w[1], 16),
+                               __builtin_amdgcn_alignbit(w[3], w[2], 16), __builtin_amdgcn_alignbit(next, w[3], 16));
             }
         }
         __syncthreads();
@@ -107,33 +142,47 @@ __global__ __launch_bounds__(kS2Threads) void subband_sum_kernel(
             const uint16_t* first = sub + static_cast<int64_t>(ncoarse) * (s * nsamps - cum[s]) +
                                     static_cast<int64_t>(q) * nrow + t0 + lo_qs;
             const int mis = static_cast<int>((reinterpret_cast<uintptr_t>(first) >> 1) & 7);
-            const uint16_t* src = rows + k * row_stride + tid;
-            int off[GM];
+            int off[GM];   // bytes
+#pragma unroll
+            for (int g = 0; g < GM; ++g) {
+                const int o = inter[static_cast<int64_t>(d0 + min(g, gq - 1)) * nsub + s] -
+                              static_cast<int>(lo_qs) + mis;
+                off[g] = (2 * k + (o & 1)) * row_stride * 2 + (o >> 1) * 4;
+            }
+            uint32_t v[GM][kS2Pairs];
+#pragma unroll
+            for (int g = 0; g < GM; ++g) {
+                const uint32_t* src = reinterpret_cast<const uint32_t*>(rows + off[g]) + tid;
+#pragma unroll
+                for (int j = 0; j < kS2Pairs; ++j) v[g][j] = src[j * kS2Threads];
+            }
 #pragma unroll
             for (int g = 0; g < GM; ++g)
-                off[g] = inter[static_cast<int64_t>(d0 + min(g, gq - 1)) * nsub + s] -
-                         static_cast<int>(lo_qs) + mis;
-            uint32_t v[GM][kS2PerThread];
 #pragma unroll
-            for (int g = 0; g < GM; ++g)
-#pragma unroll
-                for (int j = 0; j < kS2PerThread; ++j) v[g][j] = src[off[g] + j * kS2Threads];
-#pragma unroll
-            for (int g = 0; g < GM; ++g)
-#pragma unroll
-                for (int j = 0; j < kS2PerThread; ++j) acc[g][j] += v[g][j];
+                for (int j = 0; j < kS2Pairs; ++j) acc[g][j] += __builtin_bit_cast(u16x2, v[g][j]);
         }
         __syncthreads();
     }
 #pragma unroll
     for (int g = 0; g < GM; ++g) {
+        if (g >= gq) break;
 #pragma unroll
-        for (int j = 0; j < kS2PerThread; ++j) {
-            const int64_t t = t0 + tid + j * kS2Threads;
-            if (g < gq && t < nout) {
-                const int64_t o = static_cast<int64_t>(d0 + g) * nout + t;
-                if (OUT16) static_cast<uint16_t*>(out)[o] = static_cast<uint16_t>(acc[g][j]);
-                else static_cast<int32_t*>(out)[o] = static_cast<int32_t>(acc[g][j]);
+        for (int j = 0; j < kS2Pairs; ++j) {
+            const int64_t t = t0 + 2 * (tid + j * kS2Threads);
+            const int64_t o = static_cast<int64_t>(d0 + g) * nout + t;
+            const uint32_t w = __builtin_bit_cast(uint32_t, acc[g][j]);
+            if (OUT16) {
+                uint16_t* p = static_cast<uint16_t*>(out) + o;
+                if (t + 1 < nout)
+                    *reinterpret_cast<Word1*>(p) = Word1{w};
+                else if (t < nout)
+                    *p = static_cast<uint16_t>(w);
+            } else {
+                int32_t* p = static_cast<int32_t*>(out) + o;
+                if (t + 1 < nout)
+                    *reinterpret_cast<Word2*>(p) = Word2{{w & 0xFFFFu, w >> 16}};
+                else if (t < nout)
+                    *p = static_cast<int32_t>(w & 0xFFFFu);
             }
         }
     }
@@ -263,7 +312,7 @@ extern "C" dedisp_status dedisp_subband_create(dedisp_plan plan, int32_t nsub, i
             lo[static_cast<size_t>(q) * nsub + s] = mn;
             b->span = std::max(b->span, mx - mn);
         }
-    if (static_cast<int64_t>(kS2Tile + b->span + 16) * 2 > kS2LdsBytes) {
+    if (b->span > kS2MaxSpan) {
         free_subband(b);
         return fail(DEDISP_ERR_UNSUPPORTED,
                     "a group's subband delays spread over %d samples: use smaller groups", b->span);
@@ -341,9 +390,9 @@ extern "C" dedisp_status dedisp_subband_execute(dedisp_subband b, const uint8_t*
     const int64_t nout = nsamps - b->loss;
     const int row_len = kS2Tile + b->span;
     const int row_stride = (row_len + 7 + 7) & ~7;        // room for the leading misalignment
-    const int chunk = std::max(1, std::min(kS2MaxChunk, kS2LdsBytes / (row_stride * 2)));
+    const int chunk = std::max(1, std::min(kS2MaxChunk, kS2LdsBytes / (row_stride * 4)));
     const dim3 grid(static_cast<unsigned>((nout + kS2Tile - 1) / kS2Tile), static_cast<unsigned>(b->ncoarse));
-    const size_t lds = static_cast<size_t>(chunk) * row_stride * 2;
+    const size_t lds = static_cast<size_t>(chunk) * row_stride * 4;   // every row twice
     const bool u16 = out_type == DEDISP_OUT_U16;
 #define DD_S2(GM_)                                                                             \
     if (b->group <= GM_) {                                                                     \

@@ -85,3 +85,18 @@ def test_survey_beam_sampled_trials():
     for k, d in enumerate(rows):
         assert (got[d] == ref[k]).all(), d
     log(f"survey subband: span {sb.span}, max delay {sb.max_delay}, ncoarse {sb.ncoarse}")
+
+
+@pytest.mark.parametrize("extra", [1, 2, 2047, 2049])
+def test_output_lengths_around_a_tile(extra):
+    """Outputs that end at, before and after a stage-2 tile, rows of odd
+    length (pairs of samples off word alignment), trials at odd and even
+    offsets; both output types."""
+    from paper_1112_0065_amd import _lib as L
+    fb, dly, x, direct = small_case()
+    plan = L.dedisp_plan_create(fb.nchans, fb.f_top, fb.df, fb.tsamp, fb.dm_list)
+    nsamps = L.dedisp_subband_create(plan, 8, 3).max_delay + extra
+    ref = subband_dedisperse(x[:, :nsamps], fb.f_top, fb.df, fb.tsamp, fb.dm_list, 8, 3)
+    for u16 in (True, False):
+        _, got = _run(fb, plan, 8, 3, u16, packed=fb.packed[:nsamps * fb.nchans // 4], nsamps=nsamps)
+        assert got.shape == ref.shape == (len(fb.dm_list), extra) and (got == ref).all(), u16
