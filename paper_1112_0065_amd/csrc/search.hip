@@ -653,6 +653,466 @@ __global__ __launch_bounds__(kThreads) void boxcar_stats_kernel(const T* __restr
     }
 }
 
+// ----------------------------------------------------------------------------
+// Pass 1 on 16-bit running sums.
+//
+// With c near the window's mean sample, P'(k) = P(k) - c k stays close to 0: the
+// running sum of a noise series of sigma 30 wanders about 5000 over a window of
+// 9216 samples.  While P' spans at most 2^14 - 1 over the window, every centred
+// boxcar B' = P'(p + w) - P'(p) = B - c w does too, so two positions share a
+// word: one packed subtraction, one v_dot2_i32_i16 for the squares and one
+// packed maximum per two positions and width, instead of a subtraction, a
+// 64-bit multiply-add and half a three-way maximum each.  The sums of B follow
+// exactly: S1 = S1' + n c w, S2 = S2' + 2 c w S1' + n (c w)^2.  The running sums
+// take half the LDS as well (20 KiB a block), and rows of any alignment load in
+// aligned quads.  Bound by VALU issue as before, with less to issue: find_peaks
+// on the survey series 1029 -> 851 us (10 widths), on 301 int32 rows of odd
+// length 164 -> 131.  Six waves per SIMD with eight steps unrolled: five 865,
+// seven 922 (two steps), four steps 952.
+// Windows that span more (bright pulses, a drifting baseline) take 32-bit sums
+// in two halves, large values and ragged ones the general code.
+// ----------------------------------------------------------------------------
+constexpr int kSegLen = 8192;                       // positions per segment
+constexpr int kHalfLen = kSegLen / 2;
+constexpr int kWinSamples = 4 * kThreads * kRounds;     // samples a block loads
+constexpr int kMaxSpan16 = (1 << 14) - 1;
+// widest boxcar: 3 samples of misalignment, the last position and the window
+// of the widest boxcar inside the running sums P(0 .. kWinSamples - 1)
+constexpr int kMaxWidth16 = kWinSamples - 3 - kSegLen;
+// LDS words: the 16-bit running sums (up to 3 places on), or half a window's
+// 32-bit ones, or a value of 8 bytes per pair of lanes and width (16 widths)
+constexpr int kPairStride = kThreads / 2 + 16;
+constexpr int kLds16Words = kHalfLen + kMaxWidth16 + 2;
+static_assert(kLds16Words * 2 >= kWinSamples + 4, "16-bit sums fit");
+static_assert(kLds16Words >= 2 * 16 * kPairStride, "reductions fit");
+
+typedef short i16x2 __attribute__((ext_vector_type(2)));
+
+// Minimum and maximum over the wave (in lane 63).
+__device__ __forceinline__ int dpp_i32(int x, int ctrl) {
+    switch (ctrl) {
+        case 0: return __builtin_amdgcn_update_dpp(x, x, 0x111, 0xF, 0xF, false);
+        case 1: return __builtin_amdgcn_update_dpp(x, x, 0x112, 0xF, 0xF, false);
+        case 2: return __builtin_amdgcn_update_dpp(x, x, 0x114, 0xF, 0xF, false);
+        case 3: return __builtin_amdgcn_update_dpp(x, x, 0x118, 0xF, 0xF, false);
+        case 4: return __builtin_amdgcn_update_dpp(x, x, 0x142, 0xA, 0xF, false);
+        default: return __builtin_amdgcn_update_dpp(x, x, 0x143, 0xC, 0xF, false);
+    }
+}
+__device__ __forceinline__ int wave_max_i32(int x) {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) x = max(x, dpp_i32(x, c));
+    return x;
+}
+
+// The block's totals of NW widths from every thread's sum of squares and
+// maximum (as int), and every wave's sums (lane wi: width wi).  Lane 16 wi of
+// the block returns true with width wi's totals.  lds: 2 NW kPairStride words,
+// free on entry for every thread (the caller's barrier).
+template <int NW>
+__device__ __forceinline__ bool stats_reduce(const uint64_t (&s2)[NW], const int (&mx)[NW], int64_t s1,
+                                             uint32_t* lds, uint64_t* s2_out, int* mx_out, int64_t* s1_out) {
+    const int t = threadIdx.x, lane = t & 63;
+    uint64_t* r = reinterpret_cast<uint64_t*>(lds);
+    // pairs of lanes first, then rows of 128 values per width: lane 16 wi + l
+    // takes l, l + 16, ... and the 16 lanes of a DPP row their sum
+#pragma unroll
+    for (int wi = 0; wi < NW; ++wi) {
+        const uint64_t o = (static_cast<uint64_t>(dpp_u32(static_cast<uint32_t>(s2[wi] >> 32), 0)) << 32) |
+                           dpp_u32(static_cast<uint32_t>(s2[wi]), 0);
+        if (!(t & 1)) r[wi * kPairStride + (t >> 1)] = s2[wi] + o;
+    }
+    __syncthreads();
+    uint64_t acc = 0;
+    if (t < NW * 16) {
+        const uint64_t* q = r + (t >> 4) * kPairStride + (t & 15);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) acc += q[16 * k];
+    }
+    acc = row_sum_u64(acc);
+    __syncthreads();
+    int* rm = reinterpret_cast<int*>(lds) + 2 * 16 * (kThreads / 64);
+#pragma unroll
+    for (int wi = 0; wi < NW; ++wi) {
+        const int o = max(mx[wi], static_cast<int>(dpp_u32(static_cast<uint32_t>(mx[wi]), 0)));
+        if (!(t & 1)) rm[wi * kPairStride + (t >> 1)] = o;
+    }
+    int64_t* rs = reinterpret_cast<int64_t*>(lds);
+    if (lane < NW) rs[(t >> 6) * NW + lane] = s1;
+    __syncthreads();
+    int am = INT32_MIN;
+    int64_t a1 = 0;
+    if (t < NW * 16) {
+        const int* q = rm + (t >> 4) * kPairStride + (t & 15);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) am = max(am, q[16 * k]);
+        if ((t & 15) == 0) {
+#pragma unroll
+            for (int v = 0; v < kThreads / 64; ++v) a1 += rs[v * NW + (t >> 4)];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) am = max(am, static_cast<int>(dpp_u32(static_cast<uint32_t>(am), c)));
+    *s2_out = acc;
+    *mx_out = am;
+    *s1_out = a1;
+    return t < NW * 16 && (t & 15) == 0;
+}
+
+// This lane's width (lane wi < NW) and the wave's share of its sum of boxcars
+// over n positions, by telescoping: sum_p (P(p + w) - P(p)) = sum_{i < w}
+// (P(n + i) - P(i)).  diff(i) gives the i-th term; lane l takes i = i0 + l, a DPP
+// scan gives the prefix, lane wi fetches the one at w - 1.  |term| < 2^25, or
+// any unsigned 32-bit term when WIDE (its 16-bit halves are scanned apart).
+template <bool WIDE, int NW, typename F>
+__device__ __forceinline__ int64_t telescoped(const int (&w)[NW], F diff) {
+    const int lane = threadIdx.x & 63;
+    int myw = 0;
+#pragma unroll
+    for (int wi = 0; wi < NW; ++wi)
+        if (lane == wi) myw = w[wi];
+    int64_t s1 = 0;
+    for (int i0 = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) & ~63); i0 < w[NW - 1];
+         i0 += kThreads) {
+        const int i = i0 + lane;
+        const int d = i < w[NW - 1] ? diff(i) : 0;
+        const int l = myw - 1 - i0;
+        const int src = min(max(l, 0), 63);
+        int64_t got;
+        if (WIDE) {
+            const uint32_t a = wave_incl_scan(static_cast<uint32_t>(d) & 0xFFFFu);
+            const uint32_t b = wave_incl_scan(static_cast<uint32_t>(d) >> 16);
+            got = static_cast<int64_t>(__shfl(static_cast<int>(a), src, 64)) +
+                  (static_cast<int64_t>(__shfl(static_cast<int>(b), src, 64)) << 16);
+        } else {
+            got = __shfl(static_cast<int>(wave_incl_scan(static_cast<uint32_t>(d))), src, 64);
+        }
+        if (l >= 0) s1 += got;
+    }
+    return s1;
+}
+
+// Four consecutive samples, as loaded (one aligned 8- or 16-byte load).
+template <typename T>
+struct Quad;
+template <>
+struct Quad<uint16_t> {
+    uint32_t v[2];
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, int off) {
+        const auto x = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
+        v[0] = x[0];
+        v[1] = x[1];
+    }
+    __device__ __forceinline__ uint32_t get(int j) const { return (v[j >> 1] >> (16 * (j & 1))) & 0xFFFFu; }
+    __device__ __forceinline__ void set(int j, uint32_t s) {
+        v[j >> 1] = (v[j >> 1] & (j & 1 ? 0xFFFFu : 0xFFFF0000u)) | (s << (16 * (j & 1)));
+    }
+    __device__ __forceinline__ uint32_t sum() const { return add_halves(v[1], add_halves(v[0], 0u)); }
+    // P(0 .. 2) of the quad on top of base
+    __device__ __forceinline__ uint32_t s1(uint32_t base) const { return base + (v[0] & 0xFFFFu); }
+    __device__ __forceinline__ uint32_t s2(uint32_t base) const { return add_halves(v[0], base); }
+    __device__ __forceinline__ uint32_t s3(uint32_t base) const { return s2(base) + (v[1] & 0xFFFFu); }
+    __device__ __forceinline__ uint32_t vmax(uint32_t) const { return 0u; }   // below 2^16 anyway
+};
+template <>
+struct Quad<int32_t> {
+    uint32_t v[4];
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, int off) {
+        const auto x = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = x[j];
+    }
+    __device__ __forceinline__ uint32_t get(int j) const { return v[j]; }
+    __device__ __forceinline__ void set(int j, uint32_t s) { v[j] = s; }
+    __device__ __forceinline__ uint32_t sum() const { return v[0] + v[1] + v[2] + v[3]; }
+    __device__ __forceinline__ uint32_t s1(uint32_t base) const { return base + v[0]; }
+    __device__ __forceinline__ uint32_t s2(uint32_t base) const { return base + v[0] + v[1]; }
+    __device__ __forceinline__ uint32_t s3(uint32_t base) const { return base + v[0] + v[1] + v[2]; }
+    __device__ __forceinline__ uint32_t vmax(uint32_t m) const { return max(max(max(m, v[0]), max(v[1], v[2])), v[3]); }
+};
+
+// One (DM, segment) per block.  `in` is aligned to four samples; w_max <=
+// kMaxWidth16; every width even, but for the first one when ODD1.
+template <typename T, int NW, bool ODD1>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NW <= 10 ? 6 : 5))) void boxcar_stats16_kernel(const T* __restrict__ in, int64_t nout,
+                                                                  int64_t nbx, dd::Widths W, int nseg,
+                                                                  dd::PeaksWs ws) {
+    __shared__ uint4 lds16[(kLds16Words + 3) / 4];
+    __shared__ uint32_t round_tot[kRounds * (kThreads / 64)];
+    __shared__ int span[2][kThreads / 64];      // per wave: largest P' and largest -P'
+    __shared__ uint32_t vmax_w[kThreads / 64];
+    uint32_t* lds = reinterpret_cast<uint32_t*>(lds16);
+    const int d = blockIdx.y, seg = blockIdx.x;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int64_t s0 = static_cast<int64_t>(seg) * kSegLen;
+    const int npos = static_cast<int>(min<int64_t>(kSegLen, nbx - s0));
+    int w[NW];
+#pragma unroll
+    for (int wi = 0; wi < NW; ++wi) w[wi] = W.w[wi];
+    const int w_max = w[NW - 1];
+    // The window: kWinSamples samples from the four-sample boundary at or before
+    // the segment's first one (k0 samples on), loaded in kRounds rounds of one
+    // aligned quad per thread, up to the end of the array; what lies past the
+    // segment's last window (the next row) enters no difference that is used.
+    const int64_t first = static_cast<int64_t>(d) * nout + s0;
+    const int k0 = static_cast<int>(first & 3);
+    const int64_t left = static_cast<int64_t>(gridDim.y) * nout - (first - k0);
+    const int num = static_cast<int>(min<int64_t>(left, kWinSamples));
+    const T* win = in + (first - k0);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<T*>(win), 0, (num & ~3) * static_cast<int>(sizeof(T)), kRowRsrcWord3);
+    Quad<T> v[kRounds];
+#pragma unroll
+    for (int i = 0; i < kRounds; ++i) v[i].load(rs, 4 * (i * kThreads + t) * static_cast<int>(sizeof(T)));
+    if (num & 3) {   // the array ends inside a quad: its samples one by one
+        uint32_t tail[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) tail[j] = j < (num & 3) ? static_cast<uint32_t>(win[(num & ~3) + j]) : 0u;
+#pragma unroll
+        for (int i = 0; i < kRounds; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) v[i].set(j, i * kThreads + t == num >> 2 ? tail[j] : v[i].get(j));
+    }
+    uint32_t excl[kRounds];
+    uint32_t vm = 0;
+#pragma unroll
+    for (int i = 0; i < kRounds; ++i) {
+        const uint32_t c = v[i].sum();
+        const uint32_t incl = wave_incl_scan(c);
+        excl[i] = incl - c;
+        if (lane == 63) round_tot[i * (kThreads / 64) + wave] = incl;
+        vm = v[i].vmax(vm);
+    }
+    if (!std::is_same<T, uint16_t>::value) {
+        vm = static_cast<uint32_t>(wave_max_i32(static_cast<int>(min(vm, 0x7FFFFFFFu))));
+        if (lane == 63) vmax_w[wave] = vm;
+    }
+    __syncthreads();
+    const uint32_t tv = lane < kRounds * (kThreads / 64) ? round_tot[lane] : 0u;
+    const uint32_t tin = wave_incl_scan(tv);
+    const uint32_t tex = tin - tv;
+    // a sample near the mean, the same in every lane (any value gives exact
+    // sums: a poor one only widens the span)
+    const uint32_t total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(tin), 63));
+    const int c = __builtin_amdgcn_readfirstlane(
+        static_cast<int>(fminf(static_cast<float>(total) * __builtin_amdgcn_rcpf(static_cast<float>(num)), 1e9f) + 0.5f));
+    // P' of the thread's quads, P'(4 g .. 4 g + 3); the places used are k0 ..
+    // kneed
+    const int kneed = k0 + npos - 1 + w_max;
+    const int off = k0 & 1 ? 4 - k0 : 0;   // k0 + off is even: pairs of positions are words
+    int hi = 0, lo = 0;
+    uint32_t word[kRounds][2];
+#pragma unroll
+    for (int i = 0; i < kRounds; ++i) {
+        const uint32_t pre = static_cast<uint32_t>(
+            __builtin_amdgcn_readlane(static_cast<int>(tex), i * (kThreads / 64) + wave));
+        const uint32_t base = pre + excl[i] - static_cast<uint32_t>(c) * 4u * static_cast<uint32_t>(i * kThreads + t);
+        const int p0 = static_cast<int>(base);
+        const int p1 = static_cast<int>(v[i].s1(base) - c);
+        const int p2 = static_cast<int>(v[i].s2(base) - 2 * c);
+        const int p3 = static_cast<int>(v[i].s3(base) - 3 * c);
+        const bool need = 4 * (i * kThreads + t) <= kneed;
+        const int h4 = max(max(max(hi, p0), max(p1, p2)), p3), l4 = min(min(min(lo, p0), min(p1, p2)), p3);
+        hi = need ? h4 : hi;
+        lo = need ? l4 : lo;
+        word[i][0] = __builtin_amdgcn_perm(static_cast<uint32_t>(p1), static_cast<uint32_t>(p0), 0x05040100u);
+        word[i][1] = __builtin_amdgcn_perm(static_cast<uint32_t>(p3), static_cast<uint32_t>(p2), 0x05040100u);
+    }
+    hi = wave_max_i32(hi);
+    lo = wave_max_i32(-lo);
+    if (lane == 63) {
+        span[0][wave] = hi;
+        span[1][wave] = lo;
+    }
+    // half-word h = k + off holds P'(k)
+    uint16_t* half = reinterpret_cast<uint16_t*>(lds);
+    if (off == 0) {
+#pragma unroll
+        for (int i = 0; i < kRounds; ++i)
+            *reinterpret_cast<uint2*>(lds + 2 * (i * kThreads + t)) = make_uint2(word[i][0], word[i][1]);
+    } else {
+#pragma unroll
+        for (int i = 0; i < kRounds; ++i) {   // odd off: a half, a word, a half
+            const int h = 4 * (i * kThreads + t) + off;
+            half[h] = static_cast<uint16_t>(word[i][0]);
+            *reinterpret_cast<uint32_t*>(half + h + 1) = __builtin_amdgcn_alignbit(word[i][1], word[i][0], 16);
+            half[h + 3] = static_cast<uint16_t>(word[i][1] >> 16);
+        }
+    }
+    __syncthreads();
+    int smax = 0, smin = 0;
+    uint32_t vmax = 0xFFFFu;
+#pragma unroll
+    for (int k = 0; k < kThreads / 64; ++k) {
+        smax = max(smax, span[0][k]);
+        smin = max(smin, span[1][k]);
+        if (!std::is_same<T, uint16_t>::value) vmax = k == 0 ? vmax_w[0] : max(vmax, vmax_w[k]);
+    }
+    // P and c k below 2^31 apart (so P' did not wrap), the span, and every
+    // square sum below 2^13 x 2^50
+    const bool narrow = vmax < (1u << 17) && smax <= kMaxSpan16 - smin && smin <= kMaxSpan16 &&
+                        static_cast<int64_t>(c) * w_max + (1 << 14) < (1 << 25);
+    const int64_t idx0 = static_cast<int64_t>(d) * nseg + seg;
+    const int64_t stride = static_cast<int64_t>(gridDim.y) * nseg;
+    if (narrow) {
+        uint32_t sq[2][NW];   // at most 16 squares below 2^28 each
+        i16x2 mx[NW];
+#pragma unroll
+        for (int wi = 0; wi < NW; ++wi) {
+            sq[0][wi] = sq[1][wi] = 0u;
+            mx[wi] = i16x2{INT16_MIN, INT16_MIN};
+        }
+        const uint32_t* base = lds + (k0 + off) / 2 + t;
+        auto pair = [&](const uint32_t* q, int wi) -> uint32_t {
+            return ODD1 && wi == 0 ? __builtin_amdgcn_alignbit(q[(w[0] + 1) / 2], q[(w[0] - 1) / 2], 16)
+                                   : q[w[wi] / 2];
+        };
+        if (npos == kSegLen) {
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf)
+#pragma unroll 8
+                for (int j = 0; j < 8; ++j) {
+                    const uint32_t* q = base + (8 * hf + j) * kThreads;
+                    const i16x2 p = __builtin_bit_cast(i16x2, q[0]);
+#pragma unroll
+                    for (int wi = 0; wi < NW; ++wi) {
+                        const i16x2 b = __builtin_bit_cast(i16x2, pair(q, wi)) - p;
+                        sq[hf][wi] = static_cast<uint32_t>(
+                            __builtin_amdgcn_sdot2(b, b, static_cast<int>(sq[hf][wi]), false));
+                        mx[wi] = __builtin_elementwise_max(mx[wi], b);
+                    }
+                }
+        } else {
+            for (int j = 0; j < 16 && 2 * j * kThreads < npos; ++j) {
+                const uint32_t* q = base + j * kThreads;
+                const int at = 2 * (j * kThreads + t);
+                const uint32_t m = at + 1 < npos ? 0xFFFFFFFFu : at < npos ? 0xFFFFu : 0u;
+                const i16x2 p = __builtin_bit_cast(i16x2, q[0]);
+#pragma unroll
+                for (int wi = 0; wi < NW; ++wi) {
+                    const uint32_t b = __builtin_bit_cast(uint32_t, __builtin_bit_cast(i16x2, pair(q, wi)) - p);
+                    const i16x2 bs = __builtin_bit_cast(i16x2, b & m);
+                    const uint32_t dot = static_cast<uint32_t>(
+                        __builtin_amdgcn_sdot2(bs, bs, static_cast<int>(j < 8 ? sq[0][wi] : sq[1][wi]), false));
+                    if (j < 8) sq[0][wi] = dot;
+                    else sq[1][wi] = dot;
+                    mx[wi] = __builtin_elementwise_max(mx[wi], __builtin_bit_cast(i16x2, (b & m) | (0x80008000u & ~m)));
+                }
+            }
+        }
+        const int16_t* ph = reinterpret_cast<const int16_t*>(half) + k0 + off;
+        const int64_t s1 = telescoped<false, NW>(w, [&](int i) { return static_cast<int>(ph[npos + i]) - ph[i]; });
+        uint64_t s2[NW];
+        int m32[NW];
+#pragma unroll
+        for (int wi = 0; wi < NW; ++wi) {
+            s2[wi] = static_cast<uint64_t>(sq[0][wi]) + sq[1][wi];
+            m32[wi] = max(static_cast<int>(mx[wi].x), static_cast<int>(mx[wi].y));
+        }
+        __syncthreads();   // the running sums are no longer needed
+        uint64_t a2;
+        int am;
+        int64_t a1;
+        if (stats_reduce<NW>(s2, m32, s1, lds, &a2, &am, &a1)) {
+            const int wi = t >> 4;
+            const int64_t cw = static_cast<int64_t>(c) * W.w[wi];
+            const int64_t i = idx0 + wi * stride;
+            ws.part_s1[i] = static_cast<uint64_t>(a1 + npos * cw);
+            ws.part_s2lo[i] = a2 + static_cast<uint64_t>(2 * cw * a1 + npos * cw * cw);
+            ws.part_s2hi[i] = 0u;
+            ws.part_max[i] = static_cast<uint32_t>(am + static_cast<int>(cw));
+        }
+        return;
+    }
+    // 32-bit running sums of half the segment at a time
+    __shared__ uint32_t wave_tot[kThreads / 64];
+    __shared__ uint32_t vhalf[2];
+    __shared__ uint64_t red1[kThreads / 64][NW];
+    __shared__ u128 red2[kThreads / 64][NW];
+    __shared__ uint32_t redm[kThreads / 64][NW];
+    const T* row = in + static_cast<int64_t>(d) * nout;
+    if (t < 2) vhalf[t] = 0u;
+    if (npos == kSegLen) {
+        uint64_t s2[NW];
+        int mx[NW];
+        int64_t s1 = 0;
+#pragma unroll
+        for (int wi = 0; wi < NW; ++wi) {
+            s2[wi] = 0;
+            mx[wi] = 0;
+        }
+        bool small = true;
+        for (int hf = 0; hf < 2 && small; ++hf) {
+            __syncthreads();
+            load_prefix(row, nout, s0 + hf * kHalfLen - 1, kHalfLen + w_max + 1, lds, wave_tot, &vhalf[hf]);
+            // every boxcar below 2^25, every sum of kHalfLen samples below 2^32
+            const uint64_t bmax = static_cast<uint64_t>(vhalf[hf]) * static_cast<uint64_t>(w_max);
+            small = bmax < (uint64_t(1) << 25) && vhalf[hf] < (1u << 20);
+            if (!small) break;
+            const uint32_t* base = lds + 1 + t;
+#pragma unroll 2
+            for (int j = 0; j < kHalfLen / kThreads; ++j) {
+                const uint32_t p0 = base[j * kThreads];
+#pragma unroll
+                for (int wi = 0; wi < NW; ++wi) {
+                    const uint32_t b = base[j * kThreads + w[wi]] - p0;
+                    s2[wi] += static_cast<uint64_t>(b) * b;
+                    mx[wi] = max(mx[wi], static_cast<int>(b));
+                }
+            }
+            s1 += telescoped<true, NW>(w, [&](int i) { return static_cast<int>(lds[1 + kHalfLen + i] - lds[1 + i]); });
+        }
+        __syncthreads();
+        if (small) {
+            uint64_t a2;
+            int am;
+            int64_t a1;
+            if (stats_reduce<NW>(s2, mx, s1, lds, &a2, &am, &a1)) {
+                const int64_t i = idx0 + (t >> 4) * stride;
+                ws.part_s1[i] = static_cast<uint64_t>(a1);
+                ws.part_s2lo[i] = a2;
+                ws.part_s2hi[i] = 0u;
+                ws.part_max[i] = static_cast<uint32_t>(am);
+            }
+            return;
+        }
+    }
+    // any values, any length: 128-bit sums, one width after the other
+    for (int hf = 0; hf < 2; ++hf) {
+        __syncthreads();
+        const int n = min(kHalfLen, npos - hf * kHalfLen);
+        if (n > 0) load_prefix(row, nout, s0 + hf * kHalfLen - 1, kHalfLen + w_max + 1, lds, wave_tot);
+        for (int wi = 0; wi < W.n; ++wi) {
+            uint64_t a1 = 0;
+            u128 a2 = 0;
+            uint32_t am = 0;
+            if (n > 0) width_sums<false>(lds, n, W.w[wi], &a1, &a2, &am);
+            if (lane == 0) {
+                red1[wave][wi] = (hf ? red1[wave][wi] : 0) + a1;
+                red2[wave][wi] = (hf ? red2[wave][wi] : 0) + a2;
+                redm[wave][wi] = max(hf ? redm[wave][wi] : 0u, am);
+            }
+        }
+    }
+    __syncthreads();
+    if (t < W.n) {
+        uint64_t a1 = 0;
+        u128 a2 = 0;
+        uint32_t am = 0;
+        for (int k = 0; k < kThreads / 64; ++k) {
+            a1 += red1[k][t];
+            a2 += red2[k][t];
+            am = max(am, redm[k][t]);
+        }
+        const int64_t i = idx0 + t * stride;
+        ws.part_s1[i] = a1;
+        ws.part_s2lo[i] = static_cast<uint64_t>(a2);
+        ws.part_s2hi[i] = static_cast<uint64_t>(a2 >> 64);
+        ws.part_max[i] = am;
+    }
+}
+
 // Pass 2: exact sums, D and B_thr per (width, DM) series, kSerPerBlock
 // series per block.  A series' partials are contiguous (series-major), so the
 // block stages a chunk of segments of all its series in LDS with loads that
@@ -1341,9 +1801,48 @@ hipError_t launch_stats_w(const void* in, int64_t nout, const Widths& W, const P
     }
 }
 
+// The 16-bit form's rule: whole segments of kSegLen, a series that starts on a
+// four-sample boundary (rows need not), 4 to 12 widths that fit its window,
+// all even but the first (two positions share a word, so an odd width costs a
+// shift per word and width).
+template <typename T>
+bool stats16_fits(const void* in, const Widths& W, const PeaksLayout& lay) {
+    if (lay.L != kSegLen || W.n < 4 || W.n > 12 || W.w[W.n - 1] > kMaxWidth16 ||
+        reinterpret_cast<uintptr_t>(in) % (4 * sizeof(T)))
+        return false;
+    for (int i = 1; i < W.n; ++i)
+        if (W.w[i] & 1) return false;
+    return true;
+}
+
+template <typename T, int NW>
+hipError_t launch_stats16_nw(const T* in, int64_t nout, const Widths& W, const PeaksLayout& lay,
+                             const PeaksWs& ws, dim3 grid, hipStream_t s) {
+    if (W.w[0] & 1)
+        hipLaunchKernelGGL((boxcar_stats16_kernel<T, NW, true>), grid, dim3(kThreads), 0, s, in, nout, lay.nbx, W,
+                           lay.nseg, ws);
+    else
+        hipLaunchKernelGGL((boxcar_stats16_kernel<T, NW, false>), grid, dim3(kThreads), 0, s, in, nout, lay.nbx, W,
+                           lay.nseg, ws);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t launch_stats16(const void* in, int64_t nout, const Widths& W, const PeaksLayout& lay,
+                          const PeaksWs& ws, dim3 grid, hipStream_t s) {
+    switch (W.n) {
+#define DD_NW(N) case N: return launch_stats16_nw<T, N>(static_cast<const T*>(in), nout, W, lay, ws, grid, s);
+        DD_NW(4) DD_NW(5) DD_NW(6) DD_NW(7) DD_NW(8) DD_NW(9) DD_NW(10) DD_NW(11) DD_NW(12)
+#undef DD_NW
+        default: return hipErrorInvalidValue;
+    }
+}
+
 hipError_t launch_stats(const void* in, int in_u16, int64_t nout, const Widths& W,
                         const PeaksLayout& lay, const PeaksWs& ws, dim3 grid, size_t lds,
                         hipStream_t s) {
+    if (in_u16 && stats16_fits<uint16_t>(in, W, lay)) return launch_stats16<uint16_t>(in, nout, W, lay, ws, grid, s);
+    if (!in_u16 && stats16_fits<int32_t>(in, W, lay)) return launch_stats16<int32_t>(in, nout, W, lay, ws, grid, s);
     return in_u16 ? launch_stats_w<uint16_t>(in, nout, W, lay, ws, grid, lds, s)
                   : launch_stats_w<int32_t>(in, nout, W, lay, ws, grid, lds, s);
 }

@@ -305,3 +305,51 @@ def test_event_slots_over_series_and_segments(ndm, nout, nw):
     for u16 in (False, True):
         ev, _ = _find(series, widths, 4.0, u16, capacity=1 << 19)
         events_equal(ev, ref)
+
+
+@pytest.mark.parametrize("widths,nout", [
+    ([1, 2, 4, 8], 8192 + 7),                        # the last window ends the row; one whole segment
+    ([1, 2, 4, 8, 16], 8192 + 15),                   # one position more than a segment less one
+    ([3, 4, 10, 64], 16384 + 64),                    # odd first width; one position in the third segment
+    ([2, 6, 100, 512, 1020], 16384 + 1019 + 511),    # even widths, the widest that fits; ragged tail
+    ([1, 2, 4, 8, 16, 32, 64, 128, 256, 512, 514, 600], 12001),
+    ([1, 2, 4, 1022], 20002),                        # too wide: the 32-bit form
+    ([1, 2, 4, 7, 8], 9000),                         # an odd width further on: the 32-bit form
+])
+def test_statistics_forms_and_their_limits(widths, nout):
+    """The 16-bit statistics pass (rows at every alignment, whole and ragged
+    segments), its 32-bit halves for windows of a wide span, the general sums
+    for large values, and the lists it does not take: sums, cuts and events
+    equal the oracle's."""
+    rng = np.random.default_rng(nout)
+    ndm = 7
+    series = rng.normal(1500.0, 30.0, size=(ndm, nout)).round().astype(np.int64)
+    series[1, 3000:3600] += 60                   # spans more than 2^14
+    series[2] += (400 * np.sin(np.arange(nout) / 2000.0)).astype(np.int64)   # a drifting baseline
+    series[3] = 60000 + series[3] % 64           # near the largest 16-bit value
+    series[4, nout - 40:] += 80                  # into the last window
+    series[5] = 1500                             # constant
+    for big in (False, True):
+        if big:
+            series[0] += 1 << 21                 # int32 only: beyond the fast forms
+            series[6, ::2] = 0
+        ref_ev = oracle.find_events(oracle.boxcar(series, widths), 5.0)
+        s1, s2, thr = _ref_stats(oracle.boxcar(series, widths), 5.0)
+        for u16 in (False,) if big else (True, False):
+            ev, (g1, g2, gt) = _find(series, widths, 5.0, u16, capacity=1 << 18)
+            assert (g1 == s1).all() and (g2 == s2).all() and (gt == thr).all(), (big, u16)
+            events_equal(ev, ref_ev)
+
+
+def test_statistics_square_sums_use_all_32_bits():
+    """Windows that span just under 2^14: a thread's 16 squares sum to nearly
+    2^32."""
+    nout = 8192 + 511
+    series = np.zeros((2, nout), np.int64)
+    series[0, ::512] = 2 * 16000                 # +-16000 around a mean of 62.5
+    series[1, 100:8200:1024] = 16000
+    for widths in ([1, 2, 4, 256, 512], [2, 4, 8, 512]):
+        s1, s2, thr = _ref_stats(oracle.boxcar(series, widths), 3.0)
+        for u16 in (True, False):
+            _, (g1, g2, gt) = _find(series, widths, 3.0, u16, capacity=1 << 18)
+            assert (g1 == s1).all() and (g2 == s2).all() and (gt == thr).all(), u16
