@@ -667,10 +667,12 @@ __global__ __launch_bounds__(kThreads) void boxcar_stats_kernel(const T* __restr
 // take half the LDS as well (20 KiB a block), and rows of any alignment load in
 // aligned quads.  Bound by VALU issue as before, with less to issue: find_peaks
 // on the survey series 1029 -> 851 us (10 widths), on 301 int32 rows of odd
-// length 164 -> 131.  Six waves per SIMD with eight steps unrolled: five 865,
-// seven 922 (two steps), four steps 952.
-// Windows that span more (bright pulses, a drifting baseline) take 32-bit sums
-// in two halves, large values and ragged ones the general code.
+// length 164 -> 133.  Eight steps unrolled (four: 952 us).  Five waves per SIMD
+// for uint16, four for int32 (whose quads take twice the registers): one more
+// spills the 32-bit form's sums (the drifting series 1330 us) and gains nothing.
+// Windows that span more (bright pulses, a drifting baseline) put the same sums
+// into LDS with 32 bits, half the segment at a time (a survey series that all
+// drifts: 963 us, 920 before); large values and ragged ones take the general code.
 // ----------------------------------------------------------------------------
 constexpr int kSegLen = 8192;                       // positions per segment
 constexpr int kHalfLen = kSegLen / 2;
@@ -682,7 +684,10 @@ constexpr int kMaxWidth16 = kWinSamples - 3 - kSegLen;
 // LDS words: the 16-bit running sums (up to 3 places on), or half a window's
 // 32-bit ones, or a value of 8 bytes per pair of lanes and width (16 widths)
 constexpr int kPairStride = kThreads / 2 + 16;
-constexpr int kLds16Words = kHalfLen + kMaxWidth16 + 2;
+constexpr int kHalfRounds = kRounds - 4;            // rounds that half a segment's window takes
+constexpr int kLds16Words = 4 * kThreads * kHalfRounds;
+static_assert(kHalfLen == 4 * 4 * kThreads, "a half starts at a round");
+static_assert(kLds16Words >= kHalfLen + kMaxWidth16 + 3, "half a window fits");
 static_assert(kLds16Words * 2 >= kWinSamples + 4, "16-bit sums fit");
 static_assert(kLds16Words >= 2 * 16 * kPairStride, "reductions fit");
 
@@ -762,9 +767,8 @@ __device__ __forceinline__ bool stats_reduce(const uint64_t (&s2)[NW], const int
 // This lane's width (lane wi < NW) and the wave's share of its sum of boxcars
 // over n positions, by telescoping: sum_p (P(p + w) - P(p)) = sum_{i < w}
 // (P(n + i) - P(i)).  diff(i) gives the i-th term; lane l takes i = i0 + l, a DPP
-// scan gives the prefix, lane wi fetches the one at w - 1.  |term| < 2^25, or
-// any unsigned 32-bit term when WIDE (its 16-bit halves are scanned apart).
-template <bool WIDE, int NW, typename F>
+// scan gives the prefix, lane wi fetches the one at w - 1.  |term| < 2^25.
+template <int NW, typename F>
 __device__ __forceinline__ int64_t telescoped(const int (&w)[NW], F diff) {
     const int lane = threadIdx.x & 63;
     int myw = 0;
@@ -778,15 +782,7 @@ __device__ __forceinline__ int64_t telescoped(const int (&w)[NW], F diff) {
         const int d = i < w[NW - 1] ? diff(i) : 0;
         const int l = myw - 1 - i0;
         const int src = min(max(l, 0), 63);
-        int64_t got;
-        if (WIDE) {
-            const uint32_t a = wave_incl_scan(static_cast<uint32_t>(d) & 0xFFFFu);
-            const uint32_t b = wave_incl_scan(static_cast<uint32_t>(d) >> 16);
-            got = static_cast<int64_t>(__shfl(static_cast<int>(a), src, 64)) +
-                  (static_cast<int64_t>(__shfl(static_cast<int>(b), src, 64)) << 16);
-        } else {
-            got = __shfl(static_cast<int>(wave_incl_scan(static_cast<uint32_t>(d))), src, 64);
-        }
+        const int got = __shfl(static_cast<int>(wave_incl_scan(static_cast<uint32_t>(d))), src, 64);
         if (l >= 0) s1 += got;
     }
     return s1;
@@ -834,7 +830,7 @@ struct Quad<int32_t> {
 // One (DM, segment) per block.  `in` is aligned to four samples; w_max <=
 // kMaxWidth16; every width even, but for the first one when ODD1.
 template <typename T, int NW, bool ODD1>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NW <= 10 ? 6 : 5))) void boxcar_stats16_kernel(const T* __restrict__ in, int64_t nout,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 5 : 4))) void boxcar_stats16_kernel(const T* __restrict__ in, int64_t nout,
                                                                   int64_t nbx, dd::Widths W, int nseg,
                                                                   dd::PeaksWs ws) {
     __shared__ uint4 lds16[(kLds16Words + 3) / 4];
@@ -908,6 +904,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NW <= 
         const uint32_t pre = static_cast<uint32_t>(
             __builtin_amdgcn_readlane(static_cast<int>(tex), i * (kThreads / 64) + wave));
         const uint32_t base = pre + excl[i] - static_cast<uint32_t>(c) * 4u * static_cast<uint32_t>(i * kThreads + t);
+        excl[i] = base;   // P'(4 g) from here on
         const int p0 = static_cast<int>(base);
         const int p1 = static_cast<int>(v[i].s1(base) - c);
         const int p2 = static_cast<int>(v[i].s2(base) - 2 * c);
@@ -955,6 +952,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NW <= 
                         static_cast<int64_t>(c) * w_max + (1 << 14) < (1 << 25);
     const int64_t idx0 = static_cast<int64_t>(d) * nseg + seg;
     const int64_t stride = static_cast<int64_t>(gridDim.y) * nseg;
+    // width t / 16's totals of B from those of B' = B - c w (lane 16 wi)
+    auto store = [&](uint64_t a2, int am, int64_t a1) {
+        const int64_t cw = static_cast<int64_t>(c) * W.w[t >> 4];
+        const int64_t i = idx0 + (t >> 4) * stride;
+        ws.part_s1[i] = static_cast<uint64_t>(a1 + npos * cw);
+        ws.part_s2lo[i] = a2 + static_cast<uint64_t>(2 * cw * a1 + npos * cw * cw);
+        ws.part_s2hi[i] = 0u;
+        ws.part_max[i] = static_cast<uint32_t>(am + static_cast<int>(cw));
+    };
     if (narrow) {
         uint32_t sq[2][NW];   // at most 16 squares below 2^28 each
         i16x2 mx[NW];
@@ -1002,7 +1008,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NW <= 
             }
         }
         const int16_t* ph = reinterpret_cast<const int16_t*>(half) + k0 + off;
-        const int64_t s1 = telescoped<false, NW>(w, [&](int i) { return static_cast<int>(ph[npos + i]) - ph[i]; });
+        const int64_t s1 = telescoped<NW>(w, [&](int i) { return static_cast<int>(ph[npos + i]) - ph[i]; });
         uint64_t s2[NW];
         int m32[NW];
 #pragma unroll
@@ -1014,70 +1020,57 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NW <= 
         uint64_t a2;
         int am;
         int64_t a1;
-        if (stats_reduce<NW>(s2, m32, s1, lds, &a2, &am, &a1)) {
-            const int wi = t >> 4;
-            const int64_t cw = static_cast<int64_t>(c) * W.w[wi];
-            const int64_t i = idx0 + wi * stride;
-            ws.part_s1[i] = static_cast<uint64_t>(a1 + npos * cw);
-            ws.part_s2lo[i] = a2 + static_cast<uint64_t>(2 * cw * a1 + npos * cw * cw);
-            ws.part_s2hi[i] = 0u;
-            ws.part_max[i] = static_cast<uint32_t>(am + static_cast<int>(cw));
-        }
+        if (stats_reduce<NW>(s2, m32, s1, lds, &a2, &am, &a1)) store(a2, am, a1);
         return;
     }
-    // 32-bit running sums of half the segment at a time
-    __shared__ uint32_t wave_tot[kThreads / 64];
-    __shared__ uint32_t vhalf[2];
-    __shared__ uint64_t red1[kThreads / 64][NW];
-    __shared__ u128 red2[kThreads / 64][NW];
-    __shared__ uint32_t redm[kThreads / 64][NW];
-    const T* row = in + static_cast<int64_t>(d) * nout;
-    if (t < 2) vhalf[t] = 0u;
-    if (npos == kSegLen) {
+    // the same with 32-bit running sums: |B'| at most the span, every square
+    // sum below 2^13 x 2^50
+    if (npos == kSegLen && vmax < (1u << 17) && smax < (1 << 23) && smin < (1 << 23) &&
+        static_cast<int64_t>(c) * w_max < (1 << 24)) {
         uint64_t s2[NW];
         int mx[NW];
         int64_t s1 = 0;
 #pragma unroll
         for (int wi = 0; wi < NW; ++wi) {
             s2[wi] = 0;
-            mx[wi] = 0;
+            mx[wi] = INT32_MIN;
         }
-        bool small = true;
-        for (int hf = 0; hf < 2 && small; ++hf) {
+        const int* ps = reinterpret_cast<const int*>(lds) + k0;   // P' from the half's first position on
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+            __syncthreads();   // the 16-bit sums, the first half's are no longer needed
+#pragma unroll
+            for (int r = 0; r < kHalfRounds; ++r) {
+                const int i = 4 * hf + r;
+                lds16[r * kThreads + t] = make_uint4(excl[i], v[i].s1(excl[i]) - c, v[i].s2(excl[i]) - 2 * c,
+                                                     v[i].s3(excl[i]) - 3 * c);
+            }
             __syncthreads();
-            load_prefix(row, nout, s0 + hf * kHalfLen - 1, kHalfLen + w_max + 1, lds, wave_tot, &vhalf[hf]);
-            // every boxcar below 2^25, every sum of kHalfLen samples below 2^32
-            const uint64_t bmax = static_cast<uint64_t>(vhalf[hf]) * static_cast<uint64_t>(w_max);
-            small = bmax < (uint64_t(1) << 25) && vhalf[hf] < (1u << 20);
-            if (!small) break;
-            const uint32_t* base = lds + 1 + t;
-#pragma unroll 2
+            const int* base = ps + t;
+#pragma unroll 4
             for (int j = 0; j < kHalfLen / kThreads; ++j) {
-                const uint32_t p0 = base[j * kThreads];
+                const int p0 = base[j * kThreads];
 #pragma unroll
                 for (int wi = 0; wi < NW; ++wi) {
-                    const uint32_t b = base[j * kThreads + w[wi]] - p0;
-                    s2[wi] += static_cast<uint64_t>(b) * b;
-                    mx[wi] = max(mx[wi], static_cast<int>(b));
+                    const int b = base[j * kThreads + w[wi]] - p0;
+                    s2[wi] += static_cast<uint64_t>(static_cast<int64_t>(b) * b);
+                    mx[wi] = max(mx[wi], b);
                 }
             }
-            s1 += telescoped<true, NW>(w, [&](int i) { return static_cast<int>(lds[1 + kHalfLen + i] - lds[1 + i]); });
+            s1 += telescoped<NW>(w, [&](int i) { return ps[kHalfLen + i] - ps[i]; });
         }
         __syncthreads();
-        if (small) {
-            uint64_t a2;
-            int am;
-            int64_t a1;
-            if (stats_reduce<NW>(s2, mx, s1, lds, &a2, &am, &a1)) {
-                const int64_t i = idx0 + (t >> 4) * stride;
-                ws.part_s1[i] = static_cast<uint64_t>(a1);
-                ws.part_s2lo[i] = a2;
-                ws.part_s2hi[i] = 0u;
-                ws.part_max[i] = static_cast<uint32_t>(am);
-            }
-            return;
-        }
+        uint64_t a2;
+        int am;
+        int64_t a1;
+        if (stats_reduce<NW>(s2, mx, s1, lds, &a2, &am, &a1)) store(a2, am, a1);
+        return;
     }
+    __shared__ uint32_t wave_tot[kThreads / 64];
+    __shared__ uint64_t red1[kThreads / 64][NW];
+    __shared__ u128 red2[kThreads / 64][NW];
+    __shared__ uint32_t redm[kThreads / 64][NW];
+    const T* row = in + static_cast<int64_t>(d) * nout;
     // any values, any length: 128-bit sums, one width after the other
     for (int hf = 0; hf < 2; ++hf) {
         __syncthreads();
