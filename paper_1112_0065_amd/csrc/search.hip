@@ -213,18 +213,29 @@ __global__ __launch_bounds__(kThreads) void boxcar_kernel(const T* __restrict__ 
 // Baseline (red-noise) removal by a running mean (section 2.3, first
 // paragraph), streamed: out[t] = s[t + R] - floor(W(t) / (2R + 1)) + offset,
 // W(t) = sum_{j=t}^{t+2R} s[j], integer and exact.  One wave walks kBlSeg
-// outputs of one row, 64 consecutive outputs per row of a step (lane l takes
-// t = tc + 64 i + l, so every load is coalesced).  The window slides:
-// W(t + 1) - W(t) = s[t + 2R + 1] - s[t], so W(t) is W(t0) plus an exclusive
-// wave prefix (DPP scan) of those differences -- one scan per row of 64
-// outputs, every sample loaded once by the front cursor (and again, from
-// cache, by the middle and back ones), no halo re-read.  Integers modulo 2^32
-// are exact as every window sum is below 2^31; the division is the
-// multiply-shift below.  The loads of the next step are in flight while a
-// step is computed.
+// outputs of one row in steps of `bl_rows` rows of 256, a lane taking 4
+// consecutive outputs of each.  The window slides: W(t + 1) - W(t) =
+// s[t + 2R + 1] - s[t], so W(t) is W(t0) plus an exclusive wave prefix (DPP
+// scan) of those differences, one scan per 256 outputs; every sample comes once
+// through the front cursor and again, from cache, through the middle and back
+// ones.  Integers modulo 2^32 are exact as every window sum is below 2^31; the
+// division is a high multiply and a shift.
+// Bound by memory: the back cursor's samples have to outlast 2R + 1 others of
+// every stream in an XCD's 4 MB, so the outputs go past it (non-temporal stores,
+// from 128-byte boundaries of the output on, as a part of a line that leaves
+// early costs a second write), and long steps keep fewer waves on wider
+// accesses.  Survey series (1200 x 503812 samples of 16 bits, R = 2048), us: one
+// output per lane, 1024 per step 733; 4 per lane, steps of 1024 / 2048 / 4096
+// outputs 706 / 688 / 660; of 4096 with non-temporal stores 621, and aligned
+// 599 (R = 30 at 1000 x 333333: 364 before, 372 and 324).  32-bit samples: steps
+// of 2048, the same bytes in registers (1000 x 333333, R = 2048: 817 before, 661).
 constexpr int kBlSeg = 16384;       // outputs per wave
-constexpr int kBlRows = 16;         // rows of 64 outputs per step
-constexpr int kBlStep = 64 * kBlRows;
+template <typename T>
+constexpr int bl_rows() {
+    return sizeof(T) == 2 ? 16 : 8;   // rows of 256 outputs per step
+}
+constexpr int kBlShortRows = 4;     // of the shorter steps that follow
+constexpr int kBlTailRows = 16;     // rows of 64 outputs per step at a row's end
 
 // Inclusive prefix sum over the 64 lanes of a wave: shifts within each row
 // of 16 lanes, then the row totals carried across rows.
@@ -327,77 +338,144 @@ __device__ __forceinline__ const uint32_t* load_prefix_runs(const uint16_t* __re
     return lds + 3 + shift;
 }
 
+// Four consecutive samples at any element boundary, one 8- or 16-byte access.
 template <typename T>
-__device__ __forceinline__ void bl_load(__amdgpu_buffer_rsrc_t rs, int64_t tc, int lane, int radius,
-                                        uint32_t (&b)[kBlRows], uint32_t (&f)[kBlRows],
-                                        uint32_t (&m)[kBlRows]) {
-    const int sz = static_cast<int>(sizeof(T));
-    const int base = static_cast<int>(tc) + lane;
-#pragma unroll
-    for (int i = 0; i < kBlRows; ++i) {
-        b[i] = row_load(rs, (base + 64 * i) * sz, static_cast<T*>(nullptr));
-        f[i] = row_load(rs, (base + 64 * i + 2 * radius + 1) * sz, static_cast<T*>(nullptr));
-        m[i] = row_load(rs, (base + 64 * i + radius) * sz, static_cast<T*>(nullptr));
-    }
+struct __attribute__((packed, aligned(sizeof(T)))) Four {
+    T v[4];
+};
+
+// Writes o[0 .. 3], past the caches.
+template <typename U>
+__device__ __forceinline__ void bl_store(U* o, const int (&r)[4]) {
+    typedef U V4 __attribute__((ext_vector_type(4), aligned(sizeof(U))));
+    const V4 q = {static_cast<U>(r[0]), static_cast<U>(r[1]), static_cast<U>(r[2]), static_cast<U>(r[3])};
+    __builtin_nontemporal_store(q, reinterpret_cast<V4*>(o));
 }
 
 template <typename T, typename U>
 __global__ __launch_bounds__(kThreads) void baseline_kernel(const T* __restrict__ in, int ndm,
                                                             int64_t nout, int64_t nres, int radius,
-                                                            int offset, int64_t nseg, uint64_t magic,
+                                                            int offset, int64_t nseg, uint32_t magic,
                                                             int shift, U* __restrict__ out) {
     const int lane = threadIdx.x & 63;
-    // the wave's item, in scalar registers (so is everything derived from
-    // it, the row's buffer resource included: the loads need it uniform)
+    // the wave's item, in scalar registers (so is everything derived from it)
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
     const int64_t item = static_cast<int64_t>(blockIdx.x) * (kThreads / 64) + wave;
     if (item >= static_cast<int64_t>(ndm) * nseg) return;   // whole waves
     const int d = static_cast<int>(item / nseg);
-    const int64_t t0 = (item % nseg) * kBlSeg;
-    const int64_t t1 = min<int64_t>(t0 + kBlSeg, nres);
     const T* row = in + static_cast<int64_t>(d) * nout;
-    // a row stays below 2^31 bytes; offsets past it read as 0
-    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<T*>(row), 0, static_cast<int>(nout * static_cast<int64_t>(sizeof(T))), kRowRsrcWord3);
-    const int sz = static_cast<int>(sizeof(T));
-    const int win = 2 * radius + 1;
-    // front start: the sum of s[t0 .. t0 + 2R]
-    uint32_t acc = 0;
-    for (int base = static_cast<int>(t0) + lane; base < static_cast<int>(t0) + win; base += kBatch * 64) {
-        uint32_t v[kBatch];
-#pragma unroll
-        for (int k = 0; k < kBatch; ++k) {
-            const int i = base + k * 64;
-            v[k] = i < static_cast<int>(t0) + win ? row_load(rs, i * sz, static_cast<T*>(nullptr)) : 0u;
-        }
-#pragma unroll
-        for (int k = 0; k < kBatch; ++k) acc += v[k];
-    }
-    // W(t0): the sum of s[t0 .. t0 + 2R]
-    uint32_t wcur = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(wave_incl_scan(acc)), 63));
     U* o = out + static_cast<int64_t>(d) * nres;
-    uint32_t b[kBlRows], f[kBlRows], m[kBlRows];
-    bl_load<T>(rs, t0, lane, radius, b, f, m);
-    for (int64_t tc = t0; tc < t1; tc += kBlStep) {
-        uint32_t nb[kBlRows], nf[kBlRows], nm[kBlRows];
-        bl_load<T>(rs, tc + kBlStep, lane, radius, nb, nf, nm);   // next step, in flight
+    // outputs before the row's first 128-byte line of 64-element pieces; the
+    // row's first wave takes them, and every segment starts on such a boundary
+    const int head = static_cast<int>(min<int64_t>(
+        -static_cast<int64_t>(reinterpret_cast<uintptr_t>(o) / sizeof(U)) & 63, nres));
+    const int64_t seg = item % nseg;
+    const int64_t t0 = seg == 0 ? 0 : seg * kBlSeg + head;
+    const int64_t t1 = min<int64_t>((seg + 1) * kBlSeg + head, nres);
+    if (t0 >= t1) return;
+    const int win = 2 * radius + 1;
+    // floor(sum / win), exact for sum < 2^31 (see the launcher)
+    auto mean = [&](uint32_t sum) {
+        return static_cast<int>(win == 1 ? sum : __umulhi(sum, magic) >> shift);
+    };
+    // W(t0): the sum of s[t0 .. t0 + 2R]
+    uint32_t acc = 0;
+    {
+        const T* p = row + t0;
+        int i = 0;
+        for (; i + 1024 <= win; i += 1024) {
+            Four<T> f[4];
 #pragma unroll
-        for (int i = 0; i < kBlRows; ++i) {
-            const uint32_t delta = f[i] - b[i];        // W(t + 1) - W(t)
-            const uint32_t incl = wave_incl_scan(delta);
-            const uint32_t sum = wcur + incl - delta;   // W(t)
-            // floor(sum / win) as a multiply and shift (exact for sum < 2^31)
-            const uint32_t mean = static_cast<uint32_t>((static_cast<uint64_t>(sum) * magic) >> shift);
+            for (int k = 0; k < 4; ++k) f[k] = *reinterpret_cast<const Four<T>*>(p + i + 256 * k + 4 * lane);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc += static_cast<uint32_t>(f[k].v[j]);
+        }
+        uint32_t v[16];   // up to 1023 left: all the loads at once
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = static_cast<uint32_t>(p[min(i + 64 * k + lane, win - 1)]);
+#pragma unroll
+        for (int k = 0; k < 16; ++k) acc += i + 64 * k + lane < win ? v[k] : 0u;
+    }
+    uint32_t wcur = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(wave_incl_scan(acc)), 63));
+    int64_t tc = t0;
+    if (seg == 0 && head > 0) {
+        const int t = min(lane, head - 1);
+        const uint32_t bk = static_cast<uint32_t>(row[t]);
+        const uint32_t fr = static_cast<uint32_t>(row[min<int64_t>(t + win, nout - 1)]);
+        const int md = static_cast<int>(row[t + radius]);
+        const uint32_t delta = lane < head ? fr - bk : 0u;
+        const uint32_t incl = wave_incl_scan(delta);
+        if (lane < head) o[lane] = static_cast<U>(md - mean(wcur + incl - delta) + offset);
+        wcur += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
+        tc = head;
+    }
+    // whole steps, every sample they touch inside the row
+    auto walk = [&](auto rows_c) {
+        constexpr int rows = decltype(rows_c)::value, step = 256 * rows;
+        for (; tc + step <= t1 && tc + step + win <= nout; tc += step) {
+            const T* p = row + tc + 4 * lane;
+            Four<T> b[rows], f[rows], m[rows];
+#pragma unroll
+            for (int i = 0; i < rows; ++i) {
+                b[i] = *reinterpret_cast<const Four<T>*>(p + 256 * i);
+                f[i] = *reinterpret_cast<const Four<T>*>(p + 256 * i + win);
+                m[i] = *reinterpret_cast<const Four<T>*>(p + 256 * i + radius);
+            }
+#pragma unroll
+            for (int i = 0; i < rows; ++i) {
+                uint32_t w[5];   // W(t + j) - W(first of the row)
+                w[0] = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    w[j + 1] = w[j] + static_cast<uint32_t>(f[i].v[j]) - static_cast<uint32_t>(b[i].v[j]);
+                const uint32_t incl = wave_incl_scan(w[4]);
+                const uint32_t first = wcur + incl - w[4];
+                int r[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    r[j] = static_cast<int>(m[i].v[j]) - mean(first + w[j]) + offset;
+                bl_store(o + tc + 256 * i + 4 * lane, r);
+                wcur += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
+            }
+        }
+    };
+    walk(std::integral_constant<int, bl_rows<T>()>{});
+    walk(std::integral_constant<int, kBlShortRows>{});
+    // the rest, one output per lane and row.  Indices are clamped to the row;
+    // the sample that enters after the row's last output lies past its end and
+    // reaches no output.
+    struct Tail {
+        uint32_t bk[kBlTailRows], fr[kBlTailRows];
+        int md[kBlTailRows];
+    };
+    auto load = [&](Tail& q, int64_t at) {
+#pragma unroll
+        for (int i = 0; i < kBlTailRows; ++i) {
+            const int64_t t = min<int64_t>(at + 64 * i + lane, t1 - 1);
+            q.bk[i] = static_cast<uint32_t>(row[t]);
+            q.fr[i] = static_cast<uint32_t>(row[min<int64_t>(t + win, nout - 1)]);
+            q.md[i] = static_cast<int>(row[t + radius]);
+        }
+    };
+    if (tc >= t1) return;
+    Tail cur, nxt;
+    load(cur, tc);
+    for (;;) {
+        const int64_t next = tc + 64 * kBlTailRows;
+        if (next < t1) load(nxt, next);   // in flight while this one is computed
+#pragma unroll
+        for (int i = 0; i < kBlTailRows; ++i) {
             const int64_t t = tc + 64 * i + lane;
-            if (t < t1) o[t] = static_cast<U>(static_cast<int32_t>(m[i]) - static_cast<int32_t>(mean) + offset);
+            const uint32_t delta = cur.fr[i] - cur.bk[i];
+            const uint32_t incl = wave_incl_scan(delta);
+            if (t < t1) o[t] = static_cast<U>(cur.md[i] - mean(wcur + incl - delta) + offset);
             wcur += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
         }
-#pragma unroll
-        for (int i = 0; i < kBlRows; ++i) {
-            b[i] = nb[i];
-            f[i] = nf[i];
-            m[i] = nm[i];
-        }
+        if (next >= t1) break;
+        tc = next;
+        cur = nxt;
     }
 }
 
@@ -1743,8 +1821,11 @@ hipError_t launch_baseline(const void* in, int in_u16, int ndm, int64_t nout, in
     const uint32_t win = 2u * static_cast<uint32_t>(radius) + 1u;
     int lg = 0;
     while ((1u << lg) < win) ++lg;
-    const int shift = 31 + lg;
-    const uint64_t magic = ((uint64_t(1) << shift) + win - 1) / win;
+    // k >= 32 and M < 2^32 but for win = 1 (no division): the high half of the
+    // product, then a shift by k - 32.
+    const int k = 31 + lg;
+    const uint32_t magic = static_cast<uint32_t>(((uint64_t(1) << k) + win - 1) / win);
+    const int shift = std::max(k - 32, 0);
     const int64_t nseg = (nres + kBlSeg - 1) / kBlSeg;
     const int64_t waves = static_cast<int64_t>(ndm) * nseg;
     const dim3 grid(static_cast<unsigned>((waves + kThreads / 64 - 1) / (kThreads / 64)));

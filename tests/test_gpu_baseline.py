@@ -38,6 +38,21 @@ def test_matches_oracle(radius):
         assert (got == ref).all(), (radius, in_u16, out_u16)
 
 
+@pytest.mark.parametrize("nres", [1, 255, 1025, 4095, 4096, 4097, 16383, 16385, 16447, 16384 + 4096 + 2049])
+def test_lengths_around_a_step(nres):
+    # steps of 4096 (16-bit) or 2048 (32-bit) outputs, then of 1024, then rows of
+    # 64 to the end of a segment of 16384; odd lengths put the rows at odd samples
+    # and the first segment's end up to 63 outputs later
+    rng = np.random.default_rng(nres)
+    for radius in (0, 3, 600):
+        s = rng.integers(0, 3073, size=(3, nres + 2 * radius))
+        s[1] = 3072
+        ref = oracle.baseline_remove(s, radius, 3072)
+        for in_u16, out_u16 in [(True, True), (True, False), (False, True), (False, False)]:
+            got = _run(s, radius, 3072, in_u16, out_u16)
+            assert (got == ref).all(), (radius, in_u16, out_u16)
+
+
 def test_red_noise_removed_pulses_kept():
     from paper_1112_0065_amd import _lib as L
     torch = torch_dev()
