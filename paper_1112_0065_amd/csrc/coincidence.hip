@@ -13,11 +13,12 @@
 // exact integer sums; exceeding k sigma means the strict S/N > k, decided exactly
 // as in the sigma-cut (z >= ceil((S1 + isqrt(floor(k^2 D)) + 1) / n)).
 //
-// Kernels: zero-DM sums straight from the packed bytes (popcounts of the two
-// bit-planes of each 32-bit word), per-block partial sums, one thread per beam
-// for the exact cut level, and one thread per sample for the vote.  All of it
-// is bound by the one read of the packed input.
+// Kernels: zero-DM sums of all beams straight from the packed bytes (popcounts
+// of the two bit-planes of each 32-bit word) with their partial sums, one wave
+// per beam for the exact cut level, and four samples per thread for the vote.
+// All of it is bound by the one read of the packed input.
 #include <algorithm>
+#include <type_traits>
 
 #include "dedisp_internal.hpp"
 #include "intmath.hpp"
@@ -34,64 +35,26 @@ __device__ __forceinline__ uint32_t level_sum(uint32_t w) {
            2u * static_cast<uint32_t>(__builtin_popcount(w & 0xAAAAAAAAu));
 }
 
-// 1024 channels (256 bytes per sample): 16 lanes per sample, one 16-byte load
-// each, 4 samples per wave and step; a 16-lane reduction finishes each sum.
-__global__ __launch_bounds__(kCThreads) void zero_dm_256_kernel(const uint8_t* __restrict__ in,
-                                                                int64_t nsamps,
-                                                                int32_t* __restrict__ z) {
-    const int lane = threadIdx.x & 63;
-    const int64_t wave = (static_cast<int64_t>(blockIdx.x) * kCThreads + threadIdx.x) >> 6;
-    const int64_t nwaves = (static_cast<int64_t>(gridDim.x) * kCThreads) >> 6;
-    const int sub = lane >> 4;      // sample within the step
-    const int part = lane & 15;     // 16-byte part of the sample
-    for (int64_t t0 = wave * 4; t0 < nsamps; t0 += nwaves * 4) {
-        const int64_t t = t0 + sub;
-        uint32_t s = 0;
-        if (t < nsamps) {
-            const uint4 v = *reinterpret_cast<const uint4*>(in + t * 256 + part * 16);
-            s = level_sum(v.x) + level_sum(v.y) + level_sum(v.z) + level_sum(v.w);
-        }
-#pragma unroll
-        for (int o = 8; o >= 1; o >>= 1) s += __shfl_xor(s, o, 16);
-        if (part == 0 && t < nsamps) z[t] = static_cast<int32_t>(s);
-    }
-}
+struct BeamsIn {
+    const uint8_t* p[64];
+};
 
-// Any nchans (multiple of 4): one thread per sample, whole words then the
-// remaining bytes.
-__global__ __launch_bounds__(kCThreads) void zero_dm_any_kernel(const uint8_t* __restrict__ in,
-                                                                int64_t nsamps, int bps,
-                                                                int32_t* __restrict__ z) {
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * kCThreads + threadIdx.x;
-    if (t >= nsamps) return;
-    const uint8_t* p = in + t * bps;
-    uint32_t s = 0;
-    int i = 0;
-    if ((reinterpret_cast<uintptr_t>(p) & 3) == 0)
-        for (; i + 4 <= bps; i += 4) s += level_sum(*reinterpret_cast<const uint32_t*>(p + i));
-    for (; i < bps; ++i) s += level_sum(p[i]);
-    z[t] = static_cast<int32_t>(s);
-}
+// Sixteen bytes of a sample at any address, one load.
+struct __attribute__((packed, aligned(1))) Piece {
+    uint32_t w[4];
+};
 
-// Partial S1 and S2 of blocks of kStatBlock samples: grid (nblocks, nbeams).
-// z <= 3*nchans < 2^16, so S2 of up to 2^31 samples fits 64 bits.
-__global__ __launch_bounds__(kCThreads) void zero_dm_stats_kernel(const int32_t* __restrict__ z,
-                                                                  int64_t nsamps, int nblk,
-                                                                  uint64_t* __restrict__ p1,
+__global__ __launch_bounds__(kCThreads) void zero_dm_clear_kernel(int n, uint64_t* __restrict__ p1,
                                                                   uint64_t* __restrict__ p2) {
+    const int i = blockIdx.x * kCThreads + threadIdx.x;
+    if (i < n) p1[i] = p2[i] = 0ull;
+}
+
+// Adds a block's partial sums into those of its kStatBlock samples.  The sums
+// are integers: the order in which blocks add them does not matter.
+// z <= 3*nchans < 2^16, so S2 of up to 2^31 samples fits 64 bits.
+__device__ __forceinline__ void add_stats(uint64_t a1, uint64_t a2, uint64_t* p1, uint64_t* p2) {
     __shared__ uint64_t r1[kCThreads / 64], r2[kCThreads / 64];
-    const int b = blockIdx.y;
-    const int64_t t0 = static_cast<int64_t>(blockIdx.x) * kStatBlock;
-    const int32_t* zb = z + static_cast<int64_t>(b) * nsamps;
-    uint64_t a1 = 0, a2 = 0;
-    for (int i = threadIdx.x; i < kStatBlock; i += kCThreads) {
-        const int64_t t = t0 + i;
-        if (t < nsamps) {
-            const uint64_t v = static_cast<uint32_t>(zb[t]);
-            a1 += v;
-            a2 += v * v;
-        }
-    }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
         a1 += __shfl_xor(a1, o, 64);
@@ -108,51 +71,195 @@ __global__ __launch_bounds__(kCThreads) void zero_dm_stats_kernel(const int32_t*
             s1 += r1[w];
             s2 += r2[w];
         }
-        p1[static_cast<int64_t>(b) * nblk + blockIdx.x] = s1;
-        p2[static_cast<int64_t>(b) * nblk + blockIdx.x] = s2;
+        atomicAdd(reinterpret_cast<unsigned long long*>(p1), static_cast<unsigned long long>(s1));
+        atomicAdd(reinterpret_cast<unsigned long long*>(p2), static_cast<unsigned long long>(s2));
     }
 }
 
-// One thread per beam: exact sums and the cut level (thr[b] = -1: D == 0,
-// the beam never votes).  Thread 0 also clears the masked-sample counter.
-__global__ void zero_dm_threshold_kernel(int nbeams, int nblk, int64_t nsamps, uint32_t kmant,
-                                         int kexp2, const uint64_t* __restrict__ p1,
-                                         const uint64_t* __restrict__ p2,
-                                         int64_t* __restrict__ thr,
-                                         unsigned long long* __restrict__ count) {
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b == 0) *count = 0ull;
-    if (b >= nbeams) return;
-    uint64_t s1 = 0;
-    u128 s2 = 0;
-    for (int g = 0; g < nblk; ++g) {
-        s1 += p1[static_cast<int64_t>(b) * nblk + g];
-        s2 += p2[static_cast<int64_t>(b) * nblk + g];
+// Sum over groups of G lanes, left in all of them.
+template <int G>
+__device__ __forceinline__ uint32_t group_sum(uint32_t s) {
+    auto dpp = [&](auto ctrl) {
+        s += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(s), decltype(ctrl)::value,
+                                                               0xF, 0xF, true));
+    };
+    if constexpr (G >= 2) dpp(std::integral_constant<int, 0xB1>{});     // lane ^ 1
+    if constexpr (G >= 4) dpp(std::integral_constant<int, 0x4E>{});     // lane ^ 2
+    if constexpr (G >= 8) dpp(std::integral_constant<int, 0x141>{});    // mirror of 8 lanes
+    if constexpr (G >= 16) dpp(std::integral_constant<int, 0x140>{});   // mirror of 16 lanes
+    if constexpr (G >= 32) s += __shfl_xor(s, 16, 64);
+    if constexpr (G >= 64) s += __shfl_xor(s, 32, 64);
+    return s;
+}
+
+// Samples of 16 bytes or more: G lanes per sample, a 16-byte piece each (the
+// last piece is read so that it ends with the sample, and the bytes that it
+// shares with the one before are masked out), kZUnroll loads in flight per lane.
+// Grid: (blocks of `iters` * 4 waves * kZUnroll * 64 / G samples, beams); a
+// block lies inside one block of partial sums.  Bound by the read.  The whole mask
+// of 13 beams, us, with one launch per beam and separate partial sums (and, but
+// for 1024 channels, one thread per sample), and now: 1024 channels x 2^19
+// samples 398 -> 358 (the read alone 356 at a copy's rate), x 2^17 173 -> 122;
+// 256 x 2^18 210 -> 75; 1000 x 2^18 2740 -> 210; 2048 x 2^17 919 -> 199.
+constexpr int kZUnroll = 8;
+
+template <int G>
+__global__ __launch_bounds__(kCThreads) void zero_dm_kernel(BeamsIn in, int64_t nsamps, int bps,
+                                                            int iters, int nblk,
+                                                            int32_t* __restrict__ z,
+                                                            uint64_t* __restrict__ p1,
+                                                            uint64_t* __restrict__ p2) {
+    constexpr int kPer = 64 / G;                 // samples per load of a wave
+    constexpr int kStep = kPer * kZUnroll;       // and per step
+    constexpr int kPick = G < kZUnroll ? G : kZUnroll;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x >> 6));
+    const int sub = lane / G, part = lane % G;
+    const uint8_t* beam = in.p[blockIdx.y];
+    int32_t* zb = z + static_cast<int64_t>(blockIdx.y) * nsamps;
+    const int pieces = (bps + 15) / 16;
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * (kCThreads / 64) * kStep * iters;
+    uint64_t a1 = 0, a2 = 0;
+    for (int it = 0; it < iters; ++it) {
+        const int64_t tb = first + (static_cast<int64_t>(it) * (kCThreads / 64) + wave) * kStep;
+        if (tb >= nsamps) break;                 // whole waves
+        uint32_t s[kZUnroll] = {};
+        for (int c0 = 0; c0 < pieces; c0 += G) {
+            const int c = min(c0 + part, pieces - 1);
+            const int off = min(16 * c, bps - 16);
+            // bytes of this piece that the one before has, or all of them
+            const int skip = c0 + part < pieces ? 16 * c - off : 16;
+            uint32_t keep[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int n = min(max(skip - 4 * k, 0), 4);
+                keep[k] = n == 4 ? 0u : 0xFFFFFFFFu << (8 * n);
+            }
+            Piece v[kZUnroll];
+#pragma unroll
+            for (int u = 0; u < kZUnroll; ++u) {
+                const int64_t t = min<int64_t>(tb + u * kPer + sub, nsamps - 1);
+                v[u] = *reinterpret_cast<const Piece*>(beam + t * bps + off);
+            }
+#pragma unroll
+            for (int u = 0; u < kZUnroll; ++u)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) s[u] += level_sum(v[u].w[k] & keep[k]);
+        }
+#pragma unroll
+        for (int u = 0; u < kZUnroll; ++u) s[u] = group_sum<G>(s[u]);
+        // lane `part` of a group writes the group's sample of load u0 + part
+#pragma unroll
+        for (int u0 = 0; u0 < kZUnroll; u0 += kPick) {
+            uint32_t x = s[u0];
+#pragma unroll
+            for (int j = 1; j < kPick; ++j) x = part == j ? s[u0 + j] : x;
+            const int64_t t = tb + (u0 + part) * kPer + sub;
+            if (part < kPick && t < nsamps) {
+                zb[t] = static_cast<int32_t>(x);
+                a1 += x;
+                a2 += static_cast<uint64_t>(x) * x;
+            }
+        }
     }
+    const int64_t g = static_cast<int64_t>(blockIdx.y) * nblk + first / kStatBlock;
+    add_stats(a1, a2, p1 + g, p2 + g);
+}
+
+// Samples of fewer than 16 bytes: one thread per sample, whole words then the
+// remaining bytes.
+__global__ __launch_bounds__(kCThreads) void zero_dm_narrow_kernel(BeamsIn in, int64_t nsamps, int bps,
+                                                                   int nblk, int32_t* __restrict__ z,
+                                                                   uint64_t* __restrict__ p1,
+                                                                   uint64_t* __restrict__ p2) {
+    const int64_t first = static_cast<int64_t>(blockIdx.x) * kCThreads;
+    const int64_t t = first + threadIdx.x;
+    uint32_t s = 0;
+    if (t < nsamps) {
+        const uint8_t* p = in.p[blockIdx.y] + t * bps;
+        int i = 0;
+        if ((reinterpret_cast<uintptr_t>(p) & 3) == 0)
+            for (; i + 4 <= bps; i += 4) s += level_sum(*reinterpret_cast<const uint32_t*>(p + i));
+        for (; i < bps; ++i) s += level_sum(p[i]);
+        z[static_cast<int64_t>(blockIdx.y) * nsamps + t] = static_cast<int32_t>(s);
+    }
+    const int64_t g = static_cast<int64_t>(blockIdx.y) * nblk + first / kStatBlock;
+    add_stats(s, static_cast<uint64_t>(s) * s, p1 + g, p2 + g);
+}
+
+// One wave per beam: exact sums and the cut level (thr[b] = -1: D == 0,
+// the beam never votes).  The first also clears the masked-sample counter.
+__global__ __launch_bounds__(64) void zero_dm_threshold_kernel(
+    int nblk, int64_t nsamps, uint32_t kmant, int kexp2, const uint64_t* __restrict__ p1,
+    const uint64_t* __restrict__ p2, int64_t* __restrict__ thr,
+    unsigned long long* __restrict__ count) {
+    const int64_t b = blockIdx.x;
+    uint64_t s1 = 0, s2 = 0;
+    for (int g = threadIdx.x; g < nblk; g += 64) {
+        s1 += p1[b * nblk + g];
+        s2 += p2[b * nblk + g];
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        s1 += __shfl_xor(s1, o, 64);
+        s2 += __shfl_xor(s2, o, 64);
+    }
+    if (threadIdx.x != 0) return;
+    if (b == 0) *count = 0ull;
     thr[b] = cut_level(static_cast<uint64_t>(nsamps), s1, s2, kmant, kexp2, nullptr);
 }
 
-// One thread per sample: votes of the beams and the mask byte.
+// Four samples per thread: votes of the beams and the mask bytes.
+constexpr int kVote = 4;
+
 __global__ __launch_bounds__(kCThreads) void coincidence_vote_kernel(
     const int32_t* __restrict__ z, int64_t nsamps, int nbeams, int min_beams,
     const int64_t* __restrict__ thr, uint8_t* __restrict__ mask,
     unsigned long long* __restrict__ count) {
-    __shared__ unsigned long long bc;
-    if (threadIdx.x == 0) bc = 0ull;
+    struct __attribute__((packed, aligned(4))) Levels {
+        int32_t v[kVote];
+    };
+    struct __attribute__((packed, aligned(1))) Flags {
+        uint8_t m[kVote];
+    };
+    __shared__ unsigned int bc;
+    if (threadIdx.x == 0) bc = 0u;
     __syncthreads();
-    const int64_t t = static_cast<int64_t>(blockIdx.x) * kCThreads + threadIdx.x;
+    const int64_t t = (static_cast<int64_t>(blockIdx.x) * kCThreads + threadIdx.x) * kVote;
+    unsigned int n = 0;
     if (t < nsamps) {
-        int votes = 0;
-        for (int b = 0; b < nbeams; ++b) {
-            const int64_t th = thr[b];
-            votes += (th >= 0 && static_cast<int64_t>(z[static_cast<int64_t>(b) * nsamps + t]) >= th) ? 1 : 0;
+        const int64_t t4 = min<int64_t>(t, nsamps - kVote);   // the last four of the row
+        int votes[kVote] = {};
+        auto add = [&](int j, int64_t th, int32_t level) {
+            votes[j] += th >= 0 && static_cast<int64_t>(level) >= th ? 1 : 0;
+        };
+        if (t4 >= 0) {
+            for (int b = 0; b < nbeams; ++b) {
+                const Levels q = *reinterpret_cast<const Levels*>(z + static_cast<int64_t>(b) * nsamps + t4);
+                const int64_t th = thr[b];
+#pragma unroll
+                for (int j = 0; j < kVote; ++j) add(j, th, q.v[j]);
+            }
+            Flags f;
+#pragma unroll
+            for (int j = 0; j < kVote; ++j) {
+                f.m[j] = votes[j] >= min_beams ? 1 : 0;
+                n += t4 + j >= t ? f.m[j] : 0u;
+            }
+            *reinterpret_cast<Flags*>(mask + t4) = f;
+        } else {   // fewer than four samples
+            for (int64_t i = t; i < nsamps; ++i) {
+                votes[0] = 0;
+                for (int b = 0; b < nbeams; ++b) add(0, thr[b], z[static_cast<int64_t>(b) * nsamps + i]);
+                const bool m = votes[0] >= min_beams;
+                mask[i] = m ? 1 : 0;
+                n += m ? 1u : 0u;
+            }
         }
-        const bool m = votes >= min_beams;
-        mask[t] = m ? 1 : 0;
-        if (m) atomicAdd(&bc, 1ull);
     }
+    if (n) atomicAdd(&bc, n);
     __syncthreads();
-    if (threadIdx.x == 0 && bc) atomicAdd(count, bc);
+    if (threadIdx.x == 0 && bc) atomicAdd(count, static_cast<unsigned long long>(bc));
 }
 
 struct CoincLayout {
@@ -229,24 +336,39 @@ hipError_t launch_rfi_mask(const uint8_t* const* ins, int nbeams, int nchans, in
     int64_t* thr = reinterpret_cast<int64_t*>(w + l.o_thr);
     unsigned long long* count = reinterpret_cast<unsigned long long*>(w + l.o_count);
     const int bps = nchans / 4;
-    for (int b = 0; b < nbeams; ++b) {
-        int32_t* zb = z + static_cast<int64_t>(b) * nsamps;
-        if (bps == 256 && (reinterpret_cast<uintptr_t>(ins[b]) & 15) == 0) {
-            const int64_t waves = std::min<int64_t>((nsamps + 3) / 4, 256 * 64);
-            hipLaunchKernelGGL(zero_dm_256_kernel, dim3(static_cast<unsigned>((waves + 3) / 4)),
-                               dim3(kCThreads), 0, stream, ins[b], nsamps, zb);
-        } else {
-            hipLaunchKernelGGL(zero_dm_any_kernel,
-                               dim3(static_cast<unsigned>((nsamps + kCThreads - 1) / kCThreads)),
-                               dim3(kCThreads), 0, stream, ins[b], nsamps, bps, zb);
-        }
+    BeamsIn beams{};
+    for (int b = 0; b < nbeams; ++b) beams.p[b] = ins[b];
+    const int parts = nbeams * l.nblk;
+    hipLaunchKernelGGL(zero_dm_clear_kernel, dim3((parts + kCThreads - 1) / kCThreads), dim3(kCThreads), 0,
+                       stream, parts, p1, p2);
+    if (bps < 16) {
+        hipLaunchKernelGGL(zero_dm_narrow_kernel,
+                           dim3(static_cast<unsigned>((nsamps + kCThreads - 1) / kCThreads), nbeams),
+                           dim3(kCThreads), 0, stream, beams, nsamps, bps, l.nblk, z, p1, p2);
+    } else {
+        auto launch = [&](auto g) {
+            constexpr int G = decltype(g)::value;
+            // four steps per block, one where that leaves CUs without a block
+            constexpr int64_t step = int64_t(kCThreads / 64) * kZUnroll * (64 / G);
+            const int iters = (nsamps + 4 * step - 1) / (4 * step) * nbeams >= 1024 ? 4 : 1;
+            static_assert(kStatBlock % (4 * step) == 0, "a block lies inside one block of sums");
+            hipLaunchKernelGGL((zero_dm_kernel<G>),
+                               dim3(static_cast<unsigned>((nsamps + iters * step - 1) / (iters * step)), nbeams),
+                               dim3(kCThreads), 0, stream, beams, nsamps, bps, iters, l.nblk, z, p1, p2);
+        };
+        const int pieces = (bps + 15) / 16;
+        if (pieces <= 1) launch(std::integral_constant<int, 1>{});
+        else if (pieces <= 2) launch(std::integral_constant<int, 2>{});
+        else if (pieces <= 4) launch(std::integral_constant<int, 4>{});
+        else if (pieces <= 8) launch(std::integral_constant<int, 8>{});
+        else if (pieces <= 16) launch(std::integral_constant<int, 16>{});
+        else if (pieces <= 32) launch(std::integral_constant<int, 32>{});
+        else launch(std::integral_constant<int, 64>{});
     }
-    hipLaunchKernelGGL(zero_dm_stats_kernel, dim3(l.nblk, nbeams), dim3(kCThreads), 0, stream, z,
-                       nsamps, l.nblk, p1, p2);
-    hipLaunchKernelGGL(zero_dm_threshold_kernel, dim3(1), dim3(64), 0, stream, nbeams, l.nblk,
-                       nsamps, kmant, kexp2, p1, p2, thr, count);
+    hipLaunchKernelGGL(zero_dm_threshold_kernel, dim3(nbeams), dim3(64), 0, stream, l.nblk, nsamps, kmant,
+                       kexp2, p1, p2, thr, count);
     hipLaunchKernelGGL(coincidence_vote_kernel,
-                       dim3(static_cast<unsigned>((nsamps + kCThreads - 1) / kCThreads)),
+                       dim3(static_cast<unsigned>((nsamps + kCThreads * kVote - 1) / (kCThreads * kVote))),
                        dim3(kCThreads), 0, stream, z, nsamps, nbeams, min_beams, thr, mask, count);
     return hipGetLastError();
 }

@@ -56,6 +56,32 @@ def test_constant_and_ragged_beams():
     assert n >= 3
 
 
+@pytest.mark.parametrize("nchans", [4, 60, 64, 68, 128, 132, 256, 260, 512, 1000, 1024, 1028, 2048, 2052,
+                                    4096, 4100, 21844])
+def test_sample_sizes_and_alignments(nchans):
+    """Groups of 1 to 64 lanes per sample, a shared last piece of 16 bytes,
+    several pieces per lane, samples at any byte; 1 to 9001 samples (one to
+    several blocks of 8192, fewer than four for the vote)."""
+    from paper_1112_0065_amd import _lib as L
+    torch = torch_dev()
+    rng = np.random.default_rng(nchans)
+    for nsamps in (1, 3, 5, 2049, 9001):
+        packed = [rng.integers(0, 256, size=nsamps * nchans // 4, dtype=np.uint8) for _ in range(3)]
+        zs = [oracle.zero_dm_series(p, nsamps, nchans) for p in packed]
+        ref_mask, _, ref_thr = oracle.rfi_mask(zs, 1.0, 2)
+        for at in (0, 1, 6):
+            ins = [to_dev(np.concatenate([np.zeros(at, np.uint8), p]))[at:] for p in packed]
+            ws = torch.empty(L.dedisp_rfi_mask_workspace_bytes(3, nsamps), dtype=torch.uint8, device="cuda")
+            mask = torch.full((nsamps + 3,), 7, dtype=torch.uint8, device="cuda")
+            n = L.dedisp_rfi_mask(ins, nchans, nsamps, 1.0, 2, mask[:nsamps], ws)
+            z, thr = L.dedisp_rfi_mask_read_stats(ws, 3, nsamps)
+            got = mask.cpu().numpy()
+            assert (z == np.array(zs)).all(), (nsamps, at)
+            assert thr.tolist() == [-1 if t is None else t for t in ref_thr]
+            assert (got[:nsamps] == ref_mask).all() and n == int(ref_mask.sum())
+            assert (got[nsamps:] == 7).all()
+
+
 def test_full_chunk_1024_channels():
     """13 beams x 2^17 samples x 1024 channels (one streaming chunk of the
     survey backend)."""
