@@ -19,13 +19,13 @@
 // neighbouring series form one contiguous index range, found by a binary
 // search on t_end.  A table of series starts comes from one pass over the
 // list.  Components are built by lock-free union-find on a parent array: a
-// root is only ever hooked under a smaller root (one compare-and-swap), and
-// finds halve paths with plain word stores that only ever point a node at one
+// root is only ever hooked under a smaller node (an atomic minimum while all
+// are roots, one compare-and-swap later), and finds halve paths with plain word stores that only ever point a node at one
 // of its ancestors.  Every node's parent is therefore smaller than the node,
 // and each finished component's root is its lowest member whatever order the
 // threads ran in -- the result is deterministic.  Member counts, index and
 // time bounds and the representative (the largest (snr, -index) key) are
-// integer atomics into the root's slot; a scan over the roots numbers the
+// integer atomics into the root's slot; counts of the roots number the
 // clusters.  The work is a handful of dependent loads per event, so the
 // stage is bound by memory latency, not bandwidth.
 #include <algorithm>
@@ -102,6 +102,17 @@ __device__ void unite(int32_t* parent, int32_t a, int32_t b) {
     }
 }
 
+// Joins two nodes last seen as roots: the larger, if it still is one, goes
+// under the smaller whatever became of that (a root is the least node of its
+// tree, so a smaller node is not in it); one atomic and no load.
+__device__ void unite_seen(int32_t* parent, int32_t a, int32_t b) {
+    const int32_t lo = min(a, b), hi = max(a, b);
+    int32_t seen = hi;
+    if (!__hip_atomic_compare_exchange_strong(parent + hi, &seen, lo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                              __HIP_MEMORY_SCOPE_AGENT) && seen != lo)
+        unite(parent, seen, lo);
+}
+
 __device__ __forceinline__ bool event_ok(const dedisp_event& e, const ClusterParams& P) {
     return e.width_idx >= 0 && e.width_idx < P.nwidths && e.dm_idx >= 0 && e.dm_idx < P.ndm &&
            e.t_start >= 0 && e.t_end >= e.t_start && e.t_end < (int64_t(1) << 62) &&
@@ -164,74 +175,131 @@ __host__ __device__ inline int upper_series(int dm_radius, int width_radius) {
     return dm_radius + 1 + width_radius * (2 * dm_radius + 1);
 }
 
-__device__ void link_one(const ClusterParams& P, const int32_t* __restrict__ seg, int32_t* parent,
-                         int64_t i, int sidx);
-
-// Thread q handles event q / S and its neighbour series q % S (S =
-// upper_series): it unites the event with every friend of larger index in
-// that series.  One series per thread keeps each thread's chain of dependent
-// loads short.
-__global__ __launch_bounds__(kKThreads) void cluster_link_kernel(ClusterParams P,
-                                                                 const int32_t* __restrict__ seg,
-                                                                 int32_t* parent) {
-    const int S = upper_series(P.dm_radius, P.width_radius);
-    const int64_t nq = P.n * S;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * kKThreads;
-    for (int64_t q = static_cast<int64_t>(blockIdx.x) * kKThreads + threadIdx.x; q < nq; q += stride)
-        link_one(P, seg, parent, q / S, static_cast<int>(q % S));
-}
-
-__device__ void link_one(const ClusterParams& P, const int32_t* __restrict__ seg, int32_t* parent,
-                         int64_t i, int sidx) {
+// The friends of event i in neighbour series `sidx` of its upper (or lower:
+// the mirror image) half: the first one's index and the end of the series'
+// range, lo >= hi if the series is outside; `last` bounds the friends' t_start.
+template <bool UPPER>
+__device__ __forceinline__ void neighbours(const ClusterParams& P, const int32_t* __restrict__ seg,
+                                           int64_t i, int sidx, int64_t& lo, int64_t& end, int64_t& last) {
+    lo = end = last = 0;
     const dedisp_event e = P.ev[i];
     if (!event_ok(e, P)) return;
     int w = e.width_idx, d;
     if (sidx <= P.dm_radius) {
-        d = e.dm_idx + sidx;
+        d = UPPER ? e.dm_idx + sidx : e.dm_idx - sidx;
     } else {
         const int r = sidx - P.dm_radius - 1;
-        w += 1 + r / (2 * P.dm_radius + 1);
+        const int up = 1 + r / (2 * P.dm_radius + 1);
+        w += UPPER ? up : -up;
         d = e.dm_idx - P.dm_radius + r % (2 * P.dm_radius + 1);
     }
-    if (w >= P.nwidths || d < 0 || d >= P.ndm) return;
+    if (w < 0 || w >= P.nwidths || d < 0 || d >= P.ndm) return;
     const int64_t n = P.n;
     const int64_t k = static_cast<int64_t>(w) * P.ndm + d;
     int64_t a = min<int64_t>(max<int64_t>(seg[k], 0), n);
-    const int64_t b = min<int64_t>(max<int64_t>(seg[k + 1], a), n);
-    if (sidx == 0) a = max(a, i + 1);            // own series: later runs only
+    int64_t b = min<int64_t>(max<int64_t>(seg[k + 1], a), n);
+    if (sidx == 0) {                              // own series: later (earlier) runs only
+        if (UPPER) a = max(a, i + 1);
+        else b = min(b, i);
+    }
     const int64_t want_end = e.t_start - P.time_tol - P.widths[w] + 1;   // friend: t_end >= this
-    const int64_t last_start = e.t_end + P.widths[e.width_idx] - 1 + P.time_tol;
-    int64_t lo = a, hi = b;
+    last = e.t_end + P.widths[e.width_idx] - 1 + P.time_tol;
+    int64_t hi = b;
+    lo = a;
+    end = b;
     while (lo < hi) {
         const int64_t mid = (lo + hi) >> 1;
         if (P.ev[mid].t_end < want_end) lo = mid + 1;
         else hi = mid;
     }
-    for (int64_t j = lo; j < b && P.ev[j].t_start <= last_start; ++j) {
-        // most friends are already joined: a common ancestor seen through
-        // ordinary cached loads settles that without the coherent union
-        const int32_t ra = find_cached(parent, static_cast<int32_t>(i));
-        const int32_t rb = find_cached(parent, static_cast<int32_t>(j));
-        if (ra != rb) unite(parent, ra, rb);
+}
+
+// One thread per event and neighbour series, so that each thread's chain of
+// dependent loads is short: events along the grid's x (neighbouring lanes read
+// neighbouring events), the upper_series() series along y.
+//
+// First every event takes its friend of lowest index as its parent (one
+// atomic minimum per series, nothing to wait for; a parent is never above its
+// node whatever the input), and the trees are flattened.  Most pairs of
+// friends then share a root, which two cached loads show, and only what joins
+// two of these trees is left to the compare-and-swap of the union, whose chains
+// of coherent loads made the pass over the survey's 26669 events 70 us.  With
+// many events the unions hide one another's latency and the second walk over
+// the friends costs more than it saves: whole stage, us, without and with it,
+// 26669 events 119 and 99, 100000 157 and 133, 200000 168 and 177, 400000 273
+// and 290.
+constexpr int64_t kHookEvents = 131072;
+
+__global__ __launch_bounds__(kKThreads) void cluster_hook_kernel(ClusterParams P,
+                                                                 const int32_t* __restrict__ seg,
+                                                                 int32_t* __restrict__ parent) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * kKThreads + threadIdx.x;
+    if (i >= P.n) return;
+    const int S = upper_series(P.dm_radius, P.width_radius);
+    for (int q = blockIdx.y; q < S; q += gridDim.y) {
+        int64_t lo, end, last;
+        neighbours<false>(P, seg, i, q, lo, end, last);
+        if (lo < end && P.ev[lo].t_start <= last) atomicMin(parent + i, static_cast<int32_t>(lo));
     }
 }
 
-// Final roots, the accumulators of every root slot, and the root flags.
+// Every node halves its path while the others do: a chain of k nodes takes
+// about log2(k) rounds.
+__global__ __launch_bounds__(kKThreads) void cluster_flatten_kernel(int64_t n, int32_t* parent) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * kKThreads + threadIdx.x;
+    if (i >= n) return;
+    const int32_t r = find_root(parent, static_cast<int32_t>(i));
+    if (r != i) atomic_st(parent + i, r);
+}
+
+// Unites each event with every friend of larger index: thread g takes event
+// g / S and series g % S, so that a wave's unions are of few trees.  (Events
+// along x and series along y, as above, made the whole stage for the survey's
+// 26669 events 112 us in place of 98.)  Q is 32 bits where the grid's last step cannot pass 2^32.
+template <typename Q>
+__global__ __launch_bounds__(kKThreads) void cluster_link_kernel(ClusterParams P,
+                                                                 const int32_t* __restrict__ seg,
+                                                                 int32_t* parent) {
+    const Q S = upper_series(P.dm_radius, P.width_radius);
+    const Q nq = static_cast<Q>(P.n) * S;
+    for (Q g = static_cast<Q>(blockIdx.x) * kKThreads + threadIdx.x; g < nq;
+         g += static_cast<Q>(gridDim.x) * kKThreads) {
+        const int64_t i = g / S;
+        const int q = static_cast<int>(g % S);
+        int64_t lo, end, last;
+        neighbours<true>(P, seg, i, q, lo, end, last);
+        for (int64_t j = lo; j < end && P.ev[j].t_start <= last; ++j) {
+            // most friends are already joined: a common ancestor seen through
+            // ordinary cached loads settles that without the coherent union
+            const int32_t ra = find_cached(parent, static_cast<int32_t>(i));
+            const int32_t rb = find_cached(parent, static_cast<int32_t>(j));
+            if (ra != rb) unite_seen(parent, ra, rb);
+        }
+    }
+}
+
+// Final roots, the accumulators of every root slot, and the root flags (bit 0;
+// with `pack`, the first of a block also holds the block's number of roots
+// above it).
 __global__ __launch_bounds__(kKThreads) void cluster_finish_kernel(
-    int64_t n, int32_t* parent, uint32_t* __restrict__ flag, uint32_t* __restrict__ cnt,
+    int64_t n, bool pack, int32_t* parent, uint32_t* __restrict__ flag, uint32_t* __restrict__ cnt,
     int32_t* __restrict__ dmlo, int32_t* __restrict__ dmhi, int32_t* __restrict__ wlo,
     int32_t* __restrict__ whi, uint64_t* __restrict__ tlo, uint64_t* __restrict__ thi,
     uint64_t* __restrict__ key) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kKThreads + threadIdx.x;
-    if (i >= n) return;
-    int32_t r = static_cast<int32_t>(i);
-    int32_t p = atomic_ld(parent + r);
-    while (p != r) {
-        r = p;
-        p = atomic_ld(parent + r);
+    int32_t r = -1;
+    if (i < n) {
+        r = static_cast<int32_t>(i);
+        int32_t p = atomic_ld(parent + r);
+        while (p != r) {
+            r = p;
+            p = atomic_ld(parent + r);
+        }
+        atomic_st(parent + i, r);   // an ancestor of i, as every parent value is
     }
-    atomic_st(parent + i, r);   // an ancestor of i, as every parent value is
-    flag[i] = r == i;
+    const int roots = __syncthreads_count(r == i);
+    if (i >= n) return;
+    flag[i] = (r == i ? 1u : 0u) | (pack && threadIdx.x == 0 ? static_cast<uint32_t>(roots) << 1 : 0u);
     cnt[i] = 0;
     dmlo[i] = INT_MAX;
     dmhi[i] = INT_MIN;
@@ -240,6 +308,38 @@ __global__ __launch_bounds__(kKThreads) void cluster_finish_kernel(
     tlo[i] = ~0ull;
     thi[i] = 0;
     key[i] = 0;
+}
+
+// Numbers the roots in order: a block adds up the root counts of the blocks
+// before it by itself and scans its own flags.  Up to kNumberEvents events; the
+// counts are re-read by every block, so more take the scan over chunks.  26669
+// events: the whole stage 127 us with the three kernels of that scan, 112 so.
+constexpr int64_t kNumberEvents = int64_t(1) << 20;
+
+__global__ __launch_bounds__(kKThreads) void cluster_number_kernel(int64_t n, const uint32_t* __restrict__ flag,
+                                                                   int64_t* __restrict__ offs,
+                                                                   int64_t* __restrict__ total) {
+    __shared__ uint32_t before[kKThreads / 64], own[kKThreads / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * kKThreads + threadIdx.x;
+    uint32_t sum = 0;
+    for (unsigned b = threadIdx.x; b < blockIdx.x; b += kKThreads)
+        sum += flag[static_cast<int64_t>(b) * kKThreads] >> 1;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o, 64);
+    const uint64_t roots = __ballot(i < n && (flag[i] & 1u));
+    if (lane == 0) {
+        before[wave] = sum;
+        own[wave] = static_cast<uint32_t>(__popcll(roots));
+    }
+    __syncthreads();
+    uint32_t at = 0, all = 0;
+    for (int w = 0; w < kKThreads / 64; ++w) {
+        at += before[w] + (w < wave ? own[w] : 0u);
+        all += before[w] + own[w];
+    }
+    if (i < n) offs[i] = at + static_cast<uint32_t>(__popcll(roots & ((uint64_t(1) << lane) - 1)));
+    if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *total = all;
 }
 
 // Events per block of the accumulation and its LDS table (load <= 1/2).
@@ -317,7 +417,7 @@ __global__ __launch_bounds__(kKThreads) void cluster_write_kernel(
     const uint64_t* __restrict__ thi, const uint64_t* __restrict__ key,
     dedisp_cluster* __restrict__ out, int64_t capacity) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * kKThreads + threadIdx.x;
-    if (i >= P.n || !flag[i]) return;
+    if (i >= P.n || !(flag[i] & 1u)) return;
     const int64_t c = offs[i];
     if (c >= capacity) return;
     // key 0 only when no valid member reached the slot (rejected input): stay in bounds
@@ -424,14 +524,27 @@ hipError_t launch_cluster(const dedisp_event* ev, int64_t n, int32_t ndm, const 
     const dim3 g_n1(static_cast<unsigned>((n + 1 + kKThreads - 1) / kKThreads));
     hipLaunchKernelGGL(cluster_init_kernel, dim3(1), dim3(1), 0, s, err);
     hipLaunchKernelGGL(cluster_seg_kernel, g_n1, blk, 0, s, P, seg, parent, err);
-    const int64_t nq = n * upper_series(dm_radius, width_radius);
-    const int64_t link_blocks = std::min<int64_t>((nq + kKThreads - 1) / kKThreads, int64_t(1) << 20);
-    hipLaunchKernelGGL(cluster_link_kernel, dim3(static_cast<unsigned>(link_blocks)), blk, 0, s, P,
-                       seg, parent);
-    hipLaunchKernelGGL(cluster_finish_kernel, g_n, blk, 0, s, n, parent, flag, cnt, dmlo, dmhi,
-                       wlo, whi, tlo, thi, key);
-    hipError_t e = launch_scan_u32(flag, n, offs, chunk, total, s);
-    if (e != hipSuccess) return e;
+    const int S = upper_series(dm_radius, width_radius);
+    if (n <= kHookEvents) {
+        const dim3 g_pair(g_n.x, static_cast<unsigned>(std::min(S, 65535)));
+        hipLaunchKernelGGL(cluster_hook_kernel, g_pair, blk, 0, s, P, seg, parent);
+        hipLaunchKernelGGL(cluster_flatten_kernel, g_n, blk, 0, s, n, parent);
+    }
+    const int64_t nq = n * S;
+    const dim3 g_link(static_cast<unsigned>(std::min<int64_t>((nq + kKThreads - 1) / kKThreads, int64_t(1) << 20)));
+    if (nq < int64_t(1) << 31)
+        hipLaunchKernelGGL(cluster_link_kernel<uint32_t>, g_link, blk, 0, s, P, seg, parent);
+    else
+        hipLaunchKernelGGL(cluster_link_kernel<uint64_t>, g_link, blk, 0, s, P, seg, parent);
+    const bool number = n <= kNumberEvents;
+    hipLaunchKernelGGL(cluster_finish_kernel, g_n, blk, 0, s, n, number, parent, flag, cnt, dmlo,
+                       dmhi, wlo, whi, tlo, thi, key);
+    if (number) {
+        hipLaunchKernelGGL(cluster_number_kernel, g_n, blk, 0, s, n, flag, offs, total);
+    } else {
+        const hipError_t e = launch_scan_u32(flag, n, offs, chunk, total, s);
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(cluster_accumulate_kernel,
                        dim3(static_cast<unsigned>((n + kAccEvents - 1) / kAccEvents)), blk, 0, s,
                        P, parent, offs, cnt, dmlo, dmhi,

@@ -55,6 +55,25 @@ def test_matches_oracle_synthetic(seed, ndm, nwidths, nout, nclumps, nnoise, par
     _same(gl, got, ref_l, [dict(r) for r in ref])
 
 
+@pytest.mark.parametrize("m", [1, 127, 128, 129, 65536, 65537, (1 << 19) + 3])
+def test_numbering_over_blocks(m):
+    """m events in each of trials 0, 1 and 5, at the same m times: a pair of
+    trials joins into one cluster, trial 5 stays alone.  384 to 1.5 million
+    events: around the blocks of 256 that number the roots, the limits of the
+    passes that many events leave out, and the scan over chunks."""
+    ev = np.zeros(3 * m, dtype=synth.make_event_list(1, 8, 1, 1000, nclumps=1, nnoise=1).dtype)
+    t = np.tile(np.arange(m, dtype=np.int64) * 10, 3)
+    ev["t_start"], ev["t_end"], ev["t_peak"] = t, t + 3, t + 1
+    ev["dm_idx"] = np.repeat([0, 1, 5], m)
+    ev["snr"] = np.repeat([7.0, 9.0, 8.0], m)
+    nc, lab, got = _run(ev, 8, [1], 2, 1, 0)
+    own = np.arange(m)
+    assert nc == 2 * m and (lab == np.concatenate([own, own, m + own])).all()
+    assert (got["first"] == np.concatenate([own, 2 * m + own])).all()
+    assert (got["rep"] == np.concatenate([m + own, 2 * m + own])).all()
+    assert (got["n_members"] == np.repeat([2, 1], m)).all()
+
+
 def test_small_config_pipeline_events():
     """Cluster the events the GPU search finds in the small beam."""
     from paper_1112_0065_amd import _lib as L
