@@ -105,6 +105,17 @@ hipError_t launch_repack(const uint8_t* in, int64_t nsamps, int nchans, uint2* w
 dedisp_status launch_dedisperse(const dedisp_plan_s* p, const uint2* words,
                                 int64_t nwords, int64_t nout, void* out, int out_u16,
                                 const TileConfig& cfg, hipStream_t s);
+// Up to kMaxMany inputs of plans of one channel count at one tile shape, uint16
+// output, in one launch.
+constexpr int kMaxMany = 32;   // descriptors that fit a kernel's arguments (4 KB)
+struct ManyItem {
+    const dedisp_plan_s* plan;
+    const uint2* words;
+    int64_t nwords;
+    int64_t nout;
+    void* out;
+};
+dedisp_status launch_dedisperse_many(const ManyItem* items, int n, const TileConfig& cfg, hipStream_t s);
 TileConfig default_tile_config(const dedisp_plan_s* p);
 void apply_env_cache(dedisp_plan_s* p);
 BeamArgs beam_args(const dedisp_plan_s* p, const uint2* words, int64_t nwords, int64_t nout,

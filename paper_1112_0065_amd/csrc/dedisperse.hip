@@ -564,6 +564,38 @@ void dedisperse_kernel(dd::BeamArgs a, int stage_chans,
                                                reinterpret_cast<char*>(lds), lane, wave);
 }
 
+// The same over the items of several inputs (the subbands of a two-stage plan),
+// whose launches one by one each start and drain the chip.  The whole two-stage
+// call, us, with a launch per subband and with one: survey beam 16 x 8 2446 and
+// 2340, 1024 channels x 2^16, 13 coarse trials, 16
+// subbands 271 and 160 (32 items each), 256 x 2^15, 25 x 8 84 and 49.
+struct ManyArgs {
+    dd::BeamArgs b[dd::kMaxMany];
+};
+static_assert(sizeof(ManyArgs) <= 4000, "kernel arguments");
+
+template <int NL, int NDW, int G, bool OUT16>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(min_waves<NL, NDW, G>())))
+void dedisperse_many_kernel(ManyArgs m, int n, int stage_chans, int n_items) {
+    extern __shared__ uint4 lds[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int per_xcd = gridDim.x / 8;
+    const int item = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (item >= n_items) return;
+    int b = 0;
+    while (b + 1 < n && item >= m.b[b + 1].item_begin) ++b;
+    const dd::BeamArgs a = m.b[b];
+    int tile, dblk;
+    item_coords(a, item - a.item_begin, &tile, &dblk);
+    if (stage_chans == 8 && (a.nchans & 7) == 0)
+        process_item<NL, NDW, G, OUT16, true>(a, tile, dblk, 8, reinterpret_cast<char*>(lds), lane,
+                                              wave);
+    else
+        process_item<NL, NDW, G, OUT16, false>(a, tile, dblk, stage_chans,
+                                               reinterpret_cast<char*>(lds), lane, wave);
+}
+
 // Form for grids with too few items to fill the chip: an item's kFewTrials
 // trials go to kFewTrials / NWV blocks of NWV waves, one trial per wave, on
 // the ordinary kernel's tile and tables, with nsub stages per buffer (see
@@ -647,6 +679,21 @@ hipError_t launch_cfg(const dd::BeamArgs& a, int stage_chans, size_t lds, hipStr
     const int64_t nblocks = 8 * ((a.n_items + 7) / 8);
     hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(nblocks)), dim3(kThreads), lds, s, a,
                        stage_chans, static_cast<int>(a.n_items));
+    return hipGetLastError();
+}
+
+template <int NL, int NDW, int G>
+hipError_t launch_many_cfg(const ManyArgs& m, int n, int64_t total, int stage_chans, size_t lds, hipStream_t s) {
+    auto kern = dedisperse_many_kernel<NL, NDW, G, true>;
+    if (lds > 64 * 1024) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           static_cast<int>(lds));
+        if (e != hipSuccess) return e;
+    }
+    const int64_t nblocks = 8 * ((total + 7) / 8);
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(nblocks)), dim3(kThreads), lds, s, m, n, stage_chans,
+                       static_cast<int>(total));
     return hipGetLastError();
 }
 
@@ -809,6 +856,48 @@ dedisp_status launch_dedisperse(const dedisp_plan_s* p, const uint2* words, int6
     if (nl == NL_ && cfg.dms_per_block == NDW_ * kWaves && cfg.groups == G_)          \
         e = out_u16 ? launch_cfg<NL_, NDW_, G_, true>(a, cfg.stage_chans, lds, s)     \
                     : launch_cfg<NL_, NDW_, G_, false>(a, cfg.stage_chans, lds, s);
+    DD_SHAPES(DD_DISPATCH)
+#undef DD_DISPATCH
+    if (e != hipSuccess)
+        return fail(e == hipErrorInvalidValue ? DEDISP_ERR_UNSUPPORTED : DEDISP_ERR_HIP,
+                    "dedispersion launch failed: %s", hipGetErrorString(e));
+    return DEDISP_OK;
+}
+
+dedisp_status launch_dedisperse_many(const ManyItem* items, int n, const TileConfig& cfg, hipStream_t s) {
+    const int k = dm_block_index(cfg.dms_per_block);
+    ManyArgs m{};
+    int64_t total = 0;
+    size_t lds = 0;
+    bool one_by_one = n == 1 || n > kMaxMany || k < 0 || cfg.stage_chans < 4 || cfg.stage_chans % 4 ||
+                      cfg.groups < 1 || cfg.groups > 2;
+    for (int i = 0; i < n && !one_by_one; ++i) {
+        const ManyItem& it = items[i];
+        dedisp_status st = DEDISP_OK;
+        if (tile_lds_bytes(it.plan, cfg) > 160 * 1024) {
+            one_by_one = true;
+            break;
+        }
+        if (!offset_table(it.plan, cfg, true, &st)) return st;
+        m.b[i] = beam_args(it.plan, it.words, it.nwords, it.nout, it.out, cfg);
+        m.b[i].item_begin = total;
+        total += m.b[i].n_items;
+        lds = std::max(lds, tile_lds_bytes(it.plan, cfg));
+    }
+    // One launch each reports what cannot be launched.
+    if (one_by_one || total > (int64_t(1) << 30)) {
+        for (int i = 0; i < n; ++i) {
+            const ManyItem& it = items[i];
+            const dedisp_status st = launch_dedisperse(it.plan, it.words, it.nwords, it.nout, it.out, 1, cfg, s);
+            if (st != DEDISP_OK) return st;
+        }
+        return DEDISP_OK;
+    }
+    const int nl = levels_for(items[0].plan->nchans);
+    hipError_t e = hipErrorInvalidValue;
+#define DD_DISPATCH(NL_, NDW_, G_)                                                    \
+    if (nl == NL_ && cfg.dms_per_block == NDW_ * kWaves && cfg.groups == G_)          \
+        e = launch_many_cfg<NL_, NDW_, G_>(m, n, total, cfg.stage_chans, lds, s);
     DD_SHAPES(DD_DISPATCH)
 #undef DD_DISPATCH
     if (e != hipSuccess)

@@ -379,13 +379,23 @@ extern "C" dedisp_status dedisp_subband_execute(dedisp_subband b, const uint8_t*
     uint2* words = static_cast<uint2*>(workspace);
     uint16_t* series = reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + words_bytes(b, nsamps));
     DD_HIP(dd::launch_repack(in, nsamps, p->nchans, words, nwords, stream));
+    // Runs of subbands with the same tile shape (the tuner gives all the same;
+    // a tune cache may not) go in one launch.
+    dd::ManyItem items[dd::kMaxMany];
+    int n_items = 0;
     for (int s = 0; s < b->nsub; ++s) {
-        const dedisp_plan_s* sp = b->sub[s];
-        uint16_t* dst = series + static_cast<int64_t>(b->ncoarse) * (s * nsamps - b->cum[s]);
-        const dedisp_status st = dd::launch_dedisperse(sp, words + static_cast<int64_t>(s) * b->S * nwords,
-                                                       nwords, nsamps - b->maxd[s], dst, 1,
-                                                       dd::default_tile_config(sp), stream);
+        const dd::TileConfig c = dd::default_tile_config(b->sub[s]);
+        items[n_items++] = {b->sub[s], words + static_cast<int64_t>(s) * b->S * nwords, nwords,
+                            nsamps - b->maxd[s],
+                            series + static_cast<int64_t>(b->ncoarse) * (s * nsamps - b->cum[s])};
+        if (s + 1 < b->nsub && n_items < dd::kMaxMany) {
+            const dd::TileConfig d = dd::default_tile_config(b->sub[s + 1]);
+            if (c.dms_per_block == d.dms_per_block && c.groups == d.groups && c.stage_chans == d.stage_chans)
+                continue;
+        }
+        const dedisp_status st = dd::launch_dedisperse_many(items, n_items, c, stream);
         if (st != DEDISP_OK) return st;
+        n_items = 0;
     }
     const int64_t nout = nsamps - b->loss;
     const int row_len = kS2Tile + b->span;
