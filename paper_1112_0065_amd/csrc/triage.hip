@@ -172,17 +172,23 @@ __device__ __forceinline__ uint32_t neighbour(uint32_t x) {
     return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(x), 0xB1, 0xF, 0xF, false));
 }
 
-// 2x2 max-pool of four values rounded to bfloat16, ReLU included.  A value's
-// key is its bits above 3 - k, so the signed maximum is the largest value, of
-// equal ones the first in raster order; negative values lose to 0, whose
-// winner nobody asks for (a pooled 0 passes no gradient).  Returns the pooled
-// value in bits 16-31 and 3 - winner in bits 0-1.
+// 2x2 max-pool of four values rounded to bfloat16, ReLU included: max(x, 0) of
+// a NaN of either sign is 0, as fmaxf gives it.  A value's key is its bits, 0x7F
+// above them modulo 2^16, over 3 - k: the signed maximum is then the largest
+// value, of equal ones the first in raster order.  0 has 0x7F and infinity
+// 0x7FFF; negative values and NaNs with a clear sign are negative, NaNs with a
+// set sign below 0x7F, so all of these lose to 0, whose winner nobody asks for
+// (a pooled 0 passes no gradient).  Returns the pooled value in bits 16-31 and
+// 3 - winner in bits 0-1.
 __device__ __forceinline__ uint32_t pool_key(uint32_t v01, uint32_t v23) {
-    const int k0 = static_cast<int>((v01 << 16) | 3u);
-    const int k1 = static_cast<int>((v01 & 0xFFFF0000u) | 2u);
-    const int k2 = static_cast<int>((v23 << 16) | 1u);
-    const int k3 = static_cast<int>(v23 & 0xFFFF0000u);
-    return static_cast<uint32_t>(max(max(max(k0, k1), max(k2, k3)), 0));
+    const u16x2 above = {0x7F, 0x7F};
+    const uint32_t a = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, v01) + above);
+    const uint32_t b = __builtin_bit_cast(uint32_t, __builtin_bit_cast(u16x2, v23) + above);
+    const int k0 = static_cast<int>((a << 16) | 3u);
+    const int k1 = static_cast<int>((a & 0xFFFF0000u) | 2u);
+    const int k2 = static_cast<int>((b << 16) | 1u);
+    const int k3 = static_cast<int>(b & 0xFFFF0000u);
+    return static_cast<uint32_t>(max(max(max(k0, k1), max(k2, k3)), 0x7F0000)) - 0x7F0000u;
 }
 
 // ---------------------------------------------------------------------------

@@ -300,3 +300,52 @@ def test_gradient_of_a_large_batch_is_the_mean_of_its_halves():
         err = np.linalg.norm(grads[0][k] - half) / np.linalg.norm(half)
         log("grad", k, "rel L2", err)
         assert err <= 2e-4, k
+
+
+def _forward_fmax(p, vals):
+    """The oracle's forward pass with the ReLU as fmax: 0 where its input is NaN."""
+    x, cache = np.asarray(vals, np.float64)[:, None], []
+    with np.errstate(invalid="ignore"):
+        for l in range(1, cnn.NLAYERS + 1):
+            w = cnn.round_bf16(p[f"w{l}"])
+            z = cnn.conv3x3(x, w) + np.asarray(p[f"b{l}"], np.float64)[None, :, None, None]
+            a = cnn.round_bf16(np.fmax(z, 0.0))
+            q, idx = cnn.maxpool2(a)
+            cache.append((x, w, a, idx))
+            x = q
+    g = x.mean(axis=(2, 3))
+    return g @ np.asarray(p["wf"], np.float64) + float(p["bf"][0]), (cache, g)
+
+
+@pytest.mark.parametrize("bad", [0x7FC0, 0xFFC0, 0x7F81, 0xFFFF, 0x7F80, 0xFF80])
+def test_relu_of_nan_is_zero(bad):
+    """NaNs of either sign and infinities in the tiles (infinities of both signs
+    meet in the second layer and give NaNs there): a NaN's ReLU is 0, so logits,
+    and the gradients behind the first layer, are the oracle's with that rule.
+    Bounds as for finite tiles."""
+    from paper_1112_0065_amd import _lib as L
+    torch = torch_dev()
+    n = 4
+    p = _params(7)
+    bits, _ = _tiles(8, n)
+    for k, (y, x) in enumerate([(0, 0), (31, 127), (63, 255), (20, 64)]):
+        bits[k, y, x] = bad
+    vals = cnn.bf16_value(bits)
+    labels = np.arange(n) % 2 * 1.0
+    m = L.triage_create(None, 0)
+    L.triage_set_params(m, flat(p))
+    t = _dev_tiles(bits)
+    logits = torch.empty(n, dtype=torch.float32, device="cuda")
+    L.triage_forward(m, t, n, logits=logits)
+    got = logits.cpu().numpy()
+    ref_logits, cache = _forward_fmax(p, vals)
+    log("bad", hex(bad), "logits", got, "ref", ref_logits)
+    assert np.isfinite(ref_logits).all()
+    assert np.all(np.abs(got - ref_logits) <= 1e-2 * (1 + np.abs(ref_logits)))
+    L.triage_forward_backward(m, t, torch.tensor(labels, dtype=torch.float32, device="cuda"), n)
+    gg = unflat(L.triage_get_params(m)[1])
+    with np.errstate(invalid="ignore"):
+        ref = cnn.backward(p, cache, ref_logits, labels, bf16=True)
+    for k in ORDER:
+        if np.isfinite(ref[k]).all():
+            assert np.linalg.norm(gg[k] - ref[k]) <= 2e-2 * (np.linalg.norm(ref[k]) + 1e-12), k
