@@ -485,18 +485,8 @@ __global__ __launch_bounds__(kThreads) void baseline_kernel(const T* __restrict_
 // times w_max says so) a 64-bit square sum cannot overflow even after the
 // 64-lane reduction; otherwise the sums are carried as 128-bit values.
 template <bool SMALL>
-__device__ __forceinline__ void width_sums(const uint32_t* pl, int npos, int w, uint64_t* s1_out,
-                                           u128* s2_out, uint32_t* mx_out) {
-    uint64_t s1 = 0, lo = 0, hi = 0;
-    uint32_t mx = 0;
-    for (int i = threadIdx.x; i < npos; i += kThreads) {
-        const uint32_t b = pl[i + 1 + w] - pl[i + 1];
-        s1 += b;
-        const uint64_t sq = static_cast<uint64_t>(b) * b;   // one v_mad_u64_u32 when SMALL
-        lo += sq;
-        if (!SMALL) hi += lo < sq ? 1u : 0u;
-        mx = max(mx, b);
-    }
+__device__ __forceinline__ void wave_totals(uint64_t s1, uint64_t lo, uint64_t hi, uint32_t mx, uint64_t* s1_out,
+                                            u128* s2_out, uint32_t* mx_out) {
     s1 = wave_sum_u64(s1);
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) mx = max(mx, static_cast<uint32_t>(__shfl_xor(mx, o, 64)));
@@ -510,6 +500,22 @@ __device__ __forceinline__ void width_sums(const uint32_t* pl, int npos, int w, 
     }
     *s1_out = s1;
     *mx_out = mx;
+}
+
+template <bool SMALL>
+__device__ __forceinline__ void width_sums(const uint32_t* pl, int npos, int w, uint64_t* s1_out,
+                                           u128* s2_out, uint32_t* mx_out) {
+    uint64_t s1 = 0, lo = 0, hi = 0;
+    uint32_t mx = 0;
+    for (int i = threadIdx.x; i < npos; i += kThreads) {
+        const uint32_t b = pl[i + 1 + w] - pl[i + 1];
+        s1 += b;
+        const uint64_t sq = static_cast<uint64_t>(b) * b;   // one v_mad_u64_u32 when SMALL
+        lo += sq;
+        if (!SMALL) hi += lo < sq ? 1u : 0u;
+        mx = max(mx, b);
+    }
+    wave_totals<SMALL>(s1, lo, hi, mx, s1_out, s2_out, mx_out);
 }
 
 // Positions per thread in the fast path of a full segment.
@@ -747,10 +753,17 @@ __global__ __launch_bounds__(kThreads) void boxcar_stats_kernel(const T* __restr
 // on the survey series 1029 -> 851 us (10 widths), on 301 int32 rows of odd
 // length 164 -> 133.  Eight steps unrolled (four: 952 us).  Five waves per SIMD
 // for uint16, four for int32 (whose quads take twice the registers): one more
-// spills the 32-bit form's sums (the drifting series 1330 us) and gains nothing.
+// spills the sums of the wide form and gains nothing.
+//
 // Windows that span more (bright pulses, a drifting baseline) put the same sums
-// into LDS with 32 bits, half the segment at a time (a survey series that all
-// drifts: 963 us, 920 before); large values and ragged ones take the general code.
+// into LDS with 32 bits, half the segment at a time, from the samples that the
+// block still holds: as many instructions as the running sums of the general
+// kernel, but no second load.  A drift shows in the values between the waves'
+// runs, before anything is spent on 16 bits.  find_peaks on a survey series that
+// all drifts 814 us (877 in the general kernel; 927 when every window was tried on
+// 16 bits first), 11 widths to 1000 892 (949), 1200 rows of 5000 samples with pulses
+// 60 (98), int32 samples of 2^17 to 2^18 79 (125).  Samples from 2^19 on, or with a
+// widest boxcar from 2^25 on, take P itself, width by width: 160 (174) and 257 (270).
 // ----------------------------------------------------------------------------
 constexpr int kSegLen = 8192;                       // positions per segment
 constexpr int kHalfLen = kSegLen / 2;
@@ -844,23 +857,32 @@ __device__ __forceinline__ bool stats_reduce(const uint64_t (&s2)[NW], const int
 
 // This lane's width (lane wi < NW) and the wave's share of its sum of boxcars
 // over n positions, by telescoping: sum_p (P(p + w) - P(p)) = sum_{i < w}
-// (P(n + i) - P(i)).  diff(i) gives the i-th term; lane l takes i = i0 + l, a DPP
-// scan gives the prefix, lane wi fetches the one at w - 1.  |term| < 2^25.
-template <int NW, typename F>
+// (P(n + i) - P(i)).  diff(i, k) gives the i-th term, the thread's k-th; a DPP
+// scan gives the prefix, lane wi fetches the one at w - 1.  Terms up to kMaxSpan16
+// are scanned as they are; WIDE ones, any int, by 16-bit halves.
+constexpr int kTerms = (kMaxWidth16 + kThreads - 1) / kThreads;   // of a thread
+template <int NW, bool WIDE, typename F>
 __device__ __forceinline__ int64_t telescoped(const int (&w)[NW], F diff) {
+    static_assert(64 * static_cast<int64_t>(kMaxSpan16) < (int64_t(1) << 31), "the sum of a wave's terms is an int");
     const int lane = threadIdx.x & 63;
     int myw = 0;
 #pragma unroll
     for (int wi = 0; wi < NW; ++wi)
         if (lane == wi) myw = w[wi];
+    const int wave0 = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) & ~63);
     int64_t s1 = 0;
-    for (int i0 = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) & ~63); i0 < w[NW - 1];
-         i0 += kThreads) {
+#pragma unroll
+    for (int k = 0; k < kTerms; ++k) {
+        const int i0 = wave0 + k * kThreads;
+        if (i0 >= w[NW - 1]) break;
         const int i = i0 + lane;
-        const int d = i < w[NW - 1] ? diff(i) : 0;
+        const int d = i < w[NW - 1] ? diff(i, k) : 0;
         const int l = myw - 1 - i0;
         const int src = min(max(l, 0), 63);
-        const int got = __shfl(static_cast<int>(wave_incl_scan(static_cast<uint32_t>(d))), src, 64);
+        int64_t got = __shfl(static_cast<int>(wave_incl_scan(static_cast<uint32_t>(WIDE ? d & 0xFFFF : d))), src, 64);
+        if (WIDE)
+            got += int64_t(65536) *
+                   __shfl(static_cast<int>(wave_incl_scan(static_cast<uint32_t>(d >> 16))), src, 64);
         if (l >= 0) s1 += got;
     }
     return s1;
@@ -886,7 +908,12 @@ struct Quad<uint16_t> {
     __device__ __forceinline__ uint32_t s1(uint32_t base) const { return base + (v[0] & 0xFFFFu); }
     __device__ __forceinline__ uint32_t s2(uint32_t base) const { return add_halves(v[0], base); }
     __device__ __forceinline__ uint32_t s3(uint32_t base) const { return s2(base) + (v[1] & 0xFFFFu); }
-    __device__ __forceinline__ uint32_t vmax(uint32_t) const { return 0u; }   // below 2^16 anyway
+    // m, vmax: two maxima in one word
+    __device__ __forceinline__ uint32_t vmax(uint32_t m) const {
+        const u16x2 a = __builtin_bit_cast(u16x2, v[0]), b = __builtin_bit_cast(u16x2, v[1]);
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, m),
+                                                                      __builtin_elementwise_max(a, b)));
+    }
 };
 template <>
 struct Quad<int32_t> {
@@ -908,13 +935,14 @@ struct Quad<int32_t> {
 // One (DM, segment) per block.  `in` is aligned to four samples; w_max <=
 // kMaxWidth16; every width even, but for the first one when ODD1.
 template <typename T, int NW, bool ODD1>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 5 : 4))) void boxcar_stats16_kernel(const T* __restrict__ in, int64_t nout,
-                                                                  int64_t nbx, dd::Widths W, int nseg,
-                                                                  dd::PeaksWs ws) {
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 5 : 4)))
+void boxcar_stats16_kernel(const T* __restrict__ in, int64_t nout, int64_t nbx, dd::Widths W, int nseg,
+                           dd::PeaksWs ws) {
     __shared__ uint4 lds16[(kLds16Words + 3) / 4];
     __shared__ uint32_t round_tot[kRounds * (kThreads / 64)];
     __shared__ int span[2][kThreads / 64];      // per wave: largest P' and largest -P'
     __shared__ uint32_t vmax_w[kThreads / 64];
+    constexpr bool kU16 = std::is_same<T, uint16_t>::value;
     uint32_t* lds = reinterpret_cast<uint32_t*>(lds16);
     const int d = blockIdx.y, seg = blockIdx.x;
     const int t = threadIdx.x, lane = t & 63;
@@ -956,9 +984,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof
         const uint32_t incl = wave_incl_scan(c);
         excl[i] = incl - c;
         if (lane == 63) round_tot[i * (kThreads / 64) + wave] = incl;
-        vm = v[i].vmax(vm);
+        if (!kU16) vm = v[i].vmax(vm);   // below 2^16 anyway
     }
-    if (!std::is_same<T, uint16_t>::value) {
+    if (!kU16) {
         vm = static_cast<uint32_t>(wave_max_i32(static_cast<int>(min(vm, 0x7FFFFFFFu))));
         if (lane == 63) vmax_w[wave] = vm;
     }
@@ -966,68 +994,31 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof
     const uint32_t tv = lane < kRounds * (kThreads / 64) ? round_tot[lane] : 0u;
     const uint32_t tin = wave_incl_scan(tv);
     const uint32_t tex = tin - tv;
-    // a sample near the mean, the same in every lane (any value gives exact
-    // sums: a poor one only widens the span)
-    const uint32_t total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(tin), 63));
-    const int c = __builtin_amdgcn_readfirstlane(
-        static_cast<int>(fminf(static_cast<float>(total) * __builtin_amdgcn_rcpf(static_cast<float>(num)), 1e9f) + 0.5f));
-    // P' of the thread's quads, P'(4 g .. 4 g + 3); the places used are k0 ..
-    // kneed
+    // a sample near the mean, the same in every lane (int32 samples up to 2^19 sum
+    // beyond 2^32: their half sums)
+    const uint32_t sum = static_cast<uint32_t>(
+        __builtin_amdgcn_readlane(static_cast<int>(kU16 ? tin : wave_incl_scan(tv >> 1)), 63));
+    const float mean = static_cast<float>(sum) * (kU16 ? 1.0f : 2.0f) * __builtin_amdgcn_rcpf(static_cast<float>(num));
+    const int c = __builtin_amdgcn_readfirstlane(static_cast<int>(fminf(mean, 1e9f) + 0.5f));
+    // The places of P' that are used are k0 .. kneed.  Where it spans too much, mostly
+    // its values between the waves' runs of 256 samples, which every wave has, show it.
     const int kneed = k0 + npos - 1 + w_max;
-    const int off = k0 & 1 ? 4 - k0 : 0;   // k0 + off is even: pairs of positions are words
-    int hi = 0, lo = 0;
-    uint32_t word[kRounds][2];
+    const int at256 = static_cast<int>(tex - static_cast<uint32_t>(c) * 256u * static_cast<uint32_t>(lane));
+    const bool far = lane < kRounds * (kThreads / 64) && 256 * lane <= kneed &&
+                     (at256 > kMaxSpan16 || at256 < -kMaxSpan16);
+    // excl[i] = P'(4 g), g the thread's quad of round i, from here on
 #pragma unroll
     for (int i = 0; i < kRounds; ++i) {
         const uint32_t pre = static_cast<uint32_t>(
             __builtin_amdgcn_readlane(static_cast<int>(tex), i * (kThreads / 64) + wave));
-        const uint32_t base = pre + excl[i] - static_cast<uint32_t>(c) * 4u * static_cast<uint32_t>(i * kThreads + t);
-        excl[i] = base;   // P'(4 g) from here on
-        const int p0 = static_cast<int>(base);
-        const int p1 = static_cast<int>(v[i].s1(base) - c);
-        const int p2 = static_cast<int>(v[i].s2(base) - 2 * c);
-        const int p3 = static_cast<int>(v[i].s3(base) - 3 * c);
-        const bool need = 4 * (i * kThreads + t) <= kneed;
-        const int h4 = max(max(max(hi, p0), max(p1, p2)), p3), l4 = min(min(min(lo, p0), min(p1, p2)), p3);
-        hi = need ? h4 : hi;
-        lo = need ? l4 : lo;
-        word[i][0] = __builtin_amdgcn_perm(static_cast<uint32_t>(p1), static_cast<uint32_t>(p0), 0x05040100u);
-        word[i][1] = __builtin_amdgcn_perm(static_cast<uint32_t>(p3), static_cast<uint32_t>(p2), 0x05040100u);
+        excl[i] += pre - static_cast<uint32_t>(c) * 4u * static_cast<uint32_t>(i * kThreads + t);
     }
-    hi = wave_max_i32(hi);
-    lo = wave_max_i32(-lo);
-    if (lane == 63) {
-        span[0][wave] = hi;
-        span[1][wave] = lo;
-    }
-    // half-word h = k + off holds P'(k)
-    uint16_t* half = reinterpret_cast<uint16_t*>(lds);
-    if (off == 0) {
-#pragma unroll
-        for (int i = 0; i < kRounds; ++i)
-            *reinterpret_cast<uint2*>(lds + 2 * (i * kThreads + t)) = make_uint2(word[i][0], word[i][1]);
-    } else {
-#pragma unroll
-        for (int i = 0; i < kRounds; ++i) {   // odd off: a half, a word, a half
-            const int h = 4 * (i * kThreads + t) + off;
-            half[h] = static_cast<uint16_t>(word[i][0]);
-            *reinterpret_cast<uint32_t*>(half + h + 1) = __builtin_amdgcn_alignbit(word[i][1], word[i][0], 16);
-            half[h + 3] = static_cast<uint16_t>(word[i][1] >> 16);
-        }
-    }
-    __syncthreads();
-    int smax = 0, smin = 0;
     uint32_t vmax = 0xFFFFu;
+    if (!kU16) {
+        vmax = vmax_w[0];
 #pragma unroll
-    for (int k = 0; k < kThreads / 64; ++k) {
-        smax = max(smax, span[0][k]);
-        smin = max(smin, span[1][k]);
-        if (!std::is_same<T, uint16_t>::value) vmax = k == 0 ? vmax_w[0] : max(vmax, vmax_w[k]);
+        for (int k = 1; k < kThreads / 64; ++k) vmax = max(vmax, vmax_w[k]);
     }
-    // P and c k below 2^31 apart (so P' did not wrap), the span, and every
-    // square sum below 2^13 x 2^50
-    const bool narrow = vmax < (1u << 17) && smax <= kMaxSpan16 - smin && smin <= kMaxSpan16 &&
-                        static_cast<int64_t>(c) * w_max + (1 << 14) < (1 << 25);
     const int64_t idx0 = static_cast<int64_t>(d) * nseg + seg;
     const int64_t stride = static_cast<int64_t>(gridDim.y) * nseg;
     // width t / 16's totals of B from those of B' = B - c w (lane 16 wi)
@@ -1035,107 +1026,198 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof
         const int64_t cw = static_cast<int64_t>(c) * W.w[t >> 4];
         const int64_t i = idx0 + (t >> 4) * stride;
         ws.part_s1[i] = static_cast<uint64_t>(a1 + npos * cw);
-        ws.part_s2lo[i] = a2 + static_cast<uint64_t>(2 * cw * a1 + npos * cw * cw);
+        ws.part_s2lo[i] = a2 + static_cast<uint64_t>(2 * cw) * static_cast<uint64_t>(a1) +
+                          static_cast<uint64_t>(npos * cw * cw);   // below 2^64, modulo which it is formed
         ws.part_s2hi[i] = 0u;
         ws.part_max[i] = static_cast<uint32_t>(am + static_cast<int>(cw));
     };
-    if (narrow) {
-        uint32_t sq[2][NW];   // at most 16 squares below 2^28 each
-        i16x2 mx[NW];
+    int smax = INT32_MAX, smin = INT32_MAX;   // largest P' and -P'
+    if (!__ballot(far)) {
+        const int off = k0 & 1 ? 4 - k0 : 0;   // k0 + off is even: pairs of positions are words
+        int hi = 0, lo = 0;
+        uint32_t word[kRounds][2];
 #pragma unroll
-        for (int wi = 0; wi < NW; ++wi) {
-            sq[0][wi] = sq[1][wi] = 0u;
-            mx[wi] = i16x2{INT16_MIN, INT16_MIN};
+        for (int i = 0; i < kRounds; ++i) {
+            const uint32_t base = excl[i];
+            const int p0 = static_cast<int>(base);
+            const int p1 = static_cast<int>(v[i].s1(base) - c);
+            const int p2 = static_cast<int>(v[i].s2(base) - 2 * c);
+            const int p3 = static_cast<int>(v[i].s3(base) - 3 * c);
+            const bool need = 4 * (i * kThreads + t) <= kneed;
+            const int h4 = max(max(max(hi, p0), max(p1, p2)), p3), l4 = min(min(min(lo, p0), min(p1, p2)), p3);
+            hi = need ? h4 : hi;
+            lo = need ? l4 : lo;
+            word[i][0] = __builtin_amdgcn_perm(static_cast<uint32_t>(p1), static_cast<uint32_t>(p0), 0x05040100u);
+            word[i][1] = __builtin_amdgcn_perm(static_cast<uint32_t>(p3), static_cast<uint32_t>(p2), 0x05040100u);
         }
-        const uint32_t* base = lds + (k0 + off) / 2 + t;
-        auto pair = [&](const uint32_t* q, int wi) -> uint32_t {
-            return ODD1 && wi == 0 ? __builtin_amdgcn_alignbit(q[(w[0] + 1) / 2], q[(w[0] - 1) / 2], 16)
-                                   : q[w[wi] / 2];
-        };
-        if (npos == kSegLen) {
+        hi = wave_max_i32(hi);
+        lo = wave_max_i32(-lo);
+        if (lane == 63) {
+            span[0][wave] = hi;
+            span[1][wave] = lo;
+        }
+        // half-word h = k + off holds P'(k)
+        uint16_t* half = reinterpret_cast<uint16_t*>(lds);
+        if (off == 0) {
 #pragma unroll
-            for (int hf = 0; hf < 2; ++hf)
+            for (int i = 0; i < kRounds; ++i)
+                *reinterpret_cast<uint2*>(lds + 2 * (i * kThreads + t)) = make_uint2(word[i][0], word[i][1]);
+        } else {
+#pragma unroll
+            for (int i = 0; i < kRounds; ++i) {   // odd off: a half, a word, a half
+                const int h = 4 * (i * kThreads + t) + off;
+                half[h] = static_cast<uint16_t>(word[i][0]);
+                *reinterpret_cast<uint32_t*>(half + h + 1) = __builtin_amdgcn_alignbit(word[i][1], word[i][0], 16);
+                half[h + 3] = static_cast<uint16_t>(word[i][1] >> 16);
+            }
+        }
+        __syncthreads();
+        smax = smin = 0;
+#pragma unroll
+        for (int k = 0; k < kThreads / 64; ++k) {
+            smax = max(smax, span[0][k]);
+            smin = max(smin, span[1][k]);
+        }
+        // P' did not wrap (see below), the span, and every square sum below 2^13 x 2^50
+        const bool narrow = vmax < (1u << 17) && smax <= kMaxSpan16 - smin && smin <= kMaxSpan16 &&
+                            static_cast<int64_t>(c) * w_max + (1 << 14) < (1 << 25);
+        if (narrow) {
+            uint32_t sq[2][NW];   // at most 16 squares below 2^28 each
+            i16x2 mx[NW];
+#pragma unroll
+            for (int wi = 0; wi < NW; ++wi) {
+                sq[0][wi] = sq[1][wi] = 0u;
+                mx[wi] = i16x2{INT16_MIN, INT16_MIN};
+            }
+            const uint32_t* base = lds + (k0 + off) / 2 + t;
+            auto pair = [&](const uint32_t* q, int wi) -> uint32_t {
+                return ODD1 && wi == 0 ? __builtin_amdgcn_alignbit(q[(w[0] + 1) / 2], q[(w[0] - 1) / 2], 16)
+                                       : q[w[wi] / 2];
+            };
+            if (npos == kSegLen) {
+#pragma unroll
+                for (int hf = 0; hf < 2; ++hf)
 #pragma unroll 8
-                for (int j = 0; j < 8; ++j) {
-                    const uint32_t* q = base + (8 * hf + j) * kThreads;
+                    for (int j = 0; j < 8; ++j) {
+                        const uint32_t* q = base + (8 * hf + j) * kThreads;
+                        const i16x2 p = __builtin_bit_cast(i16x2, q[0]);
+#pragma unroll
+                        for (int wi = 0; wi < NW; ++wi) {
+                            const i16x2 b = __builtin_bit_cast(i16x2, pair(q, wi)) - p;
+                            sq[hf][wi] = static_cast<uint32_t>(
+                                __builtin_amdgcn_sdot2(b, b, static_cast<int>(sq[hf][wi]), false));
+                            mx[wi] = __builtin_elementwise_max(mx[wi], b);
+                        }
+                    }
+            } else {
+                for (int j = 0; j < 16 && 2 * j * kThreads < npos; ++j) {
+                    const uint32_t* q = base + j * kThreads;
+                    const int at = 2 * (j * kThreads + t);
+                    const uint32_t m = at + 1 < npos ? 0xFFFFFFFFu : at < npos ? 0xFFFFu : 0u;
                     const i16x2 p = __builtin_bit_cast(i16x2, q[0]);
 #pragma unroll
                     for (int wi = 0; wi < NW; ++wi) {
-                        const i16x2 b = __builtin_bit_cast(i16x2, pair(q, wi)) - p;
-                        sq[hf][wi] = static_cast<uint32_t>(
-                            __builtin_amdgcn_sdot2(b, b, static_cast<int>(sq[hf][wi]), false));
-                        mx[wi] = __builtin_elementwise_max(mx[wi], b);
+                        const uint32_t b = __builtin_bit_cast(uint32_t, __builtin_bit_cast(i16x2, pair(q, wi)) - p);
+                        const i16x2 bs = __builtin_bit_cast(i16x2, b & m);
+                        const uint32_t dot = static_cast<uint32_t>(
+                            __builtin_amdgcn_sdot2(bs, bs, static_cast<int>(j < 8 ? sq[0][wi] : sq[1][wi]), false));
+                        if (j < 8) sq[0][wi] = dot;
+                        else sq[1][wi] = dot;
+                        mx[wi] = __builtin_elementwise_max(
+                            mx[wi], __builtin_bit_cast(i16x2, (b & m) | (0x80008000u & ~m)));
                     }
                 }
-        } else {
-            for (int j = 0; j < 16 && 2 * j * kThreads < npos; ++j) {
-                const uint32_t* q = base + j * kThreads;
-                const int at = 2 * (j * kThreads + t);
-                const uint32_t m = at + 1 < npos ? 0xFFFFFFFFu : at < npos ? 0xFFFFu : 0u;
-                const i16x2 p = __builtin_bit_cast(i16x2, q[0]);
+            }
+            const int16_t* ph = reinterpret_cast<const int16_t*>(half) + k0 + off;
+            const int64_t s1 =
+                telescoped<NW, false>(w, [&](int i, int) { return static_cast<int>(ph[npos + i]) - ph[i]; });
+            uint64_t s2[NW];
+            int m32[NW];
 #pragma unroll
-                for (int wi = 0; wi < NW; ++wi) {
-                    const uint32_t b = __builtin_bit_cast(uint32_t, __builtin_bit_cast(i16x2, pair(q, wi)) - p);
-                    const i16x2 bs = __builtin_bit_cast(i16x2, b & m);
-                    const uint32_t dot = static_cast<uint32_t>(
-                        __builtin_amdgcn_sdot2(bs, bs, static_cast<int>(j < 8 ? sq[0][wi] : sq[1][wi]), false));
-                    if (j < 8) sq[0][wi] = dot;
-                    else sq[1][wi] = dot;
-                    mx[wi] = __builtin_elementwise_max(mx[wi], __builtin_bit_cast(i16x2, (b & m) | (0x80008000u & ~m)));
-                }
+            for (int wi = 0; wi < NW; ++wi) {
+                s2[wi] = static_cast<uint64_t>(sq[0][wi]) + sq[1][wi];
+                m32[wi] = max(static_cast<int>(mx[wi].x), static_cast<int>(mx[wi].y));
+            }
+            __syncthreads();   // the running sums are no longer needed
+            uint64_t a2;
+            int am;
+            int64_t a1;
+            if (stats_reduce<NW>(s2, m32, s1, lds, &a2, &am, &a1)) store(a2, am, a1);
+            return;
+        }
+    }
+    // 32-bit running sums, half the segment at a time, from the loaded samples.
+    // Position p of half hf is ps[p]; base(i) is P or P' at quad i.
+    const int* ps = reinterpret_cast<const int*>(lds) + k0;
+    auto fill_half = [&](int hf, int cc, auto base) {
+        __syncthreads();   // what the LDS held is no longer needed
+#pragma unroll
+        for (int r = 0; r < kHalfRounds; ++r) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {   // constant indices keep the quads in registers
+                const int i = 4 * h + r;
+                if (h != hf) continue;
+                const uint32_t b = base(i);
+                lds16[r * kThreads + t] = make_uint4(b, v[i].s1(b) - cc, v[i].s2(b) - 2 * cc, v[i].s3(b) - 3 * cc);
             }
         }
-        const int16_t* ph = reinterpret_cast<const int16_t*>(half) + k0 + off;
-        const int64_t s1 = telescoped<NW>(w, [&](int i) { return static_cast<int>(ph[npos + i]) - ph[i]; });
-        uint64_t s2[NW];
-        int m32[NW];
+        __syncthreads();
+    };
+    if (kU16 && w_max > 512) {   // (otherwise the largest 16-bit value passes below)
+        vm = 0;
 #pragma unroll
-        for (int wi = 0; wi < NW; ++wi) {
-            s2[wi] = static_cast<uint64_t>(sq[0][wi]) + sq[1][wi];
-            m32[wi] = max(static_cast<int>(mx[wi].x), static_cast<int>(mx[wi].y));
-        }
-        __syncthreads();   // the running sums are no longer needed
-        uint64_t a2;
-        int am;
-        int64_t a1;
-        if (stats_reduce<NW>(s2, m32, s1, lds, &a2, &am, &a1)) store(a2, am, a1);
-        return;
+        for (int i = 0; i < kRounds; ++i) vm = v[i].vmax(vm);
+        vm = static_cast<uint32_t>(wave_max_i32(static_cast<int>(max(vm & 0xFFFFu, vm >> 16))));
+        if (lane == 63) vmax_w[wave] = vm;
+        __syncthreads();
+        vmax = vmax_w[0];
+#pragma unroll
+        for (int k = 1; k < kThreads / 64; ++k) vmax = max(vmax, vmax_w[k]);
     }
-    // the same with 32-bit running sums: |B'| at most the span, every square
-    // sum below 2^13 x 2^50
-    if (npos == kSegLen && vmax < (1u << 17) && smax < (1 << 23) && smin < (1 << 23) &&
-        static_cast<int64_t>(c) * w_max < (1 << 24)) {
+    // Samples below 2^19: with c within 1 of their mean, P' of N samples spans at
+    // most N 2^19 / 4 (it returns to 0 at the window's end) < 2^31.  Boxcars and
+    // centred boxcars below 2^25 by the largest sample, or |B'| < 2^24 by the span
+    // and c w < 2^24: every square sum below 2^13 x 2^50.
+    const int64_t vw = static_cast<int64_t>(max(vmax, static_cast<uint32_t>(c))) * w_max;
+    if (vmax < (1u << 19) &&
+        (vw < (1 << 25) || (smax < (1 << 23) && smin < (1 << 23) && static_cast<int64_t>(c) * w_max < (1 << 24)))) {
         uint64_t s2[NW];
         int mx[NW];
         int64_t s1 = 0;
+        int first[kTerms];   // P'(i) of the thread's terms
 #pragma unroll
         for (int wi = 0; wi < NW; ++wi) {
             s2[wi] = 0;
             mx[wi] = INT32_MIN;
         }
-        const int* ps = reinterpret_cast<const int*>(lds) + k0;   // P' from the half's first position on
+        constexpr int kUnroll = NW > 10 ? 2 : 4;   // (four spill with 11 widths: 1089 us, 948)
+        const int* base = ps + t;
+        auto add = [&](const int* q) {
+            const int p0 = q[0];
+#pragma unroll
+            for (int wi = 0; wi < NW; ++wi) {
+                const int b = q[w[wi]] - p0;
+                s2[wi] += static_cast<uint64_t>(static_cast<int64_t>(b) * b);
+                mx[wi] = max(mx[wi], b);
+            }
+        };
 #pragma unroll
         for (int hf = 0; hf < 2; ++hf) {
-            __syncthreads();   // the 16-bit sums, the first half's are no longer needed
+            const int n = min(kHalfLen, npos - hf * kHalfLen);
+            if (n <= 0) break;
+            fill_half(hf, c, [&](int i) { return excl[i]; });
+            if (hf == 0) {
 #pragma unroll
-            for (int r = 0; r < kHalfRounds; ++r) {
-                const int i = 4 * hf + r;
-                lds16[r * kThreads + t] = make_uint4(excl[i], v[i].s1(excl[i]) - c, v[i].s2(excl[i]) - 2 * c,
-                                                     v[i].s3(excl[i]) - 3 * c);
+                for (int k = 0; k < kTerms; ++k) first[k] = base[k * kThreads];
             }
-            __syncthreads();
-            const int* base = ps + t;
-#pragma unroll 4
-            for (int j = 0; j < kHalfLen / kThreads; ++j) {
-                const int p0 = base[j * kThreads];
-#pragma unroll
-                for (int wi = 0; wi < NW; ++wi) {
-                    const int b = base[j * kThreads + w[wi]] - p0;
-                    s2[wi] += static_cast<uint64_t>(static_cast<int64_t>(b) * b);
-                    mx[wi] = max(mx[wi], b);
-                }
+            if (n == kHalfLen) {
+#pragma unroll kUnroll
+                for (int j = 0; j < kHalfLen / kThreads; ++j) add(base + j * kThreads);
+            } else {
+                for (int i = t; i < n; i += kThreads) add(ps + i);
             }
-            s1 += telescoped<NW>(w, [&](int i) { return ps[kHalfLen + i] - ps[i]; });
+            if (hf == 1 || npos <= kHalfLen)
+                s1 = telescoped<NW, true>(w, [&](int i, int k) { return ps[n + i] - first[k]; });
         }
         __syncthreads();
         uint64_t a2;
@@ -1144,30 +1226,48 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(sizeof
         if (stats_reduce<NW>(s2, mx, s1, lds, &a2, &am, &a1)) store(a2, am, a1);
         return;
     }
-    __shared__ uint32_t wave_tot[kThreads / 64];
+    // any values: P itself, one width after the other; 64-bit square sums for
+    // boxcars below 2^26 (see width_sums), else 128-bit ones
     __shared__ uint64_t red1[kThreads / 64][NW];
     __shared__ u128 red2[kThreads / 64][NW];
     __shared__ uint32_t redm[kThreads / 64][NW];
-    const T* row = in + static_cast<int64_t>(d) * nout;
-    // any values, any length: 128-bit sums, one width after the other
-    for (int hf = 0; hf < 2; ++hf) {
-        __syncthreads();
-        const int n = min(kHalfLen, npos - hf * kHalfLen);
-        if (n > 0) load_prefix(row, nout, s0 + hf * kHalfLen - 1, kHalfLen + w_max + 1, lds, wave_tot);
-        for (int wi = 0; wi < W.n; ++wi) {
-            uint64_t a1 = 0;
-            u128 a2 = 0;
-            uint32_t am = 0;
-            if (n > 0) width_sums<false>(lds, n, W.w[wi], &a1, &a2, &am);
-            if (lane == 0) {
-                red1[wave][wi] = (hf ? red1[wave][wi] : 0) + a1;
-                red2[wave][wi] = (hf ? red2[wave][wi] : 0) + a2;
-                redm[wave][wi] = max(hf ? redm[wave][wi] : 0u, am);
+    const bool small = static_cast<uint64_t>(vmax) * static_cast<uint64_t>(w_max) < (uint64_t(1) << 26);
+#pragma unroll 1
+    for (int wi = 0; wi < NW; ++wi) {
+        const int ww = W.w[wi];
+        uint64_t s1 = 0, lo = 0, hi = 0;
+        uint32_t mx = 0;
+#pragma unroll
+        for (int hf = 0; hf < 2; ++hf) {
+            const int n = min(kHalfLen, npos - hf * kHalfLen);
+            if (n <= 0) break;
+            fill_half(hf, 0, [&](int i) {
+                return excl[i] + static_cast<uint32_t>(c) * 4u * static_cast<uint32_t>(i * kThreads + t);
+            });
+            for (int i = t; i < n; i += kThreads) {
+                const uint32_t b = static_cast<uint32_t>(ps[i + ww]) - static_cast<uint32_t>(ps[i]);
+                const uint64_t sq = static_cast<uint64_t>(b) * b;
+                s1 += b;
+                lo += sq;
+                hi += lo < sq ? 1u : 0u;
+                mx = max(mx, b);
             }
+        }
+        uint64_t a1;
+        u128 a2;
+        uint32_t am;
+        if (small)
+            wave_totals<true>(s1, lo, hi, mx, &a1, &a2, &am);
+        else
+            wave_totals<false>(s1, lo, hi, mx, &a1, &a2, &am);
+        if (lane == 0) {
+            red1[wave][wi] = a1;
+            red2[wave][wi] = a2;
+            redm[wave][wi] = am;
         }
     }
     __syncthreads();
-    if (t < W.n) {
+    if (t < NW) {
         uint64_t a1 = 0;
         u128 a2 = 0;
         uint32_t am = 0;

@@ -353,3 +353,119 @@ def test_statistics_square_sums_use_all_32_bits():
         for u16 in (True, False):
             _, (g1, g2, gt) = _find(series, widths, 3.0, u16, capacity=1 << 18)
             assert (g1 == s1).all() and (g2 == s2).all() and (gt == thr).all(), u16
+
+
+def _window_extremes(nout):
+    """Series at the limits of the statistics pass's forms: the largest 16-bit
+    value, blocks of the smallest and largest value (the widest span of centred
+    running sums), a strong drift, pulses, and a whole row near one value."""
+    t = np.arange(nout)
+    return np.stack([
+        np.where(t // 2304 % 2 == 0, 65535, 0),
+        np.where(t < nout // 2, 65535, 0),
+        np.full(nout, 65535),
+        (15000 + 9000 * np.sin(t / 3000.0)).astype(np.int64),
+        1500 + 2000 * (t % 2500 < 300),
+        np.where(t % 4096 == 4095, 65535, 0),
+        (t * 65535) // nout,
+    ]).astype(np.int64)
+
+
+@pytest.mark.parametrize("widths", [[1, 2, 4, 8], [1, 64, 256, 512], [2, 16, 514, 1020], [2, 4, 6, 1020]])
+@pytest.mark.parametrize("nout", [700 + 1020, 4096 + 1019, 4097 + 1019, 8192 + 1019, 8192 + 3 * 4096 + 1019 + 5])
+def test_statistics_of_wide_spans(widths, nout):
+    """Windows whose centred running sums span more than 16 bits, whole and
+    ragged, around half a segment: sums, cuts and events equal the oracle's."""
+    series = _window_extremes(nout)
+    bw = oracle.boxcar(series, widths)
+    s1, s2, thr = _ref_stats(bw, 5.0)
+    ref = oracle.find_events(bw, 5.0)
+    for u16 in (True, False):
+        ev, (g1, g2, gt) = _find(series, widths, 5.0, u16, capacity=1 << 18)
+        assert (g1 == s1).all() and (g2 == s2).all() and (gt == thr).all(), u16
+        events_equal(ev, ref)
+
+
+@pytest.mark.parametrize("top", [(1 << 17) - 1, 1 << 17, (1 << 18) + 1, (1 << 19) - 1, 1 << 19, 1 << 21])
+@pytest.mark.parametrize("widths", [[1, 2, 4, 8], [1, 2, 62, 64], [1, 2, 4, 66], [1, 2, 128, 130], [2, 4, 256, 512]])
+def test_statistics_of_large_int32_values(top, widths):
+    """int32 samples around 2^17, 2^19 (where centred running sums give way to
+    plain ones) and, times the widest boxcar, around 2^25 and 2^26 (64- and
+    128-bit square sums): sums, cuts and events equal the oracle's."""
+    nout = 8192 + 4500
+    rng = np.random.default_rng(top % 97 + widths[-1])
+    t = np.arange(nout)
+    series = np.stack([np.full(nout, top), np.where(t // 2304 % 2 == 0, top, 0),
+                       np.where(t < 4608, top, 0), rng.integers(0, top + 1, size=nout),
+                       top - rng.integers(0, 64, size=nout)]).astype(np.int64)
+    bw = oracle.boxcar(series, widths)
+    s1, s2, thr = _ref_stats(bw, 3.0)
+    ref = oracle.find_events(bw, 3.0)
+    ev, (g1, g2, gt) = _find(series, widths, 3.0, False, capacity=1 << 18)
+    assert (g1 == s1).all() and (g2 == s2).all() and (gt == thr).all()
+    events_equal(ev, ref)
+
+
+def test_statistics_time_of_wide_spans():
+    """A window that the 16-bit sums do not take costs a few passes over LDS,
+    not another kind of arithmetic: per position and width a 32-bit read and a
+    64-bit multiply-add in place of half a packed word's, so a search of only
+    such windows takes at most twice one of none.  (Strong drift, and int32
+    values above 2^17; nothing is above the cut, so the rest is the same.)"""
+    import time
+    from paper_1112_0065_amd import _lib as L
+    torch = torch_dev()
+    ndm, nout, widths = 600, 200003, [1 << i for i in range(10)]
+    g = torch.Generator(device="cuda").manual_seed(1)
+    quiet = 12000 + torch.randint(0, 100, (ndm, nout), generator=g, device="cuda", dtype=torch.int32)
+    t = torch.arange(nout, device="cuda").float()
+    drift = quiet + (5000 * torch.sin(t / 3000.0)).to(torch.int32)
+    large = quiet + 60000 + torch.randint(0, 1 << 17, (ndm, nout), generator=g, device="cuda", dtype=torch.int32) // 64 * 64
+    ws = torch.empty(L.find_peaks_workspace_bytes(ndm, nout, widths), dtype=torch.uint8, device="cuda")
+    ev = torch.empty(40 << 10, dtype=torch.uint8, device="cuda")
+
+    def us(series, w):
+        def run():
+            assert L.find_peaks(series, ndm, nout, w, 1000.0, ev, 1 << 10, ws) == 0
+        for _ in range(3):
+            run()
+        times = []
+        for _ in range(7):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(5):
+                run()
+            times.append(time.perf_counter() - t0)
+        return 2e5 * sorted(times)[3]
+
+    for name, a, b, w in (("u16 drift", quiet.to(torch.int16), drift.to(torch.int16), widths),
+                          ("i32 drift", quiet, drift, widths), ("i32 large", quiet, large, widths[:8])):
+        q, x = us(a, w), us(b, w)
+        log(name, "quiet us", q, "wide us", x)
+        assert x <= 2.0 * q, name
+
+
+def test_statistics_packed_square_sums_use_all_32_bits():
+    """The packed form's accumulators near their limit: centred running sums
+    that alternate between 0 and 16000 (a span the form takes) give boxcars of
+    +-16000 at width 512, so a thread's 16 squares sum to 0.95 x 2^32."""
+    nout = 9216
+    series = np.full((3, nout), 30000, np.int64)
+    for row, off in enumerate((256, 257, 300)):
+        at = np.arange(off, nout, 512)
+        series[row, at[0::2]] += 16000
+        series[row, at[1::2]] -= 16000
+    for widths in ([2, 4, 8, 512], [1, 2, 4, 256, 512]):
+        # the form's own conditions: the span of the centred running sums of the
+        # window, and a thread's squares (positions 2 t and 2 t + 1 mod 512 of half a segment)
+        for row in range(3):
+            c = int(series[row].astype(np.float64).mean() + 0.5)
+            p = np.concatenate([[0], np.cumsum(series[row] - c)])[:8192 + 512]
+            assert c == 30000 and p.max() - min(p.min(), 0) <= (1 << 14) - 1
+            b = p[512:512 + 8192] - p[:8192]
+            sq = (b[:4096].reshape(8, 256, 2).astype(np.int64) ** 2).sum(axis=(0, 2))
+            assert (1 << 31) < sq.max() < (1 << 32)
+        s1, s2, thr = _ref_stats(oracle.boxcar(series, widths), 3.0)
+        for u16 in (True, False):
+            _, (g1, g2, gt) = _find(series, widths, 3.0, u16, capacity=1 << 18)
+            assert (g1 == s1).all() and (g2 == s2).all() and (gt == thr).all(), u16
