@@ -18,7 +18,7 @@
 // is one event) are compacted deterministically: count run starts per
 // (width, DM, segment) and per series, exclusive scan over the series, then
 // write each event at its series' slot plus the counts of the segments before
-// -- the output order is (width, DM, t_start) without any sort.  Only the
+// (a series of many segments: at the scan of all counts) -- the output order is (width, DM, t_start) without any sort.  Only the
 // (DM, segment)s whose largest boxcar reaches the cut are counted, and only
 // those with events are written: both passes work through lists of them.
 #include <algorithm>
@@ -1423,7 +1423,7 @@ __global__ __launch_bounds__(NT) void peaks_count_kernel(const T* __restrict__ i
             const int64_t series = static_cast<int64_t>(threadIdx.x) * ndm + d;
             ws.counts[series * nseg + seg] = cnt[threadIdx.x];
             // (a series of one segment: its count is its total)
-            if (nseg > 1 && cnt[threadIdx.x]) atomicAdd(&ws.tot[series], cnt[threadIdx.x]);
+            if (nseg > 1 && !ws.offs && cnt[threadIdx.x]) atomicAdd(&ws.tot[series], cnt[threadIdx.x]);
         }
         if (threadIdx.x == 0) {
             uint32_t tot = 0;
@@ -1709,14 +1709,18 @@ __device__ __forceinline__ void write_segment(const T* __restrict__ in, int ndm,
     __shared__ uint32_t wb[dd::kMaxWidths + 1], wc[dd::kMaxWidths], wfill[dd::kMaxWidths];
     __shared__ uint32_t wthr[dd::kMaxWidths];
     __shared__ int64_t woff[dd::kMaxWidths];   // slot of the segment's first event of each width
-    for (int wi = threadIdx.x >> 6; wi < W.n; wi += NT / 64) {
-        // the series' first slot, then the events of its segments before this one
-        const int64_t series = static_cast<int64_t>(wi) * ndm + d;
-        int64_t before = 0;
-        for (int k = threadIdx.x & 63; k < seg; k += 64) before += ws.counts[series * nseg + k];
+    if (ws.offs) {
+        if (threadIdx.x < W.n) woff[threadIdx.x] = ws.offs[(static_cast<int64_t>(threadIdx.x) * ndm + d) * nseg + seg];
+    } else {
+        for (int wi = threadIdx.x >> 6; wi < W.n; wi += NT / 64) {
+            // the series' first slot, then the events of its segments before this one
+            const int64_t series = static_cast<int64_t>(wi) * ndm + d;
+            int64_t before = 0;
+            for (int k = threadIdx.x & 63; k < seg; k += 64) before += ws.counts[series * nseg + k];
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
-        if ((threadIdx.x & 63) == 0) woff[wi] = ws.soff[series] + before;
+            for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
+            if ((threadIdx.x & 63) == 0) woff[wi] = ws.soff[series] + before;
+        }
     }
     if (threadIdx.x < W.n) {
         const int wi = threadIdx.x;
@@ -1834,13 +1838,12 @@ __device__ __forceinline__ void write_segment(const T* __restrict__ in, int ndm,
     }
 }
 
+// (128 registers, four waves per SIMD: with one more the many events of 74 400
+// segments at 4 sigma took 1460 us in place of 1150.)
 template <typename T, int NT>
-__global__ __launch_bounds__(NT) void peaks_write_kernel(const T* __restrict__ in, int ndm,
-                                                               int64_t nout, int64_t nbx,
-                                                               dd::Widths W, int L, int nseg,
-                                                               dd::PeaksWs ws,
-                                                               dedisp_event* __restrict__ events,
-                                                               int64_t capacity) {
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4)))
+void peaks_write_kernel(const T* __restrict__ in, int ndm, int64_t nout, int64_t nbx, dd::Widths W, int L,
+                        int nseg, dd::PeaksWs ws, dedisp_event* __restrict__ events, int64_t capacity) {
     extern __shared__ uint32_t pl[];
     __shared__ uint32_t wave_tot[NT / 64];
     __shared__ int starts[kMaxStarts];
@@ -1883,6 +1886,13 @@ constexpr int64_t kListWaves = 8192;
 // 9.6 us, where scanning the counts of all their segments with three kernels
 // took 25); more take the three-kernel scan.
 constexpr int64_t kOneBlockScan = 16 * kSeriesScan;
+
+// Most segments of a series whose counts every listed segment of it adds up by
+// itself; the events' slots of longer series come from a scan of all counts with
+// three kernels.  find_peaks on 4 series of uint16 with every segment listed, us,
+// without and with the scan: 512 segments each 280 and 303, 1024 499 and 516, 2048
+// 920 and 918, 4096 1798 and 1708; one series of 32768 segments 7315 and 5024.
+constexpr int kSeriesSegments = 2048;
 
 size_t peaks_lds_bytes(int L, int w_max) { return static_cast<size_t>(L + w_max + 1) * 4; }
 
@@ -2072,6 +2082,7 @@ PeaksWs peaks_ws(void* base, const PeaksLayout& lay) {
     ws.sqrt_d = reinterpret_cast<double*>(b + lay.o_sqrt_d);
     ws.counts = reinterpret_cast<uint32_t*>(b + lay.o_counts);
     ws.soff = reinterpret_cast<int64_t*>(b + lay.o_offs);
+    ws.offs = lay.nseg > kSeriesSegments ? ws.soff : nullptr;
     ws.tot = lay.nseg > 1 ? reinterpret_cast<uint32_t*>(ws.soff + lay.nseries) : ws.counts;
     ws.chunk_tot = reinterpret_cast<int64_t*>(b + lay.o_chunk);
     ws.total = reinterpret_cast<int64_t*>(b + lay.o_total);
@@ -2152,6 +2163,7 @@ hipError_t launch_peaks_count(const void* in, int in_u16, int ndm, int64_t nout,
         launch_count(static_cast<const int32_t*>(in), ndm, nout, W, lay, ws, lds, s);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (ws.offs) return launch_scan_u32(ws.counts, lay.ncounts, ws.offs, ws.chunk_tot, ws.total, s);
     if (lay.nseries <= kOneBlockScan) {
         hipLaunchKernelGGL(scan_series_kernel, dim3(1), dim3(kScanThreads), 0, s, ws.tot, nser, ws.soff, ws.total);
         return hipGetLastError();

@@ -34,6 +34,7 @@ struct PeaksWs {
     uint32_t* counts;      // [nw][ndm][nseg] run starts
     uint32_t* tot;         // [nw][ndm] run starts of the series (the counts themselves when nseg == 1)
     int64_t* soff;         // [nw][ndm] exclusive scan of tot: the series' first event slot
+    int64_t* offs;         // [nw][ndm][nseg] exclusive scan of counts (long series, in place of tot and soff), or NULL
     int64_t* chunk_tot;    // scan scratch
     int64_t* total;        // total number of events
     uint32_t* list;        // [ndm * nseg] (DM, segment)s to count (d * nseg + seg)

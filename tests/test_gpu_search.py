@@ -469,3 +469,61 @@ def test_statistics_packed_square_sums_use_all_32_bits():
         for u16 in (True, False):
             _, (g1, g2, gt) = _find(series, widths, 3.0, u16, capacity=1 << 18)
             assert (g1 == s1).all() and (g2 == s2).all() and (gt == thr).all(), u16
+
+
+def _us(run, calls=3, rounds=5):
+    """Median time of one call, us (find_peaks waits for the GPU by itself)."""
+    import time
+    torch = torch_dev()
+    run()
+    times = []
+    for _ in range(rounds):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        for _ in range(calls):
+            run()
+        times.append((time.perf_counter() - t0) / calls)
+    return 1e6 * sorted(times)[rounds // 2]
+
+
+@pytest.mark.parametrize("nseg", [2048, 2049])
+def test_event_slots_of_long_series(nseg):
+    """The event slots of a series of at most 2048 segments and of a longer one:
+    events in every segment's place, equal to the oracle's."""
+    rng = np.random.default_rng(nseg)
+    widths = [1, 3]
+    nout = (nseg - 1) * 8192 + 77 + widths[-1] - 1
+    series = rng.integers(0, 40, size=(2, nout)).astype(np.int64)
+    for row, step in enumerate((3001, 90001)):
+        series[row, 5::step] += 400
+    ref = oracle.find_events(oracle.boxcar(series, widths), 12.0)
+    assert len(ref) > nseg
+    for u16 in (True, False):
+        ev, _ = _find(series, widths, 12.0, u16, capacity=1 << 16)
+        events_equal(ev, ref)
+
+
+def test_time_of_a_long_series_is_linear():
+    """What the events of a series cost (every segment has one) grows with its
+    segments, not with their square: per segment 32768 of them take no more than
+    4096, half as much again allowed."""
+    from paper_1112_0065_amd import _lib as L
+    torch = torch_dev()
+    widths = [1 << i for i in range(10)]
+    g = torch.Generator(device="cuda").manual_seed(2)
+    cost = {}
+    for lg in (25, 28):
+        nout = (1 << lg) + 511
+        quiet = torch.randint(1000, 1100, (1, nout), generator=g, device="cuda", dtype=torch.int16)
+        pulses = quiet.clone()
+        pulses[:, 4000::8192] += 3000
+        ws = torch.empty(L.find_peaks_workspace_bytes(1, nout, widths), dtype=torch.uint8, device="cuda")
+        ev = torch.empty(40 << 20, dtype=torch.uint8, device="cuda")
+        nseg, t = 1 << (lg - 13), []
+        for series in (quiet, pulses):
+            n = L.find_peaks(series, 1, nout, widths, 20.0, ev, 1 << 20, ws)
+            assert n == 0 if series is quiet else n >= nseg
+            t.append(_us(lambda: L.find_peaks(series, 1, nout, widths, 20.0, ev, 1 << 20, ws)))
+        cost[lg] = (t[1] - t[0]) / nseg
+        log("segments", nseg, "quiet us", t[0], "events us", t[1], "per segment", cost[lg])
+    assert cost[28] <= 1.5 * cost[25]
