@@ -32,9 +32,8 @@
 namespace {
 
 constexpr int kThreads = 256;
-// Threads per block of the list-driven count and write passes (see
-// few_segments).
-constexpr int kFewThreads = 1024;
+// Threads per block of the list-driven count and write passes (see launch_list).
+constexpr int kFewThreads = 1024, kMidThreads = 512;
 // ----------------------------------------------------------------------------
 // Block-level helpers.
 // ----------------------------------------------------------------------------
@@ -1414,9 +1413,10 @@ __global__ __launch_bounds__(NT) void peaks_count_kernel(const T* __restrict__ i
                     }
                 }
             }
+            if (!__ballot(c != 0)) continue;   // most waves of the larger blocks
 #pragma unroll
             for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o, 64);
-            if (lane == 0 && c) atomicAdd(&cnt[wi], c);
+            if (lane == 0) atomicAdd(&cnt[wi], c);
         }
         __syncthreads();
         if (threadIdx.x < W.n) {
@@ -1712,14 +1712,17 @@ __device__ __forceinline__ void write_segment(const T* __restrict__ in, int ndm,
     if (ws.offs) {
         if (threadIdx.x < W.n) woff[threadIdx.x] = ws.offs[(static_cast<int64_t>(threadIdx.x) * ndm + d) * nseg + seg];
     } else {
-        for (int wi = threadIdx.x >> 6; wi < W.n; wi += NT / 64) {
-            // the series' first slot, then the events of its segments before this one
+        // the series' first slot, then the events of its segments before this one:
+        // 16 widths at a time
+        constexpr int kG = NT / 16;
+        const int l = threadIdx.x % kG;
+        for (int wi = threadIdx.x / kG; wi < W.n; wi += 16) {
             const int64_t series = static_cast<int64_t>(wi) * ndm + d;
-            int64_t before = 0;
-            for (int k = threadIdx.x & 63; k < seg; k += 64) before += ws.counts[series * nseg + k];
+            int64_t before = l == 0 ? ws.soff[series] : 0;
+            for (int k = l; k < seg; k += kG) before += ws.counts[series * nseg + k];
 #pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
-            if ((threadIdx.x & 63) == 0) woff[wi] = ws.soff[series] + before;
+            for (int o = kG / 2; o >= 1; o >>= 1) before += __shfl_xor(before, o, 64);
+            if (l == 0) woff[wi] = before;
         }
     }
     if (threadIdx.x < W.n) {
@@ -1870,15 +1873,23 @@ int segment_length(int w_max) {
     return L;
 }
 
-// The lists hold the few (DM, segment)s with something above the cut, a few
-// per cent of them.  Up to kFewSegments segments in all, that leaves most of
-// the chip idle and a listed segment's own time counts: blocks of kFewThreads
-// (301 series of 100 003 samples, 3913 segments: count 39 -> 26 us, write 47 ->
-// 32; 100 segments: 35 -> 18, 40 -> 20).  With more listed segments than
-// resident blocks the smaller blocks win (74 400 segments: 192 us for both
-// passes, 247 with kFewThreads).
-constexpr int64_t kFewSegments = 32768;
-bool few_segments(int ndm, int nseg) { return static_cast<int64_t>(ndm) * nseg <= kFewSegments; }
+// Blocks of the count and write passes.  They work through lists whose lengths only
+// the device knows: a few per cent of the (DM, segment)s in a clean search, most of
+// them at a low cut or with interference.  Larger blocks finish a listed segment
+// sooner, smaller ones keep more of them in flight (a block of 1024 write threads
+// fills a CU).  So the number of all segments decides, with both ends measured; us
+// for count + write with 1024, 512 and 256 threads, clean and all listed:
+//      108 segments    48   65  105       52   68  113
+//      800             44   54   86       98   87  118
+//     1960            101   83  110      210  158  190
+//     3913             75   69  110      312  253  246
+//    12400            216  155  176      969  754  722
+// (1960: more pulses than in the others' clean series.)  Up to 2560 what the largest
+// blocks lose at worst is less than the rest of the search has gained, and a clean
+// search gains (1200 series of 9500 samples, 2400 segments: 100 us, 111 with 512).
+// Beyond 32768 the larger blocks would only lose (the survey series, 74 400: 192
+// us with 256 threads, 247 with 1024).
+constexpr int64_t kFewSegments = 2560, kMidSegments = 32768;
 // Waves of the list-driven passes' blocks: 32 per CU.
 constexpr int64_t kListWaves = 8192;
 
@@ -2114,13 +2125,23 @@ void launch_count_nt(const T* in, int ndm, int64_t nout, const Widths& W, const 
                        ndm, nout, lay.nbx, W, lay.L, lay.nseg, ws);
 }
 
+// launch(block size) of a list-driven pass.
+template <typename F>
+void launch_list(int64_t segments, F launch) {
+    if (segments <= kFewSegments)
+        launch(std::integral_constant<int, kFewThreads>{});
+    else if (segments <= kMidSegments)
+        launch(std::integral_constant<int, kMidThreads>{});
+    else
+        launch(std::integral_constant<int, kThreads>{});
+}
+
 template <typename T>
 void launch_count(const T* in, int ndm, int64_t nout, const Widths& W, const PeaksLayout& lay,
                   const PeaksWs& ws, size_t lds, hipStream_t s) {
-    if (few_segments(ndm, lay.nseg))
-        launch_count_nt<T, kFewThreads>(in, ndm, nout, W, lay, ws, lds, s);
-    else
-        launch_count_nt<T, kThreads>(in, ndm, nout, W, lay, ws, lds, s);
+    launch_list(static_cast<int64_t>(ndm) * lay.nseg, [&](auto nt) {
+        launch_count_nt<T, decltype(nt)::value>(in, ndm, nout, W, lay, ws, lds, s);
+    });
 }
 
 template <typename T, int NT>
@@ -2135,10 +2156,9 @@ void launch_write_nt(const T* in, int ndm, int64_t nout, const Widths& W, const 
 template <typename T>
 void launch_write(const T* in, int ndm, int64_t nout, const Widths& W, const PeaksLayout& lay,
                   const PeaksWs& ws, dedisp_event* events, int64_t capacity, size_t lds, hipStream_t s) {
-    if (few_segments(ndm, lay.nseg))
-        launch_write_nt<T, kFewThreads>(in, ndm, nout, W, lay, ws, events, capacity, lds, s);
-    else
-        launch_write_nt<T, kThreads>(in, ndm, nout, W, lay, ws, events, capacity, lds, s);
+    launch_list(static_cast<int64_t>(ndm) * lay.nseg, [&](auto nt) {
+        launch_write_nt<T, decltype(nt)::value>(in, ndm, nout, W, lay, ws, events, capacity, lds, s);
+    });
 }
 
 hipError_t launch_peaks_count(const void* in, int in_u16, int ndm, int64_t nout, const Widths& W,

@@ -527,3 +527,43 @@ def test_time_of_a_long_series_is_linear():
         cost[lg] = (t[1] - t[0]) / nseg
         log("segments", nseg, "quiet us", t[0], "events us", t[1], "per segment", cost[lg])
     assert cost[28] <= 1.5 * cost[25]
+
+
+@pytest.mark.parametrize("ndm,nout", [(60, 8192 + 303), (2560, 90), (2561, 90), (1290, 8192 + 303), (32768, 40), (32769, 40)])
+def test_list_passes_with_every_block_size(ndm, nout):
+    """The count and write passes on both sides of the lines between their block
+    sizes (2560 and 32768 segments in all): every series listed, one with more runs
+    in a segment than the passes list at once, equal to the oracle's."""
+    rng = np.random.default_rng(ndm)
+    widths = [1, 2]
+    series = rng.integers(0, 4, size=(ndm, nout)).astype(np.int64)
+    at = rng.integers(0, nout, size=ndm)
+    series[np.arange(ndm), at] += 60
+    if nout > 8192:
+        series[:, 100:] = 0           # (few runs elsewhere)
+        series[3, ::3] += 60          # 2832 runs, 2731 of them in the first segment
+    ref = oracle.find_events(oracle.boxcar(series, widths), 1.2)
+    assert len(ref) > ndm
+    for u16 in (True, False):
+        ev, _ = _find(series, widths, 1.2, u16, capacity=1 << 20)
+        events_equal(ev, ref)
+
+
+def test_time_of_listed_segments_on_both_sides_of_the_line():
+    """With every segment listed, a segment's share of a search of 30500 segments
+    (the larger blocks) is that of 36600 (the smaller ones), 15% allowed."""
+    from paper_1112_0065_amd import _lib as L
+    torch = torch_dev()
+    widths, nout = [1 << i for i in range(10)], 500000
+    g = torch.Generator(device="cuda").manual_seed(4)
+    per = []
+    for ndm in (500, 600):
+        x = torch.randn((ndm, nout), generator=g, device="cuda").mul_(30).add_(1500).round_().to(torch.int16)
+        ws = torch.empty(L.find_peaks_workspace_bytes(ndm, nout, widths), dtype=torch.uint8, device="cuda")
+        ev = torch.empty(40 << 20, dtype=torch.uint8, device="cuda")
+        n = L.find_peaks(x, ndm, nout, widths, 4.0, ev, 1 << 20, ws)
+        segments = ndm * -(-(nout - 511) // 8192)
+        per.append(_us(lambda: L.find_peaks(x, ndm, nout, widths, 4.0, ev, 1 << 20, ws)) / segments)
+        log("segments", segments, "events", n, "us per segment", per[-1])
+        assert n > segments
+    assert per[0] <= 1.15 * per[1]
