@@ -93,26 +93,26 @@ dedisp_status repack(dedisp_plan p, const uint8_t* in, int64_t nsamps, void* wor
 }
 
 dedisp_status execute_repacked(dedisp_plan p, const void* workspace, int64_t nsamps, void* out,
-                               dedisp_out_type out_type, const TileConfig& cfg,
+                               dedisp_out_type out_type, const TileConfig& cfg, Form form,
                                hipStream_t stream) {
     dedisp_status st = check_exec(p, workspace, nsamps);
     if (st != DEDISP_OK) return st;
     if (!out) return fail(DEDISP_ERR_INVALID_ARG, "NULL output");
     if (!valid_type(out_type)) return fail(DEDISP_ERR_INVALID_ARG, "bad out_type");
     st = launch_dedisperse(p, static_cast<const uint2*>(workspace), repack_words(nsamps),
-                           nsamps - p->max_delay, out, out_type == DEDISP_OUT_U16, cfg, stream);
+                           nsamps - p->max_delay, out, out_type == DEDISP_OUT_U16, cfg, form, stream);
     if (st == DEDISP_OK) clear_error();
     return st;
 }
 
 dedisp_status execute_with_tile(dedisp_plan p, const uint8_t* in, int64_t nsamps, void* out,
                                 dedisp_out_type out_type, void* workspace, const TileConfig& cfg,
-                                hipStream_t stream) {
+                                Form form, hipStream_t stream) {
     if (!p || !in || !out || !workspace) return fail(DEDISP_ERR_INVALID_ARG, "NULL argument");
     if (!valid_type(out_type)) return fail(DEDISP_ERR_INVALID_ARG, "bad out_type");
     dedisp_status st = repack(p, in, nsamps, workspace, stream);
     if (st != DEDISP_OK) return st;
-    return execute_repacked(p, workspace, nsamps, out, out_type, cfg, stream);
+    return execute_repacked(p, workspace, nsamps, out, out_type, cfg, form, stream);
 }
 
 }  // namespace dd
@@ -122,7 +122,7 @@ extern "C" dedisp_status dedisp_execute(dedisp_plan p, const uint8_t* in, int64_
                                         dedisp_stream stream) {
     if (!p) return fail(DEDISP_ERR_INVALID_ARG, "plan is NULL");
     return dd::execute_with_tile(p, in, nsamps, out, out_type, workspace,
-                                 dd::default_tile_config(p), stream);
+                                 dd::default_tile_config(p), dd::Form::kPlan, stream);
 }
 
 namespace {
@@ -176,7 +176,7 @@ extern "C" dedisp_status dedisp_execute_tile(dedisp_plan p, const uint8_t* in, i
     dd::TileConfig cfg;
     dedisp_status st = tile_from(tile, p, &cfg);
     if (st != DEDISP_OK) return st;
-    return dd::execute_with_tile(p, in, nsamps, out, out_type, workspace, cfg, stream);
+    return dd::execute_with_tile(p, in, nsamps, out, out_type, workspace, cfg, dd::Form::kTile, stream);
 }
 
 extern "C" dedisp_status dedisp_repack(dedisp_plan p, const uint8_t* in, int64_t nsamps,
@@ -194,7 +194,8 @@ extern "C" dedisp_status dedisp_execute_repacked(dedisp_plan p, const void* work
     dd::TileConfig cfg;
     dedisp_status st = tile_from(tile, p, &cfg);
     if (st != DEDISP_OK) return st;
-    return dd::execute_repacked(p, workspace, nsamps, out, out_type, cfg, stream);
+    return dd::execute_repacked(p, workspace, nsamps, out, out_type, cfg,
+                                tile ? dd::Form::kTile : dd::Form::kPlan, stream);
 }
 
 extern "C" dedisp_status boxcar_filter(const void* in, dedisp_out_type in_type, int32_t ndm,

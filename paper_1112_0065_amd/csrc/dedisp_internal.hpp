@@ -88,6 +88,10 @@ struct dedisp_plan_s {
 
 namespace dd {
 
+inline bool same_tile(const TileConfig& a, const TileConfig& b) {
+    return a.dms_per_block == b.dms_per_block && a.groups == b.groups && a.stage_chans == b.stage_chans;
+}
+
 inline int dm_block_index(int dms_per_block) {
     switch (dms_per_block) {
         case 4: return 0;
@@ -102,9 +106,15 @@ inline int dm_block_index(int dms_per_block) {
 hipError_t launch_repack(const uint8_t* in, int64_t nsamps, int nchans, uint2* words,
                          int64_t nwords, hipStream_t s, const uint8_t* mask = nullptr,
                          int64_t mask_n = 0);
+// Kernels that a launch may take: of a grid with few items, the few-items form
+// where `cfg` is its tile (kTile) or whatever the plan's tile is (kPlan: a tuned
+// tile stands for the ordinary, persistent and many-input kernels, which the
+// tuner times); kOrdinary never takes it.
+enum class Form { kOrdinary, kTile, kPlan };
 dedisp_status launch_dedisperse(const dedisp_plan_s* p, const uint2* words,
                                 int64_t nwords, int64_t nout, void* out, int out_u16,
-                                const TileConfig& cfg, hipStream_t s);
+                                const TileConfig& cfg, Form form, hipStream_t s);
+constexpr TileConfig kDefaultTile = {16, 1, 8};   // also the few-items form's
 // Up to kMaxMany inputs of plans of one channel count at one tile shape, uint16
 // output, in one launch.
 constexpr int kMaxMany = 32;   // descriptors that fit a kernel's arguments (4 KB)

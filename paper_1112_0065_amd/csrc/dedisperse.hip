@@ -709,19 +709,25 @@ hipError_t launch_many_cfg(const ManyArgs& m, int n, int64_t total, int stage_ch
 // 960 -> 730 us).  Up to half an item per CU, halving the trials per block
 // uses twice the CUs: 70-79 us.  Above two items per CU the ordinary kernel's
 // more adds per table entry and copy win (2.5: 295 against 296 us, 3.5: 345
-// against 381).
+// against 381).  A plan with a tuned tile takes this form as well, but for just
+// above one item per CU, where a second pass runs nearly empty: of the other tiles
+// the best takes 174 us at 1.09 items per CU of 1024 channels, this form 187; 142
+// and 95 at 0.88, 209 and 187 at 1.75.
 struct FewShape {
     int waves, nsub;
 };
 
-FewShape few_shape(const dd::BeamArgs& a, const dd::TileConfig& cfg, int device) {
+// `a` at the default tile; `tuned`: the plan has another.
+FewShape few_shape(const dd::BeamArgs& a, bool tuned, int device) {
     constexpr FewShape kNone = {0, 0};
-    if (cfg.dms_per_block != kFewTrials || cfg.groups != 1 || cfg.stage_chans != 8 || (a.nchans & 7))
-        return kNone;
+    static_assert(dd::kDefaultTile.dms_per_block == kFewTrials && dd::kDefaultTile.groups == 1 &&
+                  dd::kDefaultTile.stage_chans == 8, "the form's tile");
+    if (a.nchans & 7) return kNone;
     int cus = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus < 1)
         return kNone;
     if (a.n_items > 2 * static_cast<int64_t>(cus)) return kNone;
+    if (tuned && a.n_items > cus && 4 * a.n_items <= 5 * static_cast<int64_t>(cus)) return kNone;
     // pairs of stages that both buffers hold in a CU's LDS (one block per CU)
     const int64_t pair = 2 * int64_t(16) * a.pitch * 16;
     const int64_t n = std::min<int64_t>({kLdsBytes / pair, kFewStages / 2, (a.nchans / 8 + 1) / 2});
@@ -830,7 +836,7 @@ BeamArgs beam_args(const dedisp_plan_s* p, const uint2* words, int64_t nwords, i
 
 dedisp_status launch_dedisperse(const dedisp_plan_s* p, const uint2* words, int64_t nwords,
                                 int64_t nout, void* out, int out_u16, const TileConfig& cfg,
-                                hipStream_t s) {
+                                Form form, hipStream_t s) {
     const int k = dm_block_index(cfg.dms_per_block);
     if (k < 0 || cfg.stage_chans < 4 || cfg.stage_chans % 4 || cfg.groups < 1 || cfg.groups > 2)
         return fail(DEDISP_ERR_INVALID_ARG, "unsupported tile configuration");
@@ -844,13 +850,17 @@ dedisp_status launch_dedisperse(const dedisp_plan_s* p, const uint2* words, int6
     if (!offset_table(p, cfg, true, &st)) return st;
     const BeamArgs a = beam_args(p, words, nwords, nout, out, cfg);
     hipError_t e = hipErrorInvalidValue;
-    const FewShape few = few_shape(a, cfg, p->device);
-    if (few.waves) {
-        e = nl == 12 ? (out_u16 ? launch_few_shape<12, true>(a, few, s) : launch_few_shape<12, false>(a, few, s))
-                     : (out_u16 ? launch_few_shape<16, true>(a, few, s) : launch_few_shape<16, false>(a, few, s));
-        if (e != hipSuccess)
-            return fail(DEDISP_ERR_HIP, "dedispersion launch failed: %s", hipGetErrorString(e));
-        return DEDISP_OK;
+    const bool own = same_tile(cfg, kDefaultTile);
+    if (form == Form::kPlan || (form == Form::kTile && own)) {
+        const BeamArgs b = own ? a : beam_args(p, words, nwords, nout, out, kDefaultTile);
+        const FewShape few = b.offs ? few_shape(b, !own, p->device) : FewShape{0, 0};
+        if (few.waves) {
+            e = nl == 12 ? (out_u16 ? launch_few_shape<12, true>(b, few, s) : launch_few_shape<12, false>(b, few, s))
+                         : (out_u16 ? launch_few_shape<16, true>(b, few, s) : launch_few_shape<16, false>(b, few, s));
+            if (e != hipSuccess)
+                return fail(DEDISP_ERR_HIP, "dedispersion launch failed: %s", hipGetErrorString(e));
+            return DEDISP_OK;
+        }
     }
 #define DD_DISPATCH(NL_, NDW_, G_)                                                    \
     if (nl == NL_ && cfg.dms_per_block == NDW_ * kWaves && cfg.groups == G_)          \
@@ -888,7 +898,7 @@ dedisp_status launch_dedisperse_many(const ManyItem* items, int n, const TileCon
     if (one_by_one || total > (int64_t(1) << 30)) {
         for (int i = 0; i < n; ++i) {
             const ManyItem& it = items[i];
-            const dedisp_status st = launch_dedisperse(it.plan, it.words, it.nwords, it.nout, it.out, 1, cfg, s);
+            const dedisp_status st = launch_dedisperse(it.plan, it.words, it.nwords, it.nout, it.out, 1, cfg, Form::kPlan, s);
             if (st != DEDISP_OK) return st;
         }
         return DEDISP_OK;

@@ -143,6 +143,9 @@ extern "C" dedisp_status dedisp_plan_create(int32_t nchans, double f_top, double
             dedisp_plan_destroy(p);
             return st;
         }
+        // a plan with another tile keeps the few-items form's table as well (where
+        // it can be had), as an execution builds none
+        (void)dd::offset_table(p, dd::kDefaultTile, true);
     }
     *plan_out = p;
     dd::clear_error();

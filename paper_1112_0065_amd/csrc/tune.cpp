@@ -5,7 +5,9 @@
 // deterministic pseudo-random 2-bit input on the device, computes a reference
 // with the default shape, and for each candidate first checks that its output
 // is bit-identical to the reference (candidates that differ are rejected and
-// reported, never timed), then times it with HIP events.  The fastest shape
+// reported, never timed), then times it with HIP events, in the ordinary kernel
+// whatever the length: the persistent and the many-input kernels that take the
+// plan's shape share its code.  The fastest shape
 // becomes the plan's default and is stored in a small JSON cache keyed by
 // (architecture, nchans, DM-count bucket, output type).
 #include <algorithm>
@@ -121,7 +123,7 @@ namespace dd {
 TileConfig default_tile_config(const dedisp_plan_s* p) {
     const int packed = p->tuned.load();
     if (packed) return TileConfig{packed >> 16, (packed >> 8) & 0xFF, packed & 0xFF};
-    return TileConfig{16, 1, 8};
+    return kDefaultTile;
 }
 
 TileConfig tuned_or_default(const dedisp_plan_s* p, const char* cache_path, int out_u16) {
@@ -199,7 +201,7 @@ extern "C" dedisp_status dedisp_autotune(dedisp_plan p, int64_t nsamps, dedisp_o
     e = dd::launch_repack(in, nsamps, p->nchans, words, nwords, s);
     const dd::TileConfig base = dd::default_tile_config(p);
     if (e == hipSuccess)
-        st = dd::launch_dedisperse(p, words, nwords, nout, ref, u16, base, s);
+        st = dd::launch_dedisperse(p, words, nwords, nout, ref, u16, base, dd::Form::kOrdinary, s);
     if (e != hipSuccess || st != DEDISP_OK) {
         cleanup();
         return st != DEDISP_OK ? st : fail(DEDISP_ERR_HIP, "autotune: %s", hipGetErrorString(e));
@@ -214,7 +216,7 @@ extern "C" dedisp_status dedisp_autotune(dedisp_plan p, int64_t nsamps, dedisp_o
     for (const dedisp_tile& t : cands) {
         const dd::TileConfig c{t.dms_per_block, t.groups, t.stage_chans};
         if (dd::tile_lds_bytes(p, c) > 160 * 1024) continue;
-        if (dd::launch_dedisperse(p, words, nwords, nout, cand, u16, c, s) != DEDISP_OK) continue;
+        if (dd::launch_dedisperse(p, words, nwords, nout, cand, u16, c, dd::Form::kOrdinary, s) != DEDISP_OK) continue;
         hipLaunchKernelGGL(zero_u64_kernel, dim3(1), dim3(1), 0, s, bad);
         hipLaunchKernelGGL(count_mismatch_kernel, dim3(static_cast<unsigned>((nbytes + 255) / 256)),
                            dim3(256), 0, s, ref, cand, nbytes, bad);
@@ -229,7 +231,7 @@ extern "C" dedisp_status dedisp_autotune(dedisp_plan p, int64_t nsamps, dedisp_o
         std::vector<float> ms;
         for (int rep = 0; rep < 3 && e == hipSuccess; ++rep) {
             e = hipEventRecord(e0, s);
-            if (dd::launch_dedisperse(p, words, nwords, nout, cand, u16, c, s) != DEDISP_OK) break;
+            if (dd::launch_dedisperse(p, words, nwords, nout, cand, u16, c, dd::Form::kOrdinary, s) != DEDISP_OK) break;
             if (e == hipSuccess) e = hipEventRecord(e1, s);
             if (e == hipSuccess) e = hipEventSynchronize(e1);
             float m = 0;

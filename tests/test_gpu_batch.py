@@ -288,3 +288,46 @@ def test_batch_stages_equal_standalone_and_oracle_chain():
     assert [L.events_from_buffer(evs[b], again[b]).tobytes() for b in range(nb)] == plain_ev
     _, _, captures = L.dedisp_batch_info(batch)
     assert captures == 3
+
+
+def _kernels(run):
+    """Names of the GPU kernels that run() launches."""
+    torch = torch_dev()
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        run()
+        torch.cuda.synchronize()
+    return [e.key for e in prof.key_averages()]
+
+
+def test_autotune_times_the_kernel_its_shape_is_for(tmp_path, monkeypatch):
+    """A shape is for the ordinary, persistent and many-input kernels, so the tuner
+    times those on a short input too, where a call of its own takes the few-items
+    form; and a plan with another shape than that form's takes it all the same, with
+    equal output."""
+    from paper_1112_0065_amd import _lib as L
+    torch = torch_dev()
+    nchans, ndm, nsamps = 256, 64, 12000
+    args = (nchans, 1581.8, -400.0 / nchans, 64e-6, np.linspace(0.0, 60.0, ndm))
+    cache = str(tmp_path / "tune.json")
+    p = L.dedisp_plan_create(*args)
+    names = _kernels(lambda: L.dedisp_autotune(p, nsamps, True, cache))
+    assert any("dedisperse_kernel" in n for n in names), names
+    assert not any("dedisperse_few_kernel" in n for n in names), names
+    text = open(cache).read()
+    key, row = text.split("[")
+    open(cache, "w").write(key + "[8, 2, 16, 1.0" + row[row.index("]"):])
+    monkeypatch.setenv("DEDISP_TUNE_CACHE", cache)
+    q = L.dedisp_plan_create(*args)
+    assert tuple(L.dedisp_default_tile(q)) == (8, 2, 16)
+    x = torch.randint(0, 256, (nsamps * nchans // 4,), dtype=torch.uint8, device="cuda")
+    outs = []
+    for tile in (None, (8, 2, 16)):
+        ws = torch.empty(L.dedisp_workspace_bytes(q, nsamps), dtype=torch.uint8, device="cuda")
+        out = torch.empty((ndm, nsamps - q.max_delay), dtype=torch.int16, device="cuda")
+        L.dedisp_repack(q, x, nsamps, ws)
+        names = _kernels(lambda: L.dedisp_execute_repacked(q, ws, nsamps, out, tile))
+        assert any("dedisperse_few_kernel" in n for n in names) == (tile is None), (tile, names)
+        outs.append(out)
+    assert torch.equal(*outs)
