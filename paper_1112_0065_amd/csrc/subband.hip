@@ -165,7 +165,7 @@ __global__ __launch_bounds__(kS2Threads) void subband_sum_kernel(
     }
 #pragma unroll
     for (int g = 0; g < GM; ++g) {
-        if (g >= gq) break;
+        if (g >= gq) continue;   // (a break keeps the loop of 16 rolled, its sums in scratch)
 #pragma unroll
         for (int j = 0; j < kS2Pairs; ++j) {
             const int64_t t = t0 + 2 * (tid + j * kS2Threads);

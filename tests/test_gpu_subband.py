@@ -100,3 +100,30 @@ def test_output_lengths_around_a_tile(extra):
     for u16 in (True, False):
         _, got = _run(fb, plan, 8, 3, u16, packed=fb.packed[:nsamps * fb.nchans // 4], nsamps=nsamps)
         assert got.shape == ref.shape == (len(fb.dm_list), extra) and (got == ref).all(), u16
+
+
+def test_time_of_large_groups():
+    """A group of 16 trials sums half the coarse series that groups of 8 do, and the
+    same fine ones: it takes no longer (a tenth allowed for the wider staged rows)."""
+    import time
+    from paper_1112_0065_amd import _lib as L
+    torch = torch_dev()
+    nchans, ndm, nsamps = 1024, 400, 1 << 18
+    plan = L.dedisp_plan_create(nchans, 1581.8, -400.0 / nchans, 64e-6, np.linspace(0.0, 300.0, ndm))
+    x = torch.randint(0, 256, (nsamps * nchans // 4,), dtype=torch.uint8, device="cuda")
+    us = {}
+    for group in (8, 16):
+        sb = L.dedisp_subband_create(plan, 16, group)
+        ws = torch.empty(L.dedisp_subband_workspace_bytes(sb, nsamps), dtype=torch.uint8, device="cuda")
+        out = torch.empty((ndm, nsamps - sb.max_delay), dtype=torch.int16, device="cuda")
+        times = []
+        for _ in range(6):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(5):
+                L.dedisp_subband_execute(sb, x, nsamps, out, ws)
+            torch.cuda.synchronize()
+            times.append((time.perf_counter() - t0) / 5)
+        us[group] = 1e6 * sorted(times)[2]
+    log("us by group", us)
+    assert us[16] <= 1.1 * us[8]
