@@ -16,15 +16,15 @@
 // against the direct delay grows with the subband width and the DM distance
 // to the group's middle trial.
 //
-// Design.  Stage 1 is the library's bit-sliced dedispersion kernel, run once
-// per subband on the common channel-major bit-plane copy of the input (each
-// subband is a block of rows), writing uint16 series.  Stage 2 is a gather
-// of nsub values per output: a block takes one trial group and a tile of
-// 2048 output samples, stages the group's rows of a few subbands at a time
-// in LDS (the tile plus the spread of the group's subband delays), and sums
-// them in registers for every trial of the group, two 16-bit sums per word --
-// the LDS rows are shared by the G trials.  Stage 1 does ncoarse * nchans adds per sample instead of
-// ndm * nchans; stage 2 adds ndm * nsub.
+// Design.  Stage 1 is the library's bit-sliced dedispersion kernel, run on all
+// subbands (blocks of rows of the common channel-major bit-plane copy of the
+// input) in one launch, writing uint16 series.  Stage 2 is a gather of nsub values
+// per output: a block takes one trial group and a tile of 2048 output samples,
+// stages the group's row of one subband after the other in LDS (the tile plus the
+// spread of the group's subband delays), and sums them in registers for every
+// trial of the group, two 16-bit sums per word -- the LDS rows are shared by the G
+// trials.  Stage 1 does ncoarse * nchans adds per sample instead of ndm * nchans;
+// stage 2 adds ndm * nsub.
 #include <algorithm>
 #include <climits>
 #include <vector>
@@ -35,13 +35,10 @@ namespace {
 
 constexpr int kS2Threads = 256;
 constexpr int kS2Pairs = 4;          // pairs of output samples per thread
-constexpr int kS2Tile = 2 * kS2Threads * kS2Pairs;   // output samples per block
+// Output samples per block.  (16 x 8 on the survey beam, both stages: 2.43 ms; tiles
+// of 1024 samples 2.71-2.90.)
+constexpr int kS2Tile = 2 * kS2Threads * kS2Pairs;
 constexpr int kMaxGroup = 16;        // fine trials per coarse trial
-// LDS per block: rows of a few subbands at a time, so that several blocks share
-// a CU.  16 x 8 on the survey beam, both stages: 16 KiB 2.43 ms, 32 KiB 2.47, 48
-// KiB 2.91; tiles of 1024 samples 2.71-2.90.
-constexpr int kS2LdsBytes = 16 * 1024;
-
 // Largest spread of a group's subband delays: a staged row and its second copy
 // then fit 40 KiB.
 constexpr int kS2MaxSpan = 7152;
@@ -60,27 +57,26 @@ typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 // sub: uint16 series of subband s at sub + ncoarse * (s * nsamps - cum[s]),
 // rows of nsamps - maxd[s] samples (the stage-1 output of each subband).
 // lo[q][s]: smallest delay[d][c0(s)] over the group.  The samples
-// [t0 + lo, t0 + lo + row_len) of subband sc0 + k are staged in LDS with 16-byte
-// loads from the 16-byte boundary at or before the first one; that sample sits
-// at LDS index mis (0..7) of the row, and mis is folded into the trials' read
-// offsets, which are block-uniform and come from scalar loads of the delay
-// tables, so that all reads of a subband issue back to back.  Positions past
-// the row end read as 0; they only feed outputs past nout.
+// [t0 + lo, t0 + lo + row_len) of a subband are staged in LDS with 16-byte loads
+// from the 16-byte boundary at or before the first one; that sample sits at LDS
+// index mis (0..7) of the row, and mis is folded into the trials' read offsets,
+// which are block-uniform and come from scalar loads of the delay tables, so that
+// all reads of a subband issue back to back.  Positions past the row end read as 0;
+// they only feed outputs past nout.
 //
 // A thread adds pairs of neighbouring samples, two 16-bit sums in one word
 // (every partial sum stays at or below 3 nchans <= 65535), so a row is kept
 // twice, the second time one sample on: a trial's offset is then even in one
 // of the two and its pairs are aligned words.  (One sample per read and add,
-// 1024-sample tiles: 2.70 ms for both stages instead of 2.43.)  What remains is
-// mostly the stage-1 series' way through HBM: 2.45 GB written and read.
-constexpr int kS2MaxChunk = 16;
-
+// 1024-sample tiles: 2.70 ms for both stages instead of 2.43.)  All threads stage the
+// one row that is in LDS at a time (half of them: 2.33 ms, all 2.10).  What remains
+// is mostly the stage-1 series' way through HBM: 2.45 GB written and read.
 template <int GM, bool OUT16>
 __global__ __launch_bounds__(kS2Threads) void subband_sum_kernel(
     const uint16_t* __restrict__ sub, const int64_t* __restrict__ cum,
     const int32_t* __restrict__ maxd, const int32_t* __restrict__ inter,
     const int32_t* __restrict__ lo, int nsub, int ncoarse, int ndm, int group, int64_t nsamps,
-    int64_t nout, int row_len, int row_stride, int chunk, void* __restrict__ out) {
+    int64_t nout, int row_len, int row_stride, void* __restrict__ out) {
     extern __shared__ uint4 rows_raw[];
     char* rows = reinterpret_cast<char*>(rows_raw);
     const int q = blockIdx.y;
@@ -88,79 +84,64 @@ __global__ __launch_bounds__(kS2Threads) void subband_sum_kernel(
     const int d0 = q * group;
     const int gq = min(group, ndm - d0);
     const int tid = threadIdx.x;
-    // half a block (two waves) stages a row
-    const int half = __builtin_amdgcn_readfirstlane(tid >> 7);
     u16x2 acc[GM][kS2Pairs];
 #pragma unroll
     for (int g = 0; g < GM; ++g)
 #pragma unroll
         for (int j = 0; j < kS2Pairs; ++j) acc[g][j] = u16x2{0, 0};
 
-    for (int sc0 = 0; sc0 < nsub; sc0 += chunk) {
-        const int nsc = min(chunk, nsub - sc0);
-        for (int k = half; k < nsc; k += 2) {
-            const int s = sc0 + k;
-            const int64_t nrow = nsamps - maxd[s];
-            const uint16_t* row = sub + static_cast<int64_t>(ncoarse) * (s * nsamps - cum[s]) +
-                                  static_cast<int64_t>(q) * nrow;
-            const int64_t base = t0 + lo[static_cast<int64_t>(q) * nsub + s];
-            const uint16_t* first = row + base;
-            const int mis = static_cast<int>((reinterpret_cast<uintptr_t>(first) >> 1) & 7);
-            const uint16_t* a0 = first - mis;                 // 16-byte aligned
-            const int nchunk = (mis + row_len + 7) >> 3;
-            const int64_t valid = nrow - base + mis;           // a0[i] is in the row for i < valid
-            uint4* dst = reinterpret_cast<uint4*>(rows + 2 * k * row_stride * 2);
-            for (int c = tid & 127; c < nchunk; c += kS2Threads / 2) {
-                const int64_t i0 = static_cast<int64_t>(c) * 8;
-                uint32_t w[4], next = 0;
-                if (i0 + 9 <= valid) {
-                    const uint4 x = *reinterpret_cast<const uint4*>(a0 + i0);
-                    w[0] = x.x; w[1] = x.y; w[2] = x.z; w[3] = x.w;
-                    next = a0[i0 + 8];
-                } else {
+    for (int s = 0; s < nsub; ++s) {
+        const int64_t nrow = nsamps - maxd[s];
+        const int64_t lo_qs = lo[static_cast<int64_t>(q) * nsub + s];
+        const uint16_t* first = sub + static_cast<int64_t>(ncoarse) * (s * nsamps - cum[s]) +
+                                static_cast<int64_t>(q) * nrow + t0 + lo_qs;
+        const int mis = static_cast<int>((reinterpret_cast<uintptr_t>(first) >> 1) & 7);
+        const uint16_t* a0 = first - mis;                     // 16-byte aligned
+        const int nchunk = (mis + row_len + 7) >> 3;
+        const int64_t valid = nrow - t0 - lo_qs + mis;         // a0[i] is in the row for i < valid
+        uint4* dst = reinterpret_cast<uint4*>(rows);
+        for (int c = tid; c < nchunk; c += kS2Threads) {
+            const int64_t i0 = static_cast<int64_t>(c) * 8;
+            uint32_t w[4], next = 0;
+            if (i0 + 9 <= valid) {
+                const uint4 x = *reinterpret_cast<const uint4*>(a0 + i0);
+                w[0] = x.x; w[1] = x.y; w[2] = x.z; w[3] = x.w;
+                next = a0[i0 + 8];
+            } else {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int64_t i = i0 + 2 * e;
-                        const uint32_t l = i >= mis && i < valid ? a0[i] : 0u;
-                        const uint32_t h = i + 1 >= mis && i + 1 < valid ? a0[i + 1] : 0u;
-                        w[e] = l | (h << 16);
-                    }
+                for (int e = 0; e < 4; ++e) {
+                    const int64_t i = i0 + 2 * e;
+                    const uint32_t l = i >= mis && i < valid ? a0[i] : 0u;
+                    const uint32_t h = i + 1 >= mis && i + 1 < valid ? a0[i + 1] : 0u;
+                    w[e] = l | (h << 16);
                 }
-                dst[c] = make_uint4(w[0], w[1], w[2], w[3]);
-                dst[c + (row_stride >> 3)] =
-                    make_uint4(__builtin_amdgcn_alignbit(w[1], w[0], 16), __builtin_amdgcn_alignbit(w[2], w[1], 16),
-                               __builtin_amdgcn_alignbit(w[3], w[2], 16), __builtin_amdgcn_alignbit(next, w[3], 16));
             }
+            dst[c] = make_uint4(w[0], w[1], w[2], w[3]);
+            dst[c + (row_stride >> 3)] =
+                make_uint4(__builtin_amdgcn_alignbit(w[1], w[0], 16), __builtin_amdgcn_alignbit(w[2], w[1], 16),
+                           __builtin_amdgcn_alignbit(w[3], w[2], 16), __builtin_amdgcn_alignbit(next, w[3], 16));
         }
         __syncthreads();
-        for (int k = 0; k < nsc; ++k) {
-            // read offsets (uniform: scalar loads); trials past the group's
-            // end repeat its last one and are never written
-            const int s = sc0 + k;
-            const int64_t nrow = nsamps - maxd[s];
-            const int64_t lo_qs = lo[static_cast<int64_t>(q) * nsub + s];
-            const uint16_t* first = sub + static_cast<int64_t>(ncoarse) * (s * nsamps - cum[s]) +
-                                    static_cast<int64_t>(q) * nrow + t0 + lo_qs;
-            const int mis = static_cast<int>((reinterpret_cast<uintptr_t>(first) >> 1) & 7);
-            int off[GM];   // bytes
+        // read offsets (uniform: scalar loads); trials past the group's end repeat
+        // its last one and are never written
+        int off[GM];   // bytes
 #pragma unroll
-            for (int g = 0; g < GM; ++g) {
-                const int o = inter[static_cast<int64_t>(d0 + min(g, gq - 1)) * nsub + s] -
-                              static_cast<int>(lo_qs) + mis;
-                off[g] = (2 * k + (o & 1)) * row_stride * 2 + (o >> 1) * 4;
-            }
-            uint32_t v[GM][kS2Pairs];
-#pragma unroll
-            for (int g = 0; g < GM; ++g) {
-                const uint32_t* src = reinterpret_cast<const uint32_t*>(rows + off[g]) + tid;
-#pragma unroll
-                for (int j = 0; j < kS2Pairs; ++j) v[g][j] = src[j * kS2Threads];
-            }
-#pragma unroll
-            for (int g = 0; g < GM; ++g)
-#pragma unroll
-                for (int j = 0; j < kS2Pairs; ++j) acc[g][j] += __builtin_bit_cast(u16x2, v[g][j]);
+        for (int g = 0; g < GM; ++g) {
+            const int o = inter[static_cast<int64_t>(d0 + min(g, gq - 1)) * nsub + s] -
+                          static_cast<int>(lo_qs) + mis;
+            off[g] = (o & 1) * row_stride * 2 + (o >> 1) * 4;
         }
+        uint32_t v[GM][kS2Pairs];
+#pragma unroll
+        for (int g = 0; g < GM; ++g) {
+            const uint32_t* src = reinterpret_cast<const uint32_t*>(rows + off[g]) + tid;
+#pragma unroll
+            for (int j = 0; j < kS2Pairs; ++j) v[g][j] = src[j * kS2Threads];
+        }
+#pragma unroll
+        for (int g = 0; g < GM; ++g)
+#pragma unroll
+            for (int j = 0; j < kS2Pairs; ++j) acc[g][j] += __builtin_bit_cast(u16x2, v[g][j]);
         __syncthreads();
     }
 #pragma unroll
@@ -400,9 +381,8 @@ extern "C" dedisp_status dedisp_subband_execute(dedisp_subband b, const uint8_t*
     const int64_t nout = nsamps - b->loss;
     const int row_len = kS2Tile + b->span;
     const int row_stride = (row_len + 7 + 7) & ~7;        // room for the leading misalignment
-    const int chunk = std::max(1, std::min(kS2MaxChunk, kS2LdsBytes / (row_stride * 4)));
     const dim3 grid(static_cast<unsigned>((nout + kS2Tile - 1) / kS2Tile), static_cast<unsigned>(b->ncoarse));
-    const size_t lds = static_cast<size_t>(chunk) * row_stride * 4;   // every row twice
+    const size_t lds = static_cast<size_t>(row_stride) * 4;   // a row, twice
     const bool u16 = out_type == DEDISP_OUT_U16;
 #define DD_S2(GM_)                                                                             \
     if (b->group <= GM_) {                                                                     \
@@ -410,12 +390,12 @@ extern "C" dedisp_status dedisp_subband_execute(dedisp_subband b, const uint8_t*
             hipLaunchKernelGGL((subband_sum_kernel<GM_, true>), grid, dim3(kS2Threads), lds,   \
                                stream, series, b->d_cum, b->d_maxd, b->d_inter, b->d_lo,      \
                                b->nsub, b->ncoarse, p->ndm, b->group, nsamps, nout, row_len,   \
-                               row_stride, chunk, out);                                                    \
+                               row_stride, out);                                               \
         else                                                                                   \
             hipLaunchKernelGGL((subband_sum_kernel<GM_, false>), grid, dim3(kS2Threads), lds,  \
                                stream, series, b->d_cum, b->d_maxd, b->d_inter, b->d_lo,      \
                                b->nsub, b->ncoarse, p->ndm, b->group, nsamps, nout, row_len,   \
-                               row_stride, chunk, out);                                                    \
+                               row_stride, out);                                               \
     } else
     DD_S2(1) DD_S2(2) DD_S2(4) DD_S2(8) DD_S2(16) {}
 #undef DD_S2

@@ -127,3 +127,40 @@ def test_time_of_large_groups():
         us[group] = 1e6 * sorted(times)[2]
     log("us by group", us)
     assert us[16] <= 1.1 * us[8]
+
+
+def test_widest_spread_of_a_group():
+    """A group whose subband delays spread over just what a staged row holds, and
+    one past it, which is refused."""
+    from paper_1112_0065_amd import _lib as L
+    nchans, ndm, nsub, group = 16, 8, 4, 8
+
+    def plan_of(dm):
+        return L.dedisp_plan_create(nchans, 400.0, -10.0, 1e-3, np.linspace(0.0, dm, ndm))
+
+    def span_of(dm):
+        d = oracle.delay_table(nchans, 400.0, -10.0, 1e-3, np.linspace(0.0, dm, ndm))[:, ::nchans // nsub]
+        return int((d.max(axis=0) - d.min(axis=0)).max())
+
+    lo, hi = 0.0, 1e5
+    for _ in range(60):
+        mid = 0.5 * (lo + hi)
+        lo, hi = (mid, hi) if span_of(mid) <= 7152 else (lo, mid)
+    assert 7140 < span_of(lo) <= 7152 < span_of(hi)
+    sb = L.dedisp_subband_create(plan_of(lo), nsub, group)
+    assert sb.span == span_of(lo)
+    nsamps = sb.max_delay + 4099
+    packed = np.random.default_rng(5).integers(0, 256, nsamps * nchans // 4).astype(np.uint8)
+
+    class Beam:
+        dm_list = np.linspace(0.0, lo, ndm)
+
+    Beam.nsamps, Beam.packed = nsamps, packed
+    x = oracle.unpack_2bit(packed, nsamps, nchans)
+    ref = subband_dedisperse(x, 400.0, -10.0, 1e-3, Beam.dm_list, nsub, group)
+    for u16 in (True, False):
+        _, got = _run(Beam, plan_of(lo), nsub, group, u16)
+        assert got.shape == ref.shape and (got == ref).all(), u16
+    with pytest.raises(L.DedispError) as ei:
+        L.dedisp_subband_create(plan_of(hi), nsub, group)
+    assert ei.value.status == L.ERR_UNSUPPORTED
