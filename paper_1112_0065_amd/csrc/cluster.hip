@@ -20,8 +20,9 @@
 // search on t_end.  A table of series starts comes from one pass over the
 // list.  Components are built by lock-free union-find on a parent array: a
 // root is only ever hooked under a smaller node (an atomic minimum while all
-// are roots, one compare-and-swap later), and finds halve paths with plain word stores that only ever point a node at one
-// of its ancestors.  Every node's parent is therefore smaller than the node,
+// are roots, one compare-and-swap later), and finds halve
+// paths with plain word stores that only ever point a node at one of its
+// ancestors.  Every node's parent is therefore smaller than the node,
 // and each finished component's root is its lowest member whatever order the
 // threads ran in -- the result is deterministic.  Member counts, index and
 // time bounds and the representative (the largest (snr, -index) key) are
@@ -104,13 +105,17 @@ __device__ void unite(int32_t* parent, int32_t a, int32_t b) {
 
 // Joins two nodes last seen as roots: the larger, if it still is one, goes
 // under the smaller whatever became of that (a root is the least node of its
-// tree, so a smaller node is not in it); one atomic and no load.
+// tree, so a smaller node is not in it): one load and one atomic, where a union
+// looks for both roots first.  Where many events join a few clusters most see
+// an old root; the load sends those to the union, which halves the paths (the
+// atomic alone: 100000 events in a few clusters, radii 8 and 2, 892 us, so 236).
 __device__ void unite_seen(int32_t* parent, int32_t a, int32_t b) {
     const int32_t lo = min(a, b), hi = max(a, b);
-    int32_t seen = hi;
-    if (!__hip_atomic_compare_exchange_strong(parent + hi, &seen, lo, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                              __HIP_MEMORY_SCOPE_AGENT) && seen != lo)
-        unite(parent, seen, lo);
+    int32_t seen = atomic_ld(parent + hi);
+    if (seen == hi && __hip_atomic_compare_exchange_strong(parent + hi, &seen, lo, __ATOMIC_RELAXED,
+                                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        return;
+    if (seen != lo) unite(parent, seen, lo);
 }
 
 __device__ __forceinline__ bool event_ok(const dedisp_event& e, const ClusterParams& P) {
@@ -223,12 +228,25 @@ __device__ __forceinline__ void neighbours(const ClusterParams& P, const int32_t
 // node whatever the input), and the trees are flattened.  Most pairs of
 // friends then share a root, which two cached loads show, and only what joins
 // two of these trees is left to the compare-and-swap of the union, whose chains
-// of coherent loads made the pass over the survey's 26669 events 70 us.  With
-// many events the unions hide one another's latency and the second walk over
-// the friends costs more than it saves: whole stage, us, without and with it,
-// 26669 events 119 and 99, 100000 157 and 133, 200000 168 and 177, 400000 273
-// and 290.
-constexpr int64_t kHookEvents = 131072;
+// of coherent loads made the pass over the survey's 26669 events 70 us.
+//
+// The second walk over the friends costs S = upper_series searches per event.
+// Whole stage, us, without and with it, separate clusters and a few large ones:
+//     2500 events, S = 8       91   95        91   94
+//    26669         8          145  111       147  113
+//    26669       228          214  204       241  227
+//    26669      5710         1288 1894      1783 2195   (with another union)
+//   100000         8          142  133       272  199
+//   100000        43          200  200       244  236
+//   100000       228          722  571       988  706
+//   200000         8          183  180       348  260
+//   200000        23          227  253       293  352
+//   400000         1          245  220       381  218
+//   400000         8          282  293       323  332
+//   400000        23          414  473       477  551
+bool hook_first(int64_t n, int S) {
+    return n >= 4096 && (n <= 131072 ? S <= 512 : n * S <= (int64_t(1) << 21));
+}
 
 __global__ __launch_bounds__(kKThreads) void cluster_hook_kernel(ClusterParams P,
                                                                  const int32_t* __restrict__ seg,
@@ -525,7 +543,7 @@ hipError_t launch_cluster(const dedisp_event* ev, int64_t n, int32_t ndm, const 
     hipLaunchKernelGGL(cluster_init_kernel, dim3(1), dim3(1), 0, s, err);
     hipLaunchKernelGGL(cluster_seg_kernel, g_n1, blk, 0, s, P, seg, parent, err);
     const int S = upper_series(dm_radius, width_radius);
-    if (n <= kHookEvents) {
+    if (hook_first(n, S)) {
         const dim3 g_pair(g_n.x, static_cast<unsigned>(std::min(S, 65535)));
         hipLaunchKernelGGL(cluster_hook_kernel, g_pair, blk, 0, s, P, seg, parent);
         hipLaunchKernelGGL(cluster_flatten_kernel, g_n, blk, 0, s, n, parent);

@@ -205,3 +205,63 @@ def test_bad_input_is_rejected():
     # the library still works afterwards
     nc, _, _ = _run(ev, 100, widths, 1, 1, 0)
     assert nc == len(oracle.cluster_events(ev, widths, 1, 1, 0)[1])
+
+
+@pytest.mark.parametrize("n,radius", [(4095, 5), (4098, 5), (4098, 511), (4098, 512), (131070, 511),
+                                      (131070, 512), (131073, 14), (131073, 15), (262143, 7), (262146, 7)])
+def test_passes_on_both_sides_of_their_lines(n, radius):
+    """n events, one third in each of trials 0, 1 and 5 at the same times, and radii
+    that reach all three: around the numbers of events and of neighbour series (one
+    more than the radius) that decide whether the trees are hooked first."""
+    m = n // 3
+    ev = np.zeros(n, dtype=synth.make_event_list(1, 8, 1, 1000, nclumps=1, nnoise=1).dtype)
+    t = np.tile(np.arange(m, dtype=np.int64) * 10, 3)
+    ev["t_start"], ev["t_end"], ev["t_peak"] = t, t + 3, t + 1
+    ev["dm_idx"] = np.repeat([0, 1, 5], m)
+    ev["snr"] = np.repeat([7.0, 9.0, 8.0], m)
+    nc, lab, got = _run(ev, 8, [1], radius, 0, 0)
+    own = np.arange(m)
+    assert nc == m and (lab == np.tile(own, 3)).all()
+    assert (got["first"] == own).all() and (got["rep"] == m + own).all()
+    assert (got["n_members"] == 3).all()
+
+
+def test_time_of_a_few_large_clusters():
+    """Events that all join a few clusters cost what their friends do: 100000 events
+    of pulses crowded into 1/44 of the time (the same searches, several times the
+    friends) take at most two and a half times the spread ones."""
+    import time
+    from paper_1112_0065_amd import _lib as L
+    torch = torch_dev()
+    n, ndm, widths = 100000, 1200, [1 << i for i in range(10)]
+    us = {}
+    for name, span in (("spread", 1 << 19), ("crowded", 12000)):
+        # pulses of 360 events around a trial and a time, and a tenth of lone events
+        r = np.random.default_rng(9)
+        npulse = n // 400
+        own = r.integers(npulse, size=n - n // 10)
+        d0, t0, reach = r.integers(ndm, size=npulse), r.integers(span - 4096, size=npulse), r.integers(3, 60, size=npulse)
+        dm = np.concatenate([np.clip(d0[own] + np.round(r.normal(size=own.size) * reach[own] / 2).astype(int), 0, ndm - 1),
+                             r.integers(ndm, size=n // 10)])
+        t = np.concatenate([t0[own] + r.integers(0, 400, size=own.size), r.integers(span - 4096, size=n // 10)])
+        # one event of one sample per width, trial and time
+        slot = np.unique((r.integers(10, size=n) * ndm + dm) * span + t)
+        ev = np.zeros(len(slot), dtype=L.EVENT_DTYPE)
+        k, t = slot // span, slot % span
+        ev["width_idx"], ev["dm_idx"] = k // ndm, k % ndm
+        ev["t_start"], ev["t_end"], ev["t_peak"] = t, t, t
+        ev["snr"], ev["b_peak"] = 6.0 + r.random(len(slot)), 2000
+        evd = to_dev(ev.view(np.uint8).copy())
+        ws = torch.empty(L.dedisp_cluster_workspace_bytes(len(ev), ndm, 10), dtype=torch.uint8, device="cuda")
+        cb = torch.empty(len(ev) * 72, dtype=torch.uint8, device="cuda")
+        lab = torch.empty(len(ev), dtype=torch.int32, device="cuda")
+        times = []
+        for _ in range(9):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(5):
+                nc = L.dedisp_cluster_events(evd, len(ev), ndm, widths, 8, 2, 0, cb, len(ev), ws, lab)
+            times.append((time.perf_counter() - t0) / 5)
+        us[name] = 1e6 * sorted(times)[4]
+        log(name, len(ev), "events", nc, "clusters", us[name], "us")
+    assert us["crowded"] <= 2.5 * us["spread"]
