@@ -389,8 +389,8 @@ __device__ __forceinline__ void store_tile(const uint32_t (&r)[16], void* out, i
 // One work item: DM block `dblk` x time tile `tile` of one beam.
 //
 // The LDS holds two stage buffers of `stage_chans` rows each; stage s lives in
-// buffer s & 1, so channel c sits in row c mod (2 * stage_chans) -- the row
-// the offset table assumes.  While the waves work on stage s, the copy of
+// buffer s & 1, channel c in row c mod stage_chans of it -- the row the offset
+// table assumes.  While the waves work on stage s, the copy of
 // stage s + 1 into the other buffer is in flight.  With DEEP (S8 only) a
 // buffer holds `nsub` stages of 8 channels, copied and published together:
 // stage q of the buffer takes rows 8 q .. 8 q + 7.

@@ -360,8 +360,8 @@ extern "C" dedisp_status dedisp_subband_execute(dedisp_subband b, const uint8_t*
     uint2* words = static_cast<uint2*>(workspace);
     uint16_t* series = reinterpret_cast<uint16_t*>(static_cast<char*>(workspace) + words_bytes(b, nsamps));
     DD_HIP(dd::launch_repack(in, nsamps, p->nchans, words, nwords, stream));
-    // Runs of subbands with the same tile shape (the tuner gives all the same;
-    // a tune cache may not) go in one launch.
+    // Runs of subbands with the same tile shape go in one launch (a subband that the
+    // tuned shape's LDS tile does not fit keeps its own).
     dd::ManyItem items[dd::kMaxMany];
     int n_items = 0;
     for (int s = 0; s < b->nsub; ++s) {

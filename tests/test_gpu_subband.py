@@ -164,3 +164,23 @@ def test_widest_spread_of_a_group():
     with pytest.raises(L.DedispError) as ei:
         L.dedisp_subband_create(plan_of(hi), nsub, group)
     assert ei.value.status == L.ERR_UNSUPPORTED
+
+
+def test_first_stage_that_fits_no_lds_tile_is_refused():
+    """Coarse trials so far apart that not even blocks of 4 of them fit a block's LDS:
+    the two-stage plan is made, its execution refused, and the library works on."""
+    from paper_1112_0065_amd import _lib as L
+    torch = torch_dev()
+    nchans, ndm = 16, 8
+    plan = L.dedisp_plan_create(nchans, 400.0, -10.0, 1e-3, np.linspace(0.0, 7000.0, ndm))
+    sb = L.dedisp_subband_create(plan, 2, 1)
+    nsamps = sb.max_delay + 100
+    x = torch.zeros(nsamps * nchans // 4, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(L.dedisp_subband_workspace_bytes(sb, nsamps), dtype=torch.uint8, device="cuda")
+    out = torch.empty((ndm, 100), dtype=torch.int16, device="cuda")
+    with pytest.raises(L.DedispError) as ei:
+        L.dedisp_subband_execute(sb, x, nsamps, out, ws)
+    assert ei.value.status == L.ERR_UNSUPPORTED
+    fb, _, _, direct = small_case()
+    _, got = _run(fb, L.dedisp_plan_create(fb.nchans, fb.f_top, fb.df, fb.tsamp, fb.dm_list), 1, 1)
+    assert (got == direct).all()
