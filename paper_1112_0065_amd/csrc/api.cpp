@@ -278,7 +278,7 @@ dedisp_status find_peaks_impl(const void* in, dedisp_out_type in_type, int32_t n
     // the write pass works through a list on the device (none: its blocks end
     // at once), so it needs no count on the host and one wait serves both
     if (capacity > 0)
-        DD_HIP(dd::launch_peaks_write(in, u16, ndm, nout, W, lay, ws, events, capacity, stream));
+        DD_HIP(dd::launch_peaks_write(in, u16, ndm, nout, W, lay, ws, events, capacity, kmant, kexp2, stream));
     int64_t total = 0;
     DD_HIP(hipMemcpyAsync(&total, ws.total, sizeof total, hipMemcpyDeviceToHost, stream));
     DD_HIP(hipStreamSynchronize(stream));

@@ -99,7 +99,8 @@ hipError_t launch_multi(const MultiItem* items, int n, const Widths& W, uint32_t
         const PeaksWs ws = peaks_ws(it.pk_ws, lay);
         e = launch_peaks_count(series, out_u16, p->ndm, nout, W, lay, ws, kmant, kexp2, s);
         if (e == hipSuccess && it.capacity > 0)
-            e = launch_peaks_write(series, out_u16, p->ndm, nout, W, lay, ws, it.events, it.capacity, s);
+            e = launch_peaks_write(series, out_u16, p->ndm, nout, W, lay, ws, it.events, it.capacity, kmant, kexp2,
+                                   s);
         if (e == hipSuccess)
             e = hipMemcpyAsync(it.h_total, ws.total, sizeof(int64_t), hipMemcpyDeviceToHost, s);
     }

@@ -32,7 +32,7 @@
 namespace {
 
 constexpr int kThreads = 256;
-// Threads per block of the list-driven count and write passes (see launch_list).
+// Threads per block of the list-driven count and write passes (see list_threads).
 constexpr int kFewThreads = 1024, kMidThreads = 512;
 // ----------------------------------------------------------------------------
 // Block-level helpers.
@@ -1877,21 +1877,29 @@ int segment_length(int w_max) {
 // the device knows: a few per cent of the (DM, segment)s in a clean search, most of
 // them at a low cut or with interference.  Larger blocks finish a listed segment
 // sooner, smaller ones keep more of them in flight (a block of 1024 write threads
-// fills a CU).  So the number of all segments decides, with both ends measured; us
-// for count + write with 1024, 512 and 256 threads, clean and all listed:
+// fills a CU).  So the number of all segments decides, and of those that noise alone
+// lists; us for count + write with 1024, 512 and 256 threads, clean and all listed:
 //      108 segments    48   65  105       52   68  113
 //      800             44   54   86       98   87  118
 //     1960            101   83  110      210  158  190
 //     3913             75   69  110      312  253  246
 //    12400            216  155  176      969  754  722
-// (1960: more pulses than in the others' clean series.)  Up to 2560 what the largest
-// blocks lose at worst is less than the rest of the search has gained, and a clean
-// search gains (1200 series of 9500 samples, 2400 segments: 100 us, 111 with 512).
-// A list of a handful of segments takes 12 us more with 512 than with 1024 (a beam of
-// 16 800 segments and 95 events: 50 and 38 us).
-// Beyond 32768 the larger blocks would only lose (the survey series, 74 400: 192
-// us with 256 threads, 247 with 1024).
-constexpr int64_t kFewSegments = 2560, kMidSegments = 32768;
+// (1960: more pulses than in the others' clean series.)  Up to 4096 what the largest
+// blocks lose with interference is less than the rest of the search has gained, and a
+// list of fewer segments than CUs, 12 us shorter with them (16 800 segments with 95
+// events: 38 and 50 us), is common and the call short.  Where noise lists more than
+// 512 (S/N cuts below 4.7 at 4096 segments of 10 widths) they lose outright (64 x
+// 500000 at 4 sigma: find_peaks 464 us, 352 with 512 threads).  Beyond 32768 the
+// larger blocks only lose (the survey series, 74 400: 192 us with 256 threads, 247
+// with 1024).
+constexpr int64_t kFewSegments = 4096, kMidSegments = 32768;
+constexpr double kFewNoise = 512;
+int list_threads(int64_t segments, int L, int nw, uint32_t kmant, int kexp2) {
+    if (segments > kMidSegments) return kThreads;
+    const double k = std::ldexp(static_cast<double>(kmant), kexp2);
+    const double noise = segments * std::min(1.0, 0.5 * std::erfc(k * M_SQRT1_2) * L * nw);
+    return segments <= kFewSegments && noise <= kFewNoise ? kFewThreads : kMidThreads;
+}
 // Waves of the list-driven passes' blocks: 32 per CU.
 constexpr int64_t kListWaves = 8192;
 
@@ -2129,12 +2137,12 @@ void launch_count_nt(const T* in, int ndm, int64_t nout, const Widths& W, const 
                        ndm, nout, lay.nbx, W, lay.L, lay.nseg, ws);
 }
 
-// launch(block size) of a list-driven pass.
+// launch(block size) of a list-driven pass (see list_threads).
 template <typename F>
-void launch_list(int64_t segments, F launch) {
-    if (segments <= kFewSegments)
+void launch_list(int threads, F launch) {
+    if (threads == kFewThreads)
         launch(std::integral_constant<int, kFewThreads>{});
-    else if (segments <= kMidSegments)
+    else if (threads == kMidThreads)
         launch(std::integral_constant<int, kMidThreads>{});
     else
         launch(std::integral_constant<int, kThreads>{});
@@ -2142,8 +2150,8 @@ void launch_list(int64_t segments, F launch) {
 
 template <typename T>
 void launch_count(const T* in, int ndm, int64_t nout, const Widths& W, const PeaksLayout& lay,
-                  const PeaksWs& ws, size_t lds, hipStream_t s) {
-    launch_list(static_cast<int64_t>(ndm) * lay.nseg, [&](auto nt) {
+                  const PeaksWs& ws, size_t lds, int threads, hipStream_t s) {
+    launch_list(threads, [&](auto nt) {
         launch_count_nt<T, decltype(nt)::value>(in, ndm, nout, W, lay, ws, lds, s);
     });
 }
@@ -2159,8 +2167,9 @@ void launch_write_nt(const T* in, int ndm, int64_t nout, const Widths& W, const 
 
 template <typename T>
 void launch_write(const T* in, int ndm, int64_t nout, const Widths& W, const PeaksLayout& lay,
-                  const PeaksWs& ws, dedisp_event* events, int64_t capacity, size_t lds, hipStream_t s) {
-    launch_list(static_cast<int64_t>(ndm) * lay.nseg, [&](auto nt) {
+                  const PeaksWs& ws, dedisp_event* events, int64_t capacity, size_t lds, int threads,
+                  hipStream_t s) {
+    launch_list(threads, [&](auto nt) {
         launch_write_nt<T, decltype(nt)::value>(in, ndm, nout, W, lay, ws, events, capacity, lds, s);
     });
 }
@@ -2181,10 +2190,11 @@ hipError_t launch_peaks_count(const void* in, int in_u16, int ndm, int64_t nout,
     const int64_t nblk = static_cast<int64_t>(ndm) * lay.nseg;
     hipLaunchKernelGGL(mark_kernel, dim3(static_cast<unsigned>((nblk + kThreads - 1) / kThreads)),
                        dim3(kThreads), 0, s, ndm, lay.nseg, W.n, ws);
+    const int threads = list_threads(nblk, lay.L, W.n, kmant, kexp2);
     if (in_u16)
-        launch_count(static_cast<const uint16_t*>(in), ndm, nout, W, lay, ws, lds, s);
+        launch_count(static_cast<const uint16_t*>(in), ndm, nout, W, lay, ws, lds, threads, s);
     else
-        launch_count(static_cast<const int32_t*>(in), ndm, nout, W, lay, ws, lds, s);
+        launch_count(static_cast<const int32_t*>(in), ndm, nout, W, lay, ws, lds, threads, s);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (ws.offs) return launch_scan_u32(ws.counts, lay.ncounts, ws.offs, ws.chunk_tot, ws.total, s);
@@ -2197,13 +2207,14 @@ hipError_t launch_peaks_count(const void* in, int in_u16, int ndm, int64_t nout,
 
 hipError_t launch_peaks_write(const void* in, int in_u16, int ndm, int64_t nout, const Widths& W,
                               const PeaksLayout& lay, const PeaksWs& ws, dedisp_event* events,
-                              int64_t capacity, hipStream_t s) {
+                              int64_t capacity, uint32_t kmant, int kexp2, hipStream_t s) {
     const int w_max = W.w[W.n - 1];
     const size_t lds = peaks_lds_bytes(lay.L, w_max);
+    const int threads = list_threads(static_cast<int64_t>(ndm) * lay.nseg, lay.L, W.n, kmant, kexp2);
     if (in_u16)
-        launch_write(static_cast<const uint16_t*>(in), ndm, nout, W, lay, ws, events, capacity, lds, s);
+        launch_write(static_cast<const uint16_t*>(in), ndm, nout, W, lay, ws, events, capacity, lds, threads, s);
     else
-        launch_write(static_cast<const int32_t*>(in), ndm, nout, W, lay, ws, events, capacity, lds, s);
+        launch_write(static_cast<const int32_t*>(in), ndm, nout, W, lay, ws, events, capacity, lds, threads, s);
     return hipGetLastError();
 }
 

@@ -78,7 +78,7 @@ hipError_t launch_peaks_count(const void* in, int in_u16, int ndm, int64_t nout,
                               hipStream_t s);
 hipError_t launch_peaks_write(const void* in, int in_u16, int ndm, int64_t nout, const Widths& W,
                               const PeaksLayout& lay, const PeaksWs& ws, dedisp_event* events,
-                              int64_t capacity, hipStream_t s);
+                              int64_t capacity, uint32_t kmant, int kexp2, hipStream_t s);
 
 // Shared by the batch and the streaming server: see batch.cpp.  Items with a
 // mask read flagged samples as the mean level; items with a `flat` buffer get

@@ -529,11 +529,16 @@ def test_time_of_a_long_series_is_linear():
     assert cost[28] <= 1.5 * cost[25]
 
 
-@pytest.mark.parametrize("ndm,nout", [(60, 8192 + 303), (2560, 90), (2561, 90), (1290, 8192 + 303), (32768, 40), (32769, 40)])
-def test_list_passes_with_every_block_size(ndm, nout):
+@pytest.mark.parametrize("ndm,nout,k", [
+    (60, 8192 + 303, 1.2), (4096, 90, 5.0),                           # the largest blocks
+    (4097, 90, 5.0), (1290, 8192 + 303, 1.2), (32768, 40, 1.2),       # the middle ones: by number or by cut
+    (32769, 40, 1.2),                                                 # the smallest
+])
+def test_list_passes_with_every_block_size(ndm, nout, k):
     """The count and write passes on both sides of the lines between their block
-    sizes (2560 and 32768 segments in all): every series listed, one with more runs
-    in a segment than the passes list at once, equal to the oracle's."""
+    sizes (4096 and 32768 segments in all, a cut that noise passes): every series
+    listed, one with more runs in a segment than the passes list at once, equal to the
+    oracle's."""
     rng = np.random.default_rng(ndm)
     widths = [1, 2]
     series = rng.integers(0, 4, size=(ndm, nout)).astype(np.int64)
@@ -542,10 +547,10 @@ def test_list_passes_with_every_block_size(ndm, nout):
     if nout > 8192:
         series[:, 100:] = 0           # (few runs elsewhere)
         series[3, ::3] += 60          # 2832 runs, 2731 of them in the first segment
-    ref = oracle.find_events(oracle.boxcar(series, widths), 1.2)
+    ref = oracle.find_events(oracle.boxcar(series, widths), k)
     assert len(ref) > ndm
     for u16 in (True, False):
-        ev, _ = _find(series, widths, 1.2, u16, capacity=1 << 20)
+        ev, _ = _find(series, widths, k, u16, capacity=1 << 20)
         events_equal(ev, ref)
 
 
