@@ -40,7 +40,10 @@ __device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float(stati
 // 256 KiB a row, from the last-level cache where candidates overlap).  A
 // thread per column read 2 bytes per load at a stride of 2 w bytes: 1957 us
 // for 217 candidates at widths 1..512, 0.4 TB/s.  Groups of lanes that share a
-// column and read it in consecutive 16-byte pieces take 112 us (6.5 TB/s).
+// column and read it in consecutive 16-byte pieces take 112 us (6.5 TB/s).  Widths
+// that are no multiple of 8 read pieces as well (300 tiles at width 9: a thread per
+// column 35 us, groups that read single samples 64, pieces KK9; width 33: 332, 346,
+// KK33); below 8 a thread per column is left.
 // ---------------------------------------------------------------------------
 
 // Eight consecutive samples at any (2-byte aligned) address.
@@ -49,23 +52,28 @@ struct __attribute__((packed, aligned(2))) Piece {
 };
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
-__device__ __forceinline__ uint32_t piece_sum(const Piece& p) {
+// Sum of a piece's samples from `skip` (0 .. 7; a multiple of 8 if not RAGGED) on.
+template <bool RAGGED>
+__device__ __forceinline__ uint32_t piece_sum(const Piece& p, int skip) {
     const u16x2 one = {1, 1};
     uint32_t s = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-        s = __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, p.w[i]), one, s, false);
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t keep = !RAGGED || skip <= 2 * i ? 0xFFFFFFFFu : skip == 2 * i + 1 ? 0xFFFF0000u : 0u;
+        s = __builtin_amdgcn_udot2(__builtin_bit_cast(u16x2, p.w[i] & keep), one, s, false);
+    }
     return s;
 }
 
-// Sums of the wave's 64 adjacent windows of w samples from `row` on, window
+// Sums of the wave's 64 adjacent windows of w >= 8 samples from `row` on, window
 // l in lane l; the first `ncol` (>= 1) windows lie inside the series, the
-// others repeat the last one.  WIDE: w is a multiple of 8 and a window is read
-// in 16-byte pieces, else in single samples.  G = 2^LG lanes, enough for the
+// others repeat the last one.  A window is read in 16-byte pieces; RAGGED (w not a
+// multiple of 8): the last one is read so that it ends with the window, and what it
+// shares with the one before does not count.  G = 2^LG lanes, enough for the
 // pieces or 64, share a window, so 64 / G windows are read at a time; up to 8
 // such rounds are in flight at once.  Lanes without a piece read a valid one
 // and count 0, so the loads carry no branch.
-template <bool WIDE, int LG>
+template <bool RAGGED, int LG>
 __device__ __forceinline__ uint32_t window_sums(const uint16_t* __restrict__ row, int w, int pieces,
                                                 int ncol, int lane) {
     constexpr int G = 1 << LG, C = 64 >> LG;
@@ -79,11 +87,12 @@ __device__ __forceinline__ uint32_t window_sums(const uint16_t* __restrict__ row
         for (int q0 = 0; q0 < pieces; q0 += G) {
             const bool has = q0 + p < pieces;
             const int q = has ? q0 + p : 0;
+            const int at = RAGGED ? min(8 * q, w - 8) : 8 * q;
             uint32_t x[kRounds];
 #pragma unroll
             for (int k = 0; k < kRounds; ++k) {
                 const uint16_t* src = row + static_cast<int64_t>(min((it0 + k) * C + c, ncol - 1)) * w;
-                x[k] = WIDE ? piece_sum(*reinterpret_cast<const Piece*>(src + 8 * q)) : src[q];
+                x[k] = piece_sum<RAGGED>(*reinterpret_cast<const Piece*>(src + at), 8 * q - at);
             }
 #pragma unroll
             for (int k = 0; k < kRounds; ++k) s[k] += has ? x[k] : 0u;
@@ -101,16 +110,24 @@ __device__ __forceinline__ uint32_t window_sums(const uint16_t* __restrict__ row
     return mine;
 }
 
-template <bool WIDE>
+template <bool RAGGED>
 __device__ __forceinline__ uint32_t window_sums_w(const uint16_t* __restrict__ row, int w, int ncol, int lane) {
-    const int pieces = WIDE ? w >> 3 : w;
-    if (pieces > 32) return window_sums<WIDE, 6>(row, w, pieces, ncol, lane);
-    if (pieces > 16) return window_sums<WIDE, 5>(row, w, pieces, ncol, lane);
-    if (pieces > 8) return window_sums<WIDE, 4>(row, w, pieces, ncol, lane);
-    if (pieces > 4) return window_sums<WIDE, 3>(row, w, pieces, ncol, lane);
-    if (pieces > 2) return window_sums<WIDE, 2>(row, w, pieces, ncol, lane);
-    if (pieces > 1) return window_sums<WIDE, 1>(row, w, pieces, ncol, lane);
-    return window_sums<WIDE, 0>(row, w, pieces, ncol, lane);
+    const int pieces = (w + 7) >> 3;
+    if (pieces > 32) return window_sums<RAGGED, 6>(row, w, pieces, ncol, lane);
+    if (pieces > 16) return window_sums<RAGGED, 5>(row, w, pieces, ncol, lane);
+    if (pieces > 8) return window_sums<RAGGED, 4>(row, w, pieces, ncol, lane);
+    if (pieces > 4) return window_sums<RAGGED, 3>(row, w, pieces, ncol, lane);
+    if (pieces > 2) return window_sums<RAGGED, 2>(row, w, pieces, ncol, lane);
+    if (RAGGED || pieces > 1) return window_sums<RAGGED, 1>(row, w, pieces, ncol, lane);
+    return window_sums<RAGGED, 0>(row, w, pieces, ncol, lane);
+}
+
+// Windows of fewer than 8 samples: one lane each, neighbouring ones.
+__device__ __forceinline__ uint32_t window_sums_short(const uint16_t* __restrict__ row, int w, int ncol, int lane) {
+    const uint16_t* src = row + min(lane, ncol - 1) * w;
+    uint32_t s = 0;
+    for (int k = 0; k < w; ++k) s += src[k];
+    return s;
 }
 
 __global__ __launch_bounds__(256) void tiles_kernel(const uint16_t* __restrict__ series, int ndm,
@@ -135,14 +152,15 @@ __global__ __launch_bounds__(256) void tiles_kernel(const uint16_t* __restrict__
     // the wave's columns: t = tw + w l; those below nbx are inside the series
     // with their whole window
     const int64_t tw = t0 + static_cast<int64_t>(j0) * w;
-    const int ncol = static_cast<int>(min<int64_t>(64, max<int64_t>(0, (nbx - tw + w - 1) / w)));
+    const int ncol = __popcll(__ballot(tw + static_cast<int64_t>(lane) * w < nbx));
     if (d < ndm && ncol > 0) {
         const int sidx = ev.width_idx * ndm + d;
         const double sq = sqrt_d[sidx];
         if (sq > 0.0) {
             const uint16_t* row = series + static_cast<int64_t>(d) * nout + tw;
-            const uint32_t b = (w & 7) == 0 ? window_sums_w<true>(row, w, ncol, lane)
-                                            : window_sums_w<false>(row, w, ncol, lane);
+            const uint32_t b = w < 8          ? window_sums_short(row, w, ncol, lane)
+                               : (w & 7) == 0 ? window_sums_w<false>(row, w, ncol, lane)
+                                              : window_sums_w<true>(row, w, ncol, lane);
             const int64_t lval = nbx * static_cast<int64_t>(b) - static_cast<int64_t>(s1[sidx]);
             if (lane < ncol) v = static_cast<float>(static_cast<double>(lval) / sq);
         }

@@ -349,3 +349,58 @@ def test_relu_of_nan_is_zero(bad):
     for k in ORDER:
         if np.isfinite(ref[k]).all():
             assert np.linalg.norm(gg[k] - ref[k]) <= 2e-2 * (np.linalg.norm(ref[k]) + 1e-12), k
+
+
+def test_tiles_widths_that_are_no_whole_pieces():
+    """Windows whose last 16-byte piece overlaps the one before, for every group of
+    lanes, and those shorter than a piece: equal to the oracle's tiles bit for bit, and
+    the time of a width just past a whole number of pieces near that of the next."""
+    import time
+    from paper_1112_0065_amd import _lib as L
+    torch = torch_dev()
+    widths = [4, 7, 9, 15, 17, 23, 33, 63, 65, 127, 129, 255, 257, 511, 999]
+    ndm, nout = 66, 30011
+    rng = np.random.default_rng(12)
+    out = rng.integers(0, 65536, size=(ndm, nout)).astype(np.int64)
+    out[3:6] = 65535
+    nbx = nout - widths[-1] + 1
+    series = to_dev(out.astype(np.uint16).view(np.int16))
+    pws = torch.empty(L.find_peaks_workspace_bytes(ndm, nout, widths), dtype=torch.uint8, device="cuda")
+    evb = torch.empty(40 << 16, dtype=torch.uint8, device="cuda")
+    L.find_peaks(series, ndm, nout, widths, 9.0, evb, 1 << 16, pws)
+    ev = np.zeros(3 * len(widths), dtype=L.EVENT_DTYPE)
+    ev["width_idx"] = np.arange(len(ev)) % len(widths)
+    ev["dm_idx"] = rng.integers(0, ndm, size=len(ev))
+    ev["t_peak"] = np.concatenate([np.zeros(len(widths)), np.full(len(widths), nbx - 1),
+                                   rng.integers(0, nbx, size=len(widths))])
+    tiles = torch.empty((len(ev), 64, 256), dtype=torch.int16, device="cuda")
+    L.triage_tiles(series, ndm, nout, widths, pws, to_dev(ev.view(np.uint8).copy()), len(ev), tiles)
+    got = cnn.bf16_value(tiles.cpu().numpy().view(np.uint16))
+    bw = oracle.boxcar(out, widths)
+    stats = [[oracle.series_stats(bw[wi, d]) for d in range(ndm)] for wi in range(len(widths))]
+    for k, e in enumerate(ev):
+        wi = int(e["width_idx"])
+        ref = cnn.candidate_tile(bw[wi], stats[wi], int(e["dm_idx"]), int(e["t_peak"]), widths[wi], ndm, nbx)
+        assert (got[k] == ref).all(), (k, widths[wi])
+
+    def us(w):
+        n = 300
+        e = np.zeros(n, dtype=L.EVENT_DTYPE)
+        e["dm_idx"], e["t_peak"] = rng.integers(0, ndm, size=n), rng.integers(0, nout - w, size=n)
+        L.find_peaks(series, ndm, nout, [w], 9.0, evb, 1 << 16, pws)
+        d = to_dev(e.view(np.uint8).copy())
+        t = torch.empty((n, 64, 256), dtype=torch.int16, device="cuda")
+        times = []
+        for _ in range(7):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(20):
+                L.triage_tiles(series, ndm, nout, [w], pws, d, n, t)
+            torch.cuda.synchronize()
+            times.append((time.perf_counter() - t0) / 20)
+        return 1e6 * sorted(times)[3]
+
+    for w, whole in ((9, 16), (17, 24), (33, 40), (65, 72)):
+        a, b = us(w), us(whole)
+        log("width", w, a, "us; width", whole, b, "us")
+        assert a <= 1.6 * b, w
