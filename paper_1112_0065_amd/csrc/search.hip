@@ -235,6 +235,16 @@ constexpr int bl_rows() {
 }
 constexpr int kBlShortRows = 4;     // of the shorter steps that follow
 constexpr int kBlTailRows = 16;     // rows of 64 outputs per step at a row's end
+// Rows with fewer outputs take the steps of a row's end alone, without the outputs
+// before a line and the long steps, and read past the row's end, which a buffer
+// load answers with 0, in place of clamping every index.  65535 rows of 300 outputs,
+// us: 80 with the long form, 45; 20000 of 1000 32 and 24, of 1500 41 and 34, of 2200
+// 52 and 48 (16-bit samples; 50 and 50 at R = 500), 32-bit samples 38 and 37 of
+// 1300, 49 and 60 of 1800.
+template <typename T>
+constexpr int64_t bl_brief() {
+    return sizeof(T) == 2 ? 2048 : 1600;
+}
 
 // Inclusive prefix sum over the 64 lanes of a wave: shifts within each row
 // of 16 lanes, then the row totals carried across rows.
@@ -351,7 +361,7 @@ __device__ __forceinline__ void bl_store(U* o, const int (&r)[4]) {
     __builtin_nontemporal_store(q, reinterpret_cast<V4*>(o));
 }
 
-template <typename T, typename U>
+template <typename T, typename U, bool SHORT>
 __global__ __launch_bounds__(kThreads) void baseline_kernel(const T* __restrict__ in, int ndm,
                                                             int64_t nout, int64_t nres, int radius,
                                                             int offset, int64_t nseg, uint32_t magic,
@@ -366,7 +376,7 @@ __global__ __launch_bounds__(kThreads) void baseline_kernel(const T* __restrict_
     U* o = out + static_cast<int64_t>(d) * nres;
     // outputs before the row's first 128-byte line of 64-element pieces; the
     // row's first wave takes them, and every segment starts on such a boundary
-    const int head = static_cast<int>(min<int64_t>(
+    const int head = SHORT ? 0 : static_cast<int>(min<int64_t>(
         -static_cast<int64_t>(reinterpret_cast<uintptr_t>(o) / sizeof(U)) & 63, nres));
     const int64_t seg = item % nseg;
     const int64_t t0 = seg == 0 ? 0 : seg * kBlSeg + head;
@@ -399,7 +409,7 @@ __global__ __launch_bounds__(kThreads) void baseline_kernel(const T* __restrict_
     }
     uint32_t wcur = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(wave_incl_scan(acc)), 63));
     int64_t tc = t0;
-    if (seg == 0 && head > 0) {
+    if (!SHORT && seg == 0 && head > 0) {
         const int t = min(lane, head - 1);
         const uint32_t bk = static_cast<uint32_t>(row[t]);
         const uint32_t fr = static_cast<uint32_t>(row[min<int64_t>(t + win, nout - 1)]);
@@ -440,8 +450,10 @@ __global__ __launch_bounds__(kThreads) void baseline_kernel(const T* __restrict_
             }
         }
     };
-    walk(std::integral_constant<int, bl_rows<T>()>{});
-    walk(std::integral_constant<int, kBlShortRows>{});
+    if (!SHORT) {
+        walk(std::integral_constant<int, bl_rows<T>()>{});
+        walk(std::integral_constant<int, kBlShortRows>{});
+    }
     // the rest, one output per lane and row.  Indices are clamped to the row;
     // the sample that enters after the row's last output lies past its end and
     // reaches no output.
@@ -450,6 +462,20 @@ __global__ __launch_bounds__(kThreads) void baseline_kernel(const T* __restrict_
         int md[kBlTailRows];
     };
     auto load = [&](Tail& q, int64_t at) {
+        if constexpr (SHORT) {
+            // loads at one offset per lane and cursor; past the row's end they read 0
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<T*>(row), 0, static_cast<int>(nout * static_cast<int64_t>(sizeof(T))), kRowRsrcWord3);
+            constexpr int sz = static_cast<int>(sizeof(T));
+            const int base = (static_cast<int>(at) + lane) * sz;
+#pragma unroll
+            for (int i = 0; i < kBlTailRows; ++i) {
+                q.bk[i] = row_load(rs, base + 64 * i * sz, static_cast<T*>(nullptr));
+                q.fr[i] = row_load(rs, base + win * sz + 64 * i * sz, static_cast<T*>(nullptr));
+                q.md[i] = static_cast<int>(row_load(rs, base + radius * sz + 64 * i * sz, static_cast<T*>(nullptr)));
+            }
+            return;
+        }
 #pragma unroll
         for (int i = 0; i < kBlTailRows; ++i) {
             const int64_t t = min<int64_t>(at + 64 * i + lane, t1 - 1);
@@ -466,6 +492,7 @@ __global__ __launch_bounds__(kThreads) void baseline_kernel(const T* __restrict_
         if (next < t1) load(nxt, next);   // in flight while this one is computed
 #pragma unroll
         for (int i = 0; i < kBlTailRows; ++i) {
+            if (SHORT && tc + 64 * i >= t1) break;
             const int64_t t = tc + 64 * i + lane;
             const uint32_t delta = cur.fr[i] - cur.bk[i];
             const uint32_t incl = wave_incl_scan(delta);
@@ -1961,9 +1988,9 @@ hipError_t launch_baseline(const void* in, int in_u16, int ndm, int64_t nout, in
     const int64_t waves = static_cast<int64_t>(ndm) * nseg;
     const dim3 grid(static_cast<unsigned>((waves + kThreads / 64 - 1) / (kThreads / 64)));
 #define DD_BL(T, U)                                                                            \
-    hipLaunchKernelGGL((baseline_kernel<T, U>), grid, dim3(kThreads), 0, s,                     \
-                       static_cast<const T*>(in), ndm, nout, nres, radius, offset, nseg, magic, \
-                       shift, static_cast<U*>(out));
+    hipLaunchKernelGGL((nres < bl_brief<T>() ? baseline_kernel<T, U, true> : baseline_kernel<T, U, false>), \
+                       grid, dim3(kThreads), 0, s, static_cast<const T*>(in), ndm, nout, nres, radius, \
+                       offset, nseg, magic, shift, static_cast<U*>(out));
     if (in_u16 && out_u16) DD_BL(uint16_t, uint16_t)
     else if (in_u16) DD_BL(uint16_t, int32_t)
     else if (out_u16) DD_BL(int32_t, uint16_t)

@@ -110,3 +110,41 @@ def test_bad_arguments():
         with pytest.raises(L.DedispError) as e:
             L.baseline_remove(s, 2, 100, r, 0, out)
         assert e.value.status == st
+
+
+@pytest.mark.parametrize("nres", [63, 64, 65, 1023, 1024, 1087, 1599, 1600, 2047, 2048])
+def test_lengths_of_short_rows(nres):
+    """Rows around a step of the short form and the lengths where it ends, windows
+    wider and narrower than the row, every output alignment."""
+    rng = np.random.default_rng(nres)
+    for radius in (0, 5, 900):
+        s = rng.integers(0, 4000, size=(5, nres + 2 * radius)).astype(np.int64)
+        ref = oracle.baseline_remove(s, radius, 3000)
+        for u16 in (True, False):
+            for o16 in (True, False):
+                got = _run(s, radius, 3000, u16, o16)
+                assert (got == ref).all(), (radius, u16, o16)
+
+
+def test_time_of_short_rows():
+    """65535 rows of 300 outputs are the samples of 1200 rows of 16384: a wave per row
+    starts 55 times as often, with one window to sum and one step each, in at most two
+    and a half times the time."""
+    import time
+    from paper_1112_0065_amd import _lib as L
+    torch = torch_dev()
+    us = []
+    for ndm, nres in ((1200, 16384), (65535, 300)):
+        s = torch.randint(100, 2000, (ndm, nres + 14), device="cuda", dtype=torch.int32).to(torch.int16)
+        out = torch.empty((ndm, nres), dtype=torch.int16, device="cuda")
+        times = []
+        for _ in range(9):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(30):
+                L.baseline_remove(s, ndm, nres + 14, 7, 3072, out)
+            torch.cuda.synchronize()
+            times.append((time.perf_counter() - t0) / 30)
+        us.append(1e6 * sorted(times)[4])
+    log("us", us)
+    assert us[1] <= 2.5 * us[0]
