@@ -231,8 +231,17 @@ __device__ __forceinline__ void neighbours(const ClusterParams& P, const int32_t
 // of coherent loads made the pass over the survey's 26669 events 70 us.
 //
 // The second walk over the friends costs S = upper_series searches per event.
-// Whole stage, us, without and with it, separate clusters and a few large ones:
-//     2500 events, S = 8       91   95        91   94
+// Whole stage, us, without and with it, separate clusters and a few large ones
+// (lists of a few clusters only below 4096 events); the two launches cost 1 to 4
+// where a list has few pairs to try, which is the lower line:
+//       64 events, S = 228      83   80
+//      500          8           86   86
+//     1100          8           92   92
+//     1100         43          133  119
+//     1100        228          275  161
+//     2800          1           84   85
+//     3900          8          103   99
+//     3900        228          165  131
 //    26669         8          145  111       147  113
 //    26669       228          214  204       241  227
 //    26669      5710         1288 1894      1783 2195   (with another union)
@@ -245,7 +254,7 @@ __device__ __forceinline__ void neighbours(const ClusterParams& P, const int32_t
 //   400000         8          282  293       323  332
 //   400000        23          414  473       477  551
 bool hook_first(int64_t n, int S) {
-    return n >= 4096 && (n <= 131072 ? S <= 512 : n * S <= (int64_t(1) << 21));
+    return n * S >= 4096 && (n <= 131072 ? S <= 512 : n * S <= (int64_t(1) << 21));
 }
 
 __global__ __launch_bounds__(kKThreads) void cluster_hook_kernel(ClusterParams P,

@@ -207,7 +207,7 @@ def test_bad_input_is_rejected():
     assert nc == len(oracle.cluster_events(ev, widths, 1, 1, 0)[1])
 
 
-@pytest.mark.parametrize("n,radius", [(4095, 5), (4098, 5), (4098, 511), (4098, 512), (131070, 511),
+@pytest.mark.parametrize("n,radius", [(681, 5), (684, 5), (4095, 5), (4098, 5), (4098, 511), (4098, 512), (131070, 511),
                                       (131070, 512), (131073, 14), (131073, 15), (262143, 7), (262146, 7)])
 def test_passes_on_both_sides_of_their_lines(n, radius):
     """n events, one third in each of trials 0, 1 and 5 at the same times, and radii
@@ -265,3 +265,29 @@ def test_time_of_a_few_large_clusters():
         us[name] = 1e6 * sorted(times)[4]
         log(name, len(ev), "events", nc, "clusters", us[name], "us")
     assert us["crowded"] <= 2.5 * us["spread"]
+
+
+@pytest.mark.parametrize("n,radii,hooked", [(18, (32, 3), True), (16, (32, 3), False), (512, (2, 1), True),
+                                            (511, (2, 1), False), (4096, (0, 0), True), (4095, (0, 0), False)])
+def test_short_lists_are_hooked_first(n, radii, hooked):
+    """n events of one crowded pulse: the trees are hooked first from 4096 pairs of an
+    event and a neighbour series on (228, 8 and 1 such series here), and the clusters
+    are the oracle's either way."""
+    torch = torch_dev()
+    from torch.profiler import ProfilerActivity, profile
+    ndm, widths = 168, [1 << i for i in range(9)]
+    r = np.random.default_rng(n)
+    slot = np.sort(r.choice(9 * 40 * 400, size=n, replace=False))
+    ev = np.zeros(n, dtype=synth.make_event_list(1, 8, 1, 1000, nclumps=1, nnoise=1).dtype)
+    ev["width_idx"], ev["dm_idx"] = slot // 16000, 64 + slot // 400 % 40
+    # runs of one series are disjoint and do not touch
+    ev["t_start"], ev["t_end"], ev["t_peak"] = (2 * (slot % 400),) * 3
+    ev["snr"], ev["b_peak"] = 6.0 + r.random(n), 2000
+    ref_l, ref = oracle.cluster_events(ev, widths, *radii, 0)
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        nc, lab, rec = _run(ev, ndm, widths, *radii, 0)
+    names = [e.key for e in prof.key_averages()]
+    assert any("cluster_link_kernel" in k for k in names), names
+    assert any("cluster_hook_kernel" in k for k in names) == hooked, names
+    assert nc == len(ref)
+    _same(lab, rec, ref_l, [dict(x) for x in ref])
