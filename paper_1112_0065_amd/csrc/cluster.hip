@@ -239,6 +239,9 @@ __device__ __forceinline__ void neighbours(const ClusterParams& P, const int32_t
 //     1100          8           92   92
 //     1100         43          133  119
 //     1100        228          275  161
+//      500        704          198  128
+//     1500        704          163  128
+//      500       2705          143  119
 //     2800          1           84   85
 //     3900          8          103   99
 //     3900        228          165  131
@@ -254,7 +257,7 @@ __device__ __forceinline__ void neighbours(const ClusterParams& P, const int32_t
 //   400000         8          282  293       323  332
 //   400000        23          414  473       477  551
 bool hook_first(int64_t n, int S) {
-    return n * S >= 4096 && (n <= 131072 ? S <= 512 : n * S <= (int64_t(1) << 21));
+    return n * S >= 4096 && (n * S <= (int64_t(1) << 21) || (n <= 131072 && S <= 512));
 }
 
 __global__ __launch_bounds__(kKThreads) void cluster_hook_kernel(ClusterParams P,

@@ -207,7 +207,8 @@ def test_bad_input_is_rejected():
     assert nc == len(oracle.cluster_events(ev, widths, 1, 1, 0)[1])
 
 
-@pytest.mark.parametrize("n,radius", [(681, 5), (684, 5), (4095, 5), (4098, 5), (4098, 511), (4098, 512), (131070, 511),
+@pytest.mark.parametrize("n,radius", [(681, 5), (684, 5), (4095, 5), (4098, 5), (4098, 511),
+                                      (4086, 512), (4098, 512), (131070, 511),
                                       (131070, 512), (131073, 14), (131073, 15), (262143, 7), (262146, 7)])
 def test_passes_on_both_sides_of_their_lines(n, radius):
     """n events, one third in each of trials 0, 1 and 5 at the same times, and radii
@@ -268,11 +269,12 @@ def test_time_of_a_few_large_clusters():
 
 
 @pytest.mark.parametrize("n,radii,hooked", [(18, (32, 3), True), (16, (32, 3), False), (512, (2, 1), True),
-                                            (511, (2, 1), False), (4096, (0, 0), True), (4095, (0, 0), False)])
+                                            (511, (2, 1), False), (4096, (0, 0), True), (4095, (0, 0), False),
+                                            (775, (300, 4), True), (776, (300, 4), False)])
 def test_short_lists_are_hooked_first(n, radii, hooked):
     """n events of one crowded pulse: the trees are hooked first from 4096 pairs of an
-    event and a neighbour series on (228, 8 and 1 such series here), and the clusters
-    are the oracle's either way."""
+    event and a neighbour series on (228, 8 and 1 such series here), with more than 512
+    such series (2705) up to 2^21 pairs, and the clusters are the oracle's either way."""
     torch = torch_dev()
     from torch.profiler import ProfilerActivity, profile
     ndm, widths = 168, [1 << i for i in range(9)]
